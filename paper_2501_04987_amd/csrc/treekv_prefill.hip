@@ -748,17 +748,31 @@ __global__ __launch_bounds__(AT_THREADS) void prefill_attend_kernel(Params p, co
 }
 
 // ---------------------------------------------------------------------------------------------
-// attend for fp32 storage: plain vector arithmetic, one query row at a time
+// attend for fp32 storage
 // ---------------------------------------------------------------------------------------------
-// The matrix pipe takes bf16; with fp32 storage the results are held to 1e-5, so this instance does the same
-// four steps (logits, row softmax, output, column sums) with fp32 multiply-adds.  A workgroup takes F32_ROWS
-// consecutive rows of one head: per row, LPR lanes share a key (16 bytes each, summed by shuffles), the scaled
-// logits and then the probabilities sit in LDS, the output is added up by (piece of the head dimension, stripe
-// of keys) and the stripes are merged through LDS; every thread keeps the column sums of the columns it owns and
-// adds them, as 2^-40 fixed point, to the unit's accumulators at the end (integer adds: order does not matter).
-// Not a fast path: the one configuration with fp32 storage decodes.
-constexpr int F32_THREADS = 256;
+// The same four steps (logits, row softmax, output, column sums) with v_mfma_f32_16x16x4_f32: fp32 operands, fp32
+// multiply-adds, so the results are held to 1e-5 as the vector ALU's would be.  A workgroup takes 16 query rows of
+// one head, wave w the 16-column blocks w, w + 8, ..; operands come straight from global memory in 16-byte lane loads,
+// because the order of a contraction is free as long as both operands agree on it:
+//   S^T = K Q^T    lane (lr, q4) loads dims 16 s + 4 q4 .. + 3 of K row lr and of Q row lr; component j of the four is
+//                  k-slot q4 of the j-th instruction.
+//   O^T += V^T P^T S^T's accumulator i of a lane is column 4 q4 + i of row lr, which is k-slot q4 of the B operand of the
+//                  instruction for those columns; its A operand is V[column 4 q4 + i][64 x + 4 lr + e], one component of
+//                  a 16-byte lane load for each of four instructions (so a lane's accumulators are 4 adjacent dims).
+// Sweep 1 forms the logits, parks them in LDS (a wave reads only what it wrote) and keeps a running (max, sum) per lane;
+// sweep 2 turns them into probabilities.  The first `park_blocks` blocks are parked (all of them up to 2048 columns); the
+// logits of the rest are formed again.
+// Bound by matrix issue (one 16x16x4 instruction is 32 cycles: 7.7 us here) and by the latency of the first blocks.
+// Measured at 8 heads x 200 tokens into 512 slots, head_dim 64: 17.9 us, against 380 us for one query row at a time on
+// the vector ALUs with shuffled dot products; the whole call 27 us against 397.
+constexpr int F32_THREADS = 512;
+constexpr int F32_WAVES = F32_THREADS / 64;
 constexpr int F32_ROWS = 16;
+constexpr int F32_PARK_BLOCKS = 128;               // 1 KB of LDS each
+constexpr int F32_MAX_COLS = 10240;                // visible columns the call accepts
+
+template <int D>
+constexpr size_t f32_merge_bytes() { return (size_t)F32_WAVES * F32_ROWS * (D + 4) * sizeof(float); }
 
 // ROPE (positions re-assigned to cache ranks): queries and keys are read, already turned to their ranks, from the scratch
 // prefill_turn_f32_kernel fills (the same memory the bf16 path keeps its two-part copies in).
@@ -766,19 +780,19 @@ template <int D, bool ROPE>
 __global__ __launch_bounds__(F32_THREADS) void prefill_attend_f32_kernel(Params p, const float* __restrict__ Q,
                                                                          const float* __restrict__ Kc,
                                                                          const float* __restrict__ Vc, int L,
-                                                                         float* __restrict__ out) {
-  constexpr int LPR = D / 4;                       // lanes per row (16 bytes each)
-  constexpr int KPP = F32_THREADS / LPR;           // keys per pass
-  extern __shared__ float f32_smem[];
-  const int unit = blockIdx.z, g = blockIdx.y, tid = threadIdx.x;
+                                                                         int park_blocks, float* __restrict__ out) {
+  constexpr int KQ = D / 16, VX = D / 64;          // 16-byte pieces per lane of a K row block, and of one V row
+  extern __shared__ __attribute__((aligned(16))) float f32_smem[];      // parked logits; at the end the waves' outputs
+  __shared__ float st[F32_WAVES][F32_ROWS][2];
+  const int unit = blockIdx.z, g = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lr = lane & 15, q4 = lane >> 4;
   const int kvh = unit % p.Hkv, b = unit / p.Hkv, h = kvh * p.G + g;
   const ChunkInfo ci = load_chunk_info(p.meta + (size_t)unit * META_STRIDE);
-  const int ncache = ci.n + 1;                     // slots [0, n], the free one masked
-  const int r0 = blockIdx.x * F32_ROWS, r1 = min(L, r0 + F32_ROWS);
-  const int ncols = ncache + r1;                   // columns any of this workgroup's rows can see
-  float* sp = f32_smem;                            // [ncols] scaled logits, then probabilities
-  float* sred = sp + ncols;                        // [F32_THREADS] reductions, then [KPP][D] output stripes
-  float* sq = sred + (KPP * D > F32_THREADS ? KPP * D : F32_THREADS);    // [D] the query row
+  const int r0 = blockIdx.x * F32_ROWS, my_row = r0 + lr;
+  const int n = ci.n, fslot = ci.fslot;
+  const int ncols = n + min(L, r0 + F32_ROWS);     // columns any of these rows sees: cached tokens, then the chunk's
+  const int nblk = (ncols + 15) / 16;
   const size_t krot_rows = (size_t)p.cap + p.max_chunk;          // turned keys: [U][cap + max_chunk][D] fp32
   const float* Ku = ROPE ? reinterpret_cast<const float*>(p.pf_krot) + (size_t)unit * krot_rows * D
                          : (const float*)p.K + (size_t)unit * p.cap * D;
@@ -789,99 +803,139 @@ __global__ __launch_bounds__(F32_THREADS) void prefill_attend_f32_kernel(Params 
   const size_t kcstride = ROPE ? (size_t)D : cstride;
   const float* Qsrc = ROPE ? reinterpret_cast<const float*>(p.pf_qrot) : Q;   // turned queries: [B][max_chunk][H][D] fp32
   const int q_rows = ROPE ? p.max_chunk : L;
-  const int grp = tid / LPR, piece = tid % LPR;
-  constexpr int OWN = 40;                          // columns a thread owns: ncols <= OWN * F32_THREADS (checked by the host)
-  float csum[OWN];
-#pragma unroll
-  for (int x = 0; x < OWN; ++x) csum[x] = 0.f;
-  auto block_reduce = [&](float v, bool take_max) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-      const float o = __shfl_xor(v, off, 64);
-      v = take_max ? fmaxf(v, o) : v + o;
-    }
-    __syncthreads();
-    if ((tid & 63) == 0) sred[tid >> 6] = v;
-    __syncthreads();
-    float r = sred[0];
-#pragma unroll
-    for (int w = 1; w < F32_THREADS / 64; ++w) r = take_max ? fmaxf(r, sred[w]) : r + sred[w];
-    __syncthreads();
-    return r;
+
+  // row of column j (past the last one: the last one, masked later); cache columns are the slots without the free one
+  auto row_of = [&](const float* cache, const float* chunk, size_t stride, int j) -> const float* {
+    j = min(j, ncols - 1);
+    return j < n ? cache + (size_t)(j + (j >= fslot ? 1 : 0)) * D : chunk + (size_t)(j - n) * stride;
   };
-  for (int i = r0; i < r1; ++i) {
-    const int nvis = ncache + i + 1;
-    if (tid < D) sq[tid] = Qsrc[(((size_t)b * q_rows + i) * p.H + h) * D + tid];
-    __syncthreads();
-    const float4 qv = *reinterpret_cast<const float4*>(sq + piece * 4);
-    // logits
-    for (int j0 = 0; j0 < nvis; j0 += KPP) {
-      const int j = j0 + grp;
-      float acc = 0.f;
-      if (j < nvis) {
-        const float* row = j < ncache ? Ku + (size_t)j * D : Kcu + (size_t)(j - ncache) * kcstride;
-        const float4 kv = *reinterpret_cast<const float4*>(row + piece * 4);
-        acc = kv.x * qv.x;
-        acc = fmaf(kv.y, qv.y, acc);
-        acc = fmaf(kv.z, qv.z, acc);
-        acc = fmaf(kv.w, qv.w, acc);
-      }
+  float4 qv[KQ], kv[KQ], kn[KQ], vv[4][VX], vn[4][VX];
+  auto load_k = [&](float4 (&k)[KQ], int blk) {
+    const float* row = row_of(Ku, Kcu, kcstride, blk * 16 + lr) + q4 * 4;
 #pragma unroll
-      for (int off = LPR / 2; off >= 1; off >>= 1) acc += __shfl_xor(acc, off, 64);
-      if (j < nvis && piece == 0) sp[j] = (j == ci.fslot && j < ncache) ? -INFINITY : acc * p.scale_log2e;
-    }
-    __syncthreads();
-    // row softmax
-    float mx = NEG_BIG;
-    for (int j = tid; j < nvis; j += F32_THREADS) mx = fmaxf(mx, sp[j]);
-    mx = block_reduce(mx, true);
-    float sum = 0.f;
-    for (int j = tid; j < nvis; j += F32_THREADS) {
-      const float e = fast_exp2(sp[j] - mx);
-      sp[j] = e;
-      sum += e;
-    }
-    sum = block_reduce(sum, false);
-    const float inv = 1.0f / sum;
+    for (int s = 0; s < KQ; ++s) k[s] = *reinterpret_cast<const float4*>(row + s * 16);
+  };
+  auto load_v = [&](float4 (&v)[4][VX], int blk) {
 #pragma unroll
-    for (int x = 0; x < OWN; ++x) {
-      const int j = tid + x * F32_THREADS;
-      if (j < nvis) {
-        const float pj = sp[j] * inv;
-        sp[j] = pj;
-        csum[x] += pj;
-      }
-    }
-    __syncthreads();
-    // output: this thread's 4 dimensions over its stripe of keys
-    float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int j = grp; j < nvis; j += KPP) {
-      const float* row = j < ncache ? Vu + (size_t)j * D : Vcu + (size_t)(j - ncache) * cstride;
-      const float4 vv = *reinterpret_cast<const float4*>(row + piece * 4);
-      const float pj = sp[j];
-      o.x = fmaf(pj, vv.x, o.x); o.y = fmaf(pj, vv.y, o.y); o.z = fmaf(pj, vv.z, o.z); o.w = fmaf(pj, vv.w, o.w);
-    }
-    *reinterpret_cast<float4*>(sred + grp * D + piece * 4) = o;
-    __syncthreads();
-    if (tid < D) {
-      float a = 0.f;
+    for (int i = 0; i < 4; ++i) {
+      const float* row = row_of(Vu, Vcu, cstride, blk * 16 + q4 * 4 + i) + lr * 4;
 #pragma unroll
-      for (int w = 0; w < KPP; ++w) a += sred[w * D + tid];
-      out[(((size_t)b * L + i) * p.H + h) * D + tid] = a;
+      for (int x = 0; x < VX; ++x) v[i][x] = *reinterpret_cast<const float4*>(row + x * 64);
     }
-    __syncthreads();
+  };
+  const int first = min(wave, nblk - 1);           // (a wave without a block loads one it does not use)
+  load_k(kv, first);
+  {
+    const float* qp = Qsrc + (((size_t)b * q_rows + min(my_row, L - 1)) * p.H + h) * D + q4 * 4;
+#pragma unroll
+    for (int s = 0; s < KQ; ++s) qv[s] = *reinterpret_cast<const float4*>(qp + s * 16);
   }
-  // the column sums of this workgroup's rows
+  // scaled logits of block `blk`: component i is column 16 blk + 4 q4 + i of row lr; what the row does not see is -inf
+  auto logits = [&](const float4 (&k)[KQ], int blk) -> f32x4_t {
+    f32x4_t a = {0.f, 0.f, 0.f, 0.f}, c = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < KQ; ++s) {
+      a = __builtin_amdgcn_mfma_f32_16x16x4f32(k[s].x, qv[s].x, a, 0, 0, 0);
+      c = __builtin_amdgcn_mfma_f32_16x16x4f32(k[s].y, qv[s].y, c, 0, 0, 0);
+      a = __builtin_amdgcn_mfma_f32_16x16x4f32(k[s].z, qv[s].z, a, 0, 0, 0);
+      c = __builtin_amdgcn_mfma_f32_16x16x4f32(k[s].w, qv[s].w, c, 0, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      a[i] = blk * 16 + q4 * 4 + i <= n + my_row ? (a[i] + c[i]) * p.scale_log2e : -INFINITY;
+    return a;
+  };
+  f32x4_t* park = reinterpret_cast<f32x4_t*>(f32_smem) + lane;
+
+  // ---- sweep 1: logits and row statistics ----
+  float m_run = NEG_BIG, l_run = 0.f;
+  for (int blk = wave; blk < nblk; blk += F32_WAVES) {
+    load_k(kn, min(blk + F32_WAVES, nblk - 1));
+    const f32x4_t s = logits(kv, blk);
+    if (blk < park_blocks) park[blk * 64] = s;
+    const float m_new = max3(m_run, fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
+    l_run = fmaf(l_run, fast_exp2(m_run - m_new), (fast_exp2(s[0] - m_new) + fast_exp2(s[1] - m_new)) +
+                                                      (fast_exp2(s[2] - m_new) + fast_exp2(s[3] - m_new)));
+    m_run = m_new;
+#pragma unroll
+    for (int x = 0; x < KQ; ++x) kv[x] = kn[x];
+  }
+  load_v(vv, first);                               // on their way while the statistics are merged
+#pragma unroll
+  for (int off = 16; off <= 32; off <<= 1) {       // the four lanes of a row, then the eight waves
+    const float mo = __shfl_xor(m_run, off, 64), lo = __shfl_xor(l_run, off, 64);
+    const float mn = fmaxf(m_run, mo);
+    l_run = l_run * fast_exp2(m_run - mn) + lo * fast_exp2(mo - mn);
+    m_run = mn;
+  }
+  if (q4 == 0) { st[wave][lr][0] = m_run; st[wave][lr][1] = l_run; }
+  __syncthreads();
+  float M = NEG_BIG, sum = 0.f;
+#pragma unroll
+  for (int w = 0; w < F32_WAVES; ++w) M = fmaxf(M, st[w][lr][0]);
+#pragma unroll
+  for (int w = 0; w < F32_WAVES; ++w) sum += st[w][lr][1] * fast_exp2(st[w][lr][0] - M);
+  const float inv = my_row < L ? 1.0f / sum : 0.f;         // rows past the chunk must not reach the column sums
+
+  // ---- sweep 2: probabilities, output, column sums ----
   const int cap_cols = (p.cap + AT_COLS - 1) / AT_COLS * AT_COLS;
   const int cs_stride = cap_cols + (p.max_chunk + AT_COLS - 1) / AT_COLS * AT_COLS;
   unsigned long long* cs_acc = p.pf_colacc + (size_t)unit * cs_stride;
+  f32x4_t o[VX][4];                                // [x][e]: component i is dim 64 x + 16 q4 + 4 i + e of row lr
 #pragma unroll
-  for (int x = 0; x < OWN; ++x) {
-    const int j = tid + x * F32_THREADS;
-    if (j < ncols && csum[x] != 0.f) {
-      const long long fix = (long long)(csum[x] * COLSUM_FIX + 0.5f);
-      atomicAdd(cs_acc + (j < ncache ? j : cap_cols + (j - ncache)), (unsigned long long)fix);
+  for (int x = 0; x < VX; ++x)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[x][e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  for (int blk = wave; blk < nblk; blk += F32_WAVES) {
+    load_v(vn, min(blk + F32_WAVES, nblk - 1));
+    f32x4_t s;
+    if (blk < park_blocks) {
+      s = park[blk * 64];
+    } else {
+      load_k(kv, blk);
+      s = logits(kv, blk);
     }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) s[i] = fast_exp2(s[i] - M) * inv;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int x = 0; x < VX; ++x) {
+        o[x][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(vv[i][x].x, s[i], o[x][0], 0, 0, 0);
+        o[x][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(vv[i][x].y, s[i], o[x][1], 0, 0, 0);
+        o[x][2] = __builtin_amdgcn_mfma_f32_16x16x4f32(vv[i][x].z, s[i], o[x][2], 0, 0, 0);
+        o[x][3] = __builtin_amdgcn_mfma_f32_16x16x4f32(vv[i][x].w, s[i], o[x][3], 0, 0, 0);
+      }
+    // lane lr < 4 of every lane group passes on column 4 q4 + lr (integer adds: the order does not matter)
+    const float c0 = row16_sum(s[0]), c1 = row16_sum(s[1]), c2 = row16_sum(s[2]), c3 = row16_sum(s[3]);
+    const float cs = lr == 0 ? c0 : lr == 1 ? c1 : lr == 2 ? c2 : c3;
+    const int j = blk * 16 + q4 * 4 + lr;
+    if (lr < 4 && j < ncols && cs != 0.f) {
+      const long long fix = (long long)(cs * COLSUM_FIX + 0.5f);
+      atomicAdd(cs_acc + (j < n ? j + (j >= fslot ? 1 : 0) : cap_cols + (j - n)), (unsigned long long)fix);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int x = 0; x < VX; ++x) vv[i][x] = vn[i][x];
+  }
+  // ---- add the waves' outputs ----
+  __syncthreads();                                 // the parked logits are done with
+  constexpr int OS = D + 4;                        // row stride: 16 lanes' 16-byte stores fall into different banks
+  float* xo = f32_smem + (size_t)(wave * F32_ROWS + lr) * OS + q4 * 16;
+#pragma unroll
+  for (int x = 0; x < VX; ++x)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      *reinterpret_cast<float4*>(xo + x * 64 + i * 4) = make_float4(o[x][0][i], o[x][1][i], o[x][2][i], o[x][3][i]);
+  __syncthreads();
+  for (int y = tid; y < F32_ROWS * D; y += F32_THREADS) {
+    const int row = y / D, col = y % D;
+    if (r0 + row >= L) break;                      // rows ascend with y
+    float a = 0.f;
+#pragma unroll
+    for (int w = 0; w < F32_WAVES; ++w) a += f32_smem[(size_t)(w * F32_ROWS + row) * OS + col];
+    out[(((size_t)b * L + r0 + row) * p.H + h) * D + col] = a;
   }
 }
 
@@ -1349,14 +1403,14 @@ __global__ __launch_bounds__(256) void prefill_turn_f32_kernel(Params p, const f
   *reinterpret_cast<float4*>(dst + part * 4) = y;
 }
 
-// fp32 storage: the vector-arithmetic attend, then the same replay.
+// fp32 storage: the fp32 matrix attend, then the same replay.
 template <int D>
 int launch_prefill_f32(const Params& p, const void* Q, const void* K, const void* V, int L, float* out,
                        int32_t* retained, int32_t* n_retained, int32_t* evicted, hipStream_t s) {
   const size_t ncols = (size_t)p.cap + L;
-  if (ncols > 40 * (size_t)F32_THREADS) return TREEKV_EUNSUPPORTED;      // a thread owns at most 40 columns' sums
-  constexpr int KPP = F32_THREADS / (D / 4);
-  const size_t lds = (ncols + (KPP * D > F32_THREADS ? KPP * D : F32_THREADS) + D) * sizeof(float);
+  if (ncols > (size_t)F32_MAX_COLS) return TREEKV_EUNSUPPORTED;
+  const int blocks = (int)((ncols + 15) / 16), park = blocks < F32_PARK_BLOCKS ? blocks : F32_PARK_BLOCKS;
+  const size_t lds = (size_t)park * 1024 > f32_merge_bytes<D>() ? (size_t)park * 1024 : f32_merge_bytes<D>();
   const bool rope = (p.flags & TREEKV_POSITION_RERANK) != 0;
   if (rope) {
     const int rows = p.budget + L + L * p.G;           // at most: every cached key, the chunk's keys and queries
@@ -1368,7 +1422,7 @@ int launch_prefill_f32(const Params& p, const void* Q, const void* K, const void
       hip_failed(hipFuncSetAttribute((const void*)attend, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)))
     return TREEKV_EHIP;
   hipLaunchKernelGGL(attend, dim3((L + F32_ROWS - 1) / F32_ROWS, p.G, p.U), dim3(F32_THREADS), lds, s, p, (const float*)Q,
-                     (const float*)K, (const float*)V, L, out);
+                     (const float*)K, (const float*)V, L, park, out);
   return launch_replay(p, K, V, L, retained, n_retained, evicted, s);
 }
 

@@ -154,3 +154,13 @@ def test_prefill_fp32_degenerate_and_keep_left(binding, oracle):
          seed=15, kind="iid", dtype="f32")
     _run(binding, oracle, [30, 30, 10, 30], B=1, H=2, Hkv=2, d=128, budget=40, n_sink=0, n_recent=8, max_chunk=32,
          flags=binding.TREEKV_KEEP_LEFT | binding.TREEKV_SCORE_ACCUMULATED, seed=16, kind="iid", dtype="f32")
+
+
+@pytest.mark.parametrize("d,budget,schedule", [
+    (64, 47, [1, 15, 16, 17, 33, 0, 48, 31]),            # row tiles and column blocks of 16, one short, exact, one over
+    (128, 127, [127, 1, 2, 129, 0, 16]),                 # fills to one slot short of the budget, then over it
+    (64, 2060, [2033, 15, 40, 0, 17]),                   # 2048 columns are parked in LDS; more are formed twice
+])
+def test_prefill_fp32_tile_edges(binding, oracle, d, budget, schedule):
+    _run(binding, oracle, schedule, B=1, H=2, Hkv=1, d=d, budget=budget, n_sink=1, n_recent=budget // 3,
+         max_chunk=max(schedule), seed=17, kind="iid", dtype="f32")
