@@ -177,8 +177,8 @@ int treekv_decode_step_static(treekv_ctx* ctx, const void* q, const void* k, con
  *   retained   [B, Hkv, c] int32, n_retained [B, Hkv] (may be NULL): as above
  *   evicted    [B, Hkv, len] int32 (may be NULL): position evicted when the
  *              chunk's i-th token was appended, or -1
- * With bf16 storage the two contractions run on the matrix pipe; with fp32 storage
- * they run, row by row, on the vector ALUs (held to 1e-5, not a fast path), for at most
+ * With bf16 storage the two contractions run on the bf16 matrix instructions; with fp32
+ * storage on the fp32 ones (held to 1e-5), for at most
  * 10240 visible columns (budget + 1 + len; TREEKV_EUNSUPPORTED beyond).
  */
 int treekv_prefill_chunk(treekv_ctx* ctx, const void* Q, const void* K, const void* V, int len,

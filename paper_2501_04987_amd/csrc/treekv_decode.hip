@@ -6,10 +6,10 @@
 //          in LDS, scores and tree positions are prefetched into registers before the streaming
 //          starts, so the epilogue (score update, eviction, retained list) waits for no global
 //          load.  Used when U alone fills the chip.
-//   SPLIT  two kernels.  grid = (nsplit, U) workgroups of 512 threads each stream a slice of the
-//          unit's slots and write a partial (output accumulator, max, sum) plus the slice's
-//          logits to scratch; a second kernel with one workgroup per unit merges the slices and
-//          runs the same epilogue.  The kernel boundary is the only synchronisation.
+//   SPLIT  one kernel too.  grid = (nsplit, U) workgroups of 512 threads each stream a slice of the unit's
+//          slots and write a partial (output accumulator, max, sum) plus the slice's logits to scratch; the workgroup
+//          of a unit that is done last merges the slices and runs the epilogue (see decode_split_kernel).  No
+//          workgroup ever waits for another one.
 //
 // Streaming.  Rows are 16-byte lane loads: LPR lanes cover one row, a wave load covers 64/LPR
 // whole rows, a tile is KU wave loads of K and of V, double buffered.  q.k is reduced inside
@@ -38,7 +38,6 @@ constexpr int FUSED_THREADS = 512;
 // context's full table in memory (budgets whose small tables would not fit)
 enum : int { ROPE_OFF = 0, ROPE_LDS = 1, ROPE_MEM = 2 };
 constexpr int SPLIT_THREADS = 512;
-constexpr int MERGE_THREADS = 1024;
 constexpr int KU = 2;                  // wave loads of K (and of V) per tile (4: measured slower)
 constexpr float NEG_BIG = -1.0e30f;
 // Iteration (of n) of the streaming loop at which a workgroup issues its mid-stream stores.  Measured: the
@@ -695,66 +694,19 @@ __device__ inline void merge_stats(const float* pm, const float* pl, int nparts,
 }
 
 // ---------------------------------------------------------------------------------------------
-// Epilogue shared by both shapes: Algorithm 1's score update and eviction block, the retained
-// list, and the append of the new row.  `logit(g, slot)` returns the scaled logit; M, invL per g.
-// EP > 0: the first EP old scores per thread come in registers, and the caller has already written
-// the retained list except for the one entry this step's decision fills in.
-// With EP > 0, `park` (LDS, may alias the logits of head 0) receives every new score and the decision reads
-// its two operands from there; with EP == 0 the two owners leave them in sm_sc.
-// A wave issues an instruction every five cycles or so and nothing else runs at this point, so this code is
-// laid out for a short instruction stream per wave: uniform exits from the unrolled loops, and the dozen
-// bookkeeping stores dealt to lane 0 of different waves.  The k, v rows are held by the last LPR threads.
+// The eviction block, once every new score is known: `sl` and `sr` are the scope's two scores.  Taken alike by lane 0 of
+// the first four waves, to which the dozen bookkeeping stores are dealt, and by the thread `ret_patch_tid`, which
+// fills in the one retained entry that was open until now; the caller lets everyone else go.
 // ---------------------------------------------------------------------------------------------
-template <typename T, int D, int G, int THREADS, int EP, class LogitFn>
-__device__ inline void epilogue(const Params& p, int unit, const Step& st, const float (&M)[G], const float (&invL)[G],
-                                LogitFn logit, const float* s_old, uint4 knew_r, uint4 vnew_r, float* sm_sc, float* park,
-                                int32_t* __restrict__ retained, int32_t* __restrict__ n_retained,
-                                int32_t* __restrict__ evicted, int* meta, int ret_patch_tid) {
-  constexpr int LPR = D / Storage<T>::EPL;
-  static_assert(THREADS >= 256 && LPR <= 64, "the bookkeeping stores are dealt to four waves");
+__device__ inline void settle(const Params& p, int unit, const Step& st, float sl, float sr,
+                              int32_t* __restrict__ retained, int32_t* __restrict__ n_retained,
+                              int32_t* __restrict__ evicted, int* meta, int ret_patch_tid) {
   const int tid = threadIdx.x;
-  float* Su = p.S + (size_t)unit * p.cap;
   int* Eu = p.E + (size_t)unit * 2 * p.m;
   int* PEu = p.PE + (size_t)unit * 2 * p.m;
   int* Ru = p.R + (size_t)unit * max(p.n_recent, 1);
-
-  auto prob = [&](int slot) -> float {
-    float a = 0.f;
-#pragma unroll
-    for (int g = 0; g < G; ++g) a += fast_exp2(logit(g, slot) - M[g]) * invL[g];
-    return a;
-  };
-  auto put_score = [&](int slot, float sn) {
-    __builtin_nontemporal_store(sn, Su + slot);    // read again only a whole step later
-    if constexpr (EP > 0) park[slot] = sn;
-    else {
-      if (slot == st.scope_l) sm_sc[0] = sn;
-      if (slot == st.scope_r) sm_sc[1] = sn;
-    }
-  };
-#pragma unroll
-  for (int x = 0; x < EP; ++x) {
-    if (x * THREADS >= st.n1) break;                 // uniform
-    const int slot = tid + x * THREADS;
-    if (slot < st.n1) put_score(slot, s_old[x] + prob(slot));
-  }
-  for (int slot = tid + EP * THREADS; slot < st.n1; slot += THREADS)
-    put_score(slot, (slot == st.fslot ? 0.f : Su[slot]) + prob(slot));
-  // the new token's k, v become cache rows
-  if (tid >= THREADS - LPR) {
-    T* Kw = (T*)p.K + ((size_t)unit * p.cap + st.fslot) * D;
-    T* Vw = (T*)p.V + ((size_t)unit * p.cap + st.fslot) * D;
-    reinterpret_cast<uint4*>(Kw)[tid - (THREADS - LPR)] = knew_r;
-    reinterpret_cast<uint4*>(Vw)[tid - (THREADS - LPR)] = vnew_r;
-  }
-  __syncthreads();
-
-  // lane 0 of the first four waves and the owner of the open retained entry take the same decision from the
-  // same two numbers; everyone else is done
-  if (EP > 0 && !((tid & 63) == 0 && tid < 256) && tid != ret_patch_tid) return;
   bool drop_right = false;
   if (st.evict) {
-    const float sl = EP > 0 ? park[st.scope_l] : sm_sc[0], sr = EP > 0 ? park[st.scope_r] : sm_sc[1];
     const bool averaged = !(p.flags & TREEKV_SCORE_ACCUMULATED);
     const float bl = averaged ? sl / (float)(st.t - st.pos_l + 1) : sl;
     const float br = averaged ? sr / (float)(st.t - st.pos_r + 1) : sr;
@@ -788,15 +740,56 @@ __device__ inline void epilogue(const Params& p, int unit, const Step& st, const
       PEu[p.m + st.j0] = st.newcomer_pos;
     }
   }
+  if (st.evict && tid == ret_patch_tid) retained[(size_t)unit * p.budget + p.n_sink + st.j0] = surv_pos;
+}
 
-  // retained positions in ascending order
-  int32_t* ret = retained + (size_t)unit * p.budget;
-  if constexpr (EP > 0) {
-    // the rest was written up front; the same thread that wrote this entry's old value patches it
-    if (st.evict && tid == ret_patch_tid) ret[p.n_sink + st.j0] = surv_pos;
-  } else {
-    for (int i = tid; i < p.budget; i += THREADS) ret[i] = position_of(p, st, PEu, i, surv_pos, true);
+// ---------------------------------------------------------------------------------------------
+// Epilogue of the fused shape: Algorithm 1's score update, the append of the new row, and the eviction block.
+// `logit(g, slot)` returns the scaled logit; M, invL per g.  The first EP old scores per thread come in registers, and
+// the caller has already written the retained list except for the one entry this step's decision fills in.
+// `park` (LDS, may alias the logits of head 0) receives every new score and the decision reads its two operands there.
+// A wave issues an instruction every five cycles or so and nothing else runs at this point, so this code is
+// laid out for a short instruction stream per wave: uniform exits from the unrolled loops, and the dozen
+// bookkeeping stores dealt to lane 0 of different waves.  The k, v rows are held by the last LPR threads.
+// ---------------------------------------------------------------------------------------------
+template <typename T, int D, int G, int THREADS, int EP, class LogitFn>
+__device__ inline void epilogue(const Params& p, int unit, const Step& st, const float (&M)[G], const float (&invL)[G],
+                                LogitFn logit, const float* s_old, uint4 knew_r, uint4 vnew_r, float* park,
+                                int32_t* __restrict__ retained, int32_t* __restrict__ n_retained,
+                                int32_t* __restrict__ evicted, int* meta, int ret_patch_tid) {
+  constexpr int LPR = D / Storage<T>::EPL;
+  static_assert(THREADS >= 256 && LPR <= 64, "the bookkeeping stores are dealt to four waves");
+  const int tid = threadIdx.x;
+  float* Su = p.S + (size_t)unit * p.cap;
+  auto prob = [&](int slot) -> float {
+    float a = 0.f;
+#pragma unroll
+    for (int g = 0; g < G; ++g) a += fast_exp2(logit(g, slot) - M[g]) * invL[g];
+    return a;
+  };
+  auto put_score = [&](int slot, float sn) {
+    __builtin_nontemporal_store(sn, Su + slot);    // read again only a whole step later
+    park[slot] = sn;
+  };
+#pragma unroll
+  for (int x = 0; x < EP; ++x) {
+    if (x * THREADS >= st.n1) break;                 // uniform
+    const int slot = tid + x * THREADS;
+    if (slot < st.n1) put_score(slot, s_old[x] + prob(slot));
   }
+  for (int slot = tid + EP * THREADS; slot < st.n1; slot += THREADS)
+    put_score(slot, (slot == st.fslot ? 0.f : Su[slot]) + prob(slot));
+  // the new token's k, v become cache rows
+  if (tid >= THREADS - LPR) {
+    T* Kw = (T*)p.K + ((size_t)unit * p.cap + st.fslot) * D;
+    T* Vw = (T*)p.V + ((size_t)unit * p.cap + st.fslot) * D;
+    reinterpret_cast<uint4*>(Kw)[tid - (THREADS - LPR)] = knew_r;
+    reinterpret_cast<uint4*>(Vw)[tid - (THREADS - LPR)] = vnew_r;
+  }
+  __syncthreads();
+  if (!((tid & 63) == 0 && tid < 256) && tid != ret_patch_tid) return;
+  settle(p, unit, st, st.evict ? park[st.scope_l] : 0.f, st.evict ? park[st.scope_r] : 0.f, retained, n_retained, evicted,
+         meta, ret_patch_tid);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -817,7 +810,6 @@ __global__ __launch_bounds__(FUSED_THREADS) void decode_fused_kernel(Params p, c
   float* sm_wm = sm_acc + WAVES * G * D;
   float* sm_wl = sm_wm + WAVES * G;
   float* sm_s = smem + St::LDS_FLOATS_FIXED;   // [G][cap]
-  __shared__ float sm_sc[2];
 
   const int unit = blockIdx.x, tid = threadIdx.x;
   int* meta = p.meta + (size_t)unit * META_STRIDE;
@@ -886,7 +878,7 @@ __global__ __launch_bounds__(FUSED_THREADS) void decode_fused_kernel(Params p, c
   const int ret_i = p.n_sink + st.j0;
   const int ret_owner = (ret_i < 4 * EP4 * THREADS ? ret_i / 4 : ret_i) % THREADS;
   epilogue<T, D, G, THREADS, EP>(p, unit, st, M, invL, [&](int g, int slot) { return sm_s[(size_t)g * p.cap + slot]; },
-                                 s_old, knew_r, vnew_r, sm_sc, sm_s, retained, n_retained, evicted, meta, ret_owner);
+                                 s_old, knew_r, vnew_r, sm_s, retained, n_retained, evicted, meta, ret_owner);
   // the attention output: last, and by the highest threads, whose waves have no bookkeeping stores to issue
   const int kvh = unit % p.Hkv, b = unit / p.Hkv;
   for (int i = THREADS - 1 - tid; i < G * D; i += THREADS) {
@@ -898,125 +890,235 @@ __global__ __launch_bounds__(FUSED_THREADS) void decode_fused_kernel(Params p, c
   }
 }
 
+// What the workgroups of a unit exchange inside one kernel goes through relaxed agent-scope atomics: such a store is
+// written through to memory and such a load does not stop at a cache another XCD's stores bypass, so no cache has to be
+// written back or invalidated (an agent-scope fence does that to the whole L2, once per workgroup: measured 5x slower).
+__device__ inline void put_shared(float* dst, float v) {
+  __hip_atomic_store(reinterpret_cast<unsigned*>(dst), __float_as_uint(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline void put_shared2(float* dst, float a, float b) {          // dst: 8-byte aligned
+  __hip_atomic_store(reinterpret_cast<unsigned long long*>(dst),
+                     (unsigned long long)__float_as_uint(a) | (unsigned long long)__float_as_uint(b) << 32,
+                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline float get_shared(const float* src) {
+  return __uint_as_float(__hip_atomic_load(reinterpret_cast<const unsigned*>(src), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+__device__ inline float2 get_shared2(const float* src) {
+  const unsigned long long v =
+      __hip_atomic_load(reinterpret_cast<const unsigned long long*>(src), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return make_float2(__uint_as_float((unsigned)v), __uint_as_float((unsigned)(v >> 32)));
+}
+
+// The same in 16-byte pieces, for which the language has no atomic: a buffer access with the cache policy an agent-scope
+// atomic has on this chip (sc1).  A piece is read only after all of it has been written (see below), so that it need not
+// be indivisible.
+typedef __attribute__((ext_vector_type(4))) unsigned u32x4_t;
+constexpr int CPOL_SC1 = 16;
+__device__ inline __amdgpu_buffer_rsrc_t shared_rsrc(const float* base, size_t floats) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), 0, (int)(floats * sizeof(float)), 0x00027000);
+}
+__device__ inline void put_shared4(__amdgpu_buffer_rsrc_t r, int float_index, float a, float b, float c, float d) {
+  const u32x4_t v = {__float_as_uint(a), __float_as_uint(b), __float_as_uint(c), __float_as_uint(d)};
+  __builtin_amdgcn_raw_buffer_store_b128(v, r, float_index * 4, 0, CPOL_SC1);
+}
+__device__ inline float4 get_shared4(__amdgpu_buffer_rsrc_t r, int float_index) {
+  const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(r, float_index * 4, 0, CPOL_SC1);
+  return make_float4(__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w));
+}
+
+// SPLIT shape.  Every workgroup streams its slice, leaves its partial result and its logits ([slot][G]) in scratch, counts
+// itself in and writes its share of the retained list (all but the entry the decision fills in); the one that finds
+// all others counted merges.  Order: a wave's scratch stores have reached memory (s_waitcnt vmcnt(0)) before
+// the workgroup's barrier, the barrier is before the count, and the count's old value is known before the last
+// workgroup's first load; every access to the scratch and the counter is an agent-scope atomic.  All reads of state the
+// epilogue overwrites (rows, bookkeeping words, order arrays) are over when the unit's last workgroup counts itself in.
+// The merge is latency and the length of one workgroup's instruction stream: everything it needs is requested in one go,
+// and code that would spare it loads (the own slice's logits from LDS, the old scores requested mid-stream) was slower by
+// more than it saved.  32 units x 1024 slots: 9.6 us per step, of which the merge is 2.7 (13.1 with the merge as a second
+// kernel of one workgroup per unit); 128 units x 4096 slots x G = 4: 53.0 us, merge 5 (56.3).
 template <typename T, int D, int G, int ROPE>
 __global__ __launch_bounds__(SPLIT_THREADS) void decode_split_kernel(Params p, const T* __restrict__ q_in,
                                                                      const T* __restrict__ k_in,
-                                                                     const T* __restrict__ v_in) {
+                                                                     const T* __restrict__ v_in,
+                                                                     float* __restrict__ out,
+                                                                     int32_t* __restrict__ retained,
+                                                                     int32_t* __restrict__ n_retained,
+                                                                     int32_t* __restrict__ evicted) {
   constexpr int THREADS = SPLIT_THREADS;
   using St = typename PickStream<T, D, G, THREADS, ROPE>::type;
   constexpr int WAVES = St::WAVES;
+  constexpr int LPR = D / Storage<T>::EPL;
+  constexpr int MAX_SPLITS = 64;
   extern __shared__ __attribute__((aligned(16))) float smem[];
   float* sm_acc = smem;
   float* sm_wm = sm_acc + WAVES * G * D;
   float* sm_wl = sm_wm + WAVES * G;
   float* sm_s = smem + St::LDS_FLOATS_FIXED;   // [G][rows_per_split]
+  __shared__ float2 sm_ml[MAX_SPLITS * G];
+  __shared__ float sm_sc[2];
+  __shared__ int sm_last;
 
   const int split = blockIdx.x, unit = blockIdx.y, tid = threadIdx.x;
-  const int* meta = p.meta + (size_t)unit * META_STRIDE;
+  int* meta = p.meta + (size_t)unit * META_STRIDE;
+  const int* PEu = p.PE + (size_t)unit * 2 * p.m;
+  const T* knew = k_in + (size_t)unit * D;
+  const T* vnew = v_in + (size_t)unit * D;
   Step st;
   int begin, end;
-  St::run(p, unit, split * p.rows_per_split, q_in, k_in + (size_t)unit * D, v_in + (size_t)unit * D, meta, sm_s,
-          p.rows_per_split, sm_acc, sm_wm, sm_wl, st, begin, end, false, [](const Step&) {}, []() {});
+  St::run(p, unit, split * p.rows_per_split, q_in, knew, vnew, meta, sm_s, p.rows_per_split, sm_acc, sm_wm, sm_wl, st, begin,
+          end, false, [](const Step&) {}, []() {});
+  // the eviction scope, and this slice's share of the retained list: on their way while the waves' results are merged
+  load_scope(p, st, p.E + (size_t)unit * 2 * p.m, PEu, p.R + (size_t)unit * max(p.n_recent, 1));
+  const int ret_n = (p.budget + p.nsplit - 1) / p.nsplit, ret_0 = split * ret_n, ret_1 = min(ret_0 + ret_n, p.budget);
+  constexpr int RET = 4;                       // entries a thread requests up front
+  int pe_pre[RET];
+#pragma unroll
+  for (int x = 0; x < RET; ++x) {
+    const int i = ret_0 + tid + x * THREADS;
+    if (i < ret_1) pe_pre[x] = position_of(p, st, PEu, i, -1, true);
+  }
   __syncthreads();
-  float* part = p.partial + ((size_t)unit * p.nsplit + split) * G * (D + 2);
+
+  // ---- this slice's results -> scratch ----
+  float* parts = p.partial + (size_t)unit * p.nsplit * G * (D + 2);
+  float* lg = p.logits + (size_t)unit * G * p.cap;
+  const __amdgpu_buffer_rsrc_t lg_rsrc = shared_rsrc(lg, (size_t)G * p.cap);
+  for (int r = tid; r < end - begin; r += THREADS) {
+    float* dst = lg + (size_t)(begin + r) * G;
+    if constexpr (G == 1) put_shared(dst, sm_s[r]);
+    else if constexpr (G == 2) put_shared2(dst, sm_s[r], sm_s[(size_t)p.rows_per_split + r]);
+    else
+#pragma unroll
+      for (int g = 0; g < G; g += 4) {
+        const float* src = sm_s + (size_t)g * p.rows_per_split + r;
+        put_shared4(lg_rsrc, (begin + r) * G + g, src[0], src[p.rows_per_split], src[2 * p.rows_per_split], src[3 * p.rows_per_split]);
+      }
+  }
   for (int i = tid; i < G * D; i += THREADS) {
     const int g = i / D, col = i % D;
     float M, L;
     merge_stats(sm_wm + g, sm_wl + g, WAVES, G, M, L);
     float a = 0.f;
     for (int w = 0; w < WAVES; ++w) a += sm_acc[(w * G + g) * D + col] * fast_exp2(sm_wm[w * G + g] - M);
-    part[(size_t)g * (D + 2) + col] = a;
-    if (col == 0) { part[(size_t)g * (D + 2) + D] = M; part[(size_t)g * (D + 2) + D + 1] = L; }
+    float* part = parts + ((size_t)split * G + g) * (D + 2);
+    put_shared(part + col, a);
+    if (col == 0) put_shared2(part + D, M, L);
   }
-  float* lg = p.logits + (size_t)unit * G * p.cap;
-  for (int g = 0; g < G; ++g)
-    for (int r = tid; r < end - begin; r += THREADS) lg[(size_t)g * p.cap + begin + r] = sm_s[(size_t)g * p.rows_per_split + r];
-}
-
-// Second kernel of the SPLIT shape: one workgroup per unit.  Latency is all that matters here, so
-// everything the epilogue needs (the slices' logits, the old scores, the tree positions) is requested in one
-// go right after the bookkeeping words, the logits are parked in LDS, and from there on the kernel is the
-// tail of the fused one.
-template <typename T, int D, int G, bool LOGITS_IN_LDS>
-__global__ __launch_bounds__(MERGE_THREADS) void decode_merge_kernel(Params p, const T* __restrict__ k_in,
-                                                                     const T* __restrict__ v_in,
-                                                                     float* __restrict__ out,
-                                                                     int32_t* __restrict__ retained,
-                                                                     int32_t* __restrict__ n_retained,
-                                                                     int32_t* __restrict__ evicted) {
-  constexpr int THREADS = MERGE_THREADS;
-  // slots / list entries per thread served from registers (none when the logits do not fit in LDS: huge budgets)
-  constexpr int EP = LOGITS_IN_LDS ? 5 * 1024 / THREADS : 0;
-  constexpr int LPR = D / Storage<T>::EPL;
-  extern __shared__ __attribute__((aligned(16))) float smem[];              // [G][cap] logits
-  __shared__ float sm_sc[2];
-  const int unit = blockIdx.x, tid = threadIdx.x;
-  int* meta = p.meta + (size_t)unit * META_STRIDE;
-  const int* PEu = p.PE + (size_t)unit * 2 * p.m;
-  const float* Su = p.S + (size_t)unit * p.cap;
-  const float* lg = p.logits + (size_t)unit * G * p.cap;
-  Step st = load_meta(p, meta);
-
-  float s_old[EP > 0 ? EP : 1], lreg[EP > 0 ? EP : 1][G];
-  int pe_pre[EP > 0 ? EP : 1];
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (tid == 0)
+    sm_last = __hip_atomic_fetch_add(meta + META_ARRIVED, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == p.nsplit - 1;
+  {
+    int32_t* ret = retained + (size_t)unit * p.budget;
+    const int open = st.evict ? p.n_sink + st.j0 : -1;       // the last workgroup's to write, and nobody else's
 #pragma unroll
-  for (int x = 0; x < EP; ++x) {
-    const int slot = tid + x * THREADS;
-    const bool live = slot < st.n1;
-    s_old[x] = (live && slot != st.fslot) ? Su[slot] : 0.f;
+    for (int x = 0; x < RET; ++x) {
+      const int i = ret_0 + tid + x * THREADS;
+      if (i < ret_1 && i != open) ret[i] = pe_pre[x];
+    }
+    for (int i = ret_0 + RET * THREADS + tid; i < ret_1; i += THREADS)
+      if (i != open) ret[i] = position_of(p, st, PEu, i, -1, true);   // (no entry the last workgroup writes is read here)
+  }
+  __syncthreads();
+  if (!sm_last) return;
+
+  // ---- the unit's last workgroup: every load of the merge, then its arithmetic ----
+  float* Su = p.S + (size_t)unit * p.cap;
+  float2 ml = make_float2(NEG_BIG, 0.f);
+  if (tid < p.nsplit * G) ml = get_shared2(parts + (size_t)tid * (D + 2) + D);     // entry tid is slice tid / G, head tid % G
+  constexpr int EPB = G <= 4 ? 9 : 4;          // slots a thread takes in one go: budgets up to 4607 in one (G <= 4)
+  float s_old[EPB], lo[EPB][G];
+  auto request = [&](int base) {
 #pragma unroll
-    for (int g = 0; g < G; ++g) lreg[x][g] = live ? lg[(size_t)g * p.cap + slot] : 0.f;
-    pe_pre[x] = position_of(p, st, PEu, slot, -1, true);
+    for (int x = 0; x < EPB; ++x) {
+      if (base + x * THREADS >= st.n1) break;           // uniform
+      const int slot = base + x * THREADS + tid;
+      if (slot < st.n1) {
+        s_old[x] = slot != st.fslot ? Su[slot] : 0.f;
+        const float* src = lg + (size_t)slot * G;
+        if constexpr (G == 1) lo[x][0] = get_shared(src);
+        else if constexpr (G == 2) { const float2 v = get_shared2(src); lo[x][0] = v.x; lo[x][1] = v.y; }
+        else
+#pragma unroll
+          for (int g = 0; g < G; g += 4) {
+            const float4 v = get_shared4(lg_rsrc, slot * G + g);
+            lo[x][g] = v.x; lo[x][g + 1] = v.y; lo[x][g + 2] = v.z; lo[x][g + 3] = v.w;
+          }
+      }
+    }
+  };
+  request(0);
+  constexpr int OPT = (G * D + THREADS - 1) / THREADS, OPS = 8 / OPT;    // outputs per thread; slices of them requested up front
+  float o_pre[OPT][OPS];
+#pragma unroll
+  for (int y = 0; y < OPT; ++y) {
+    const int i = tid + y * THREADS, g = i / D, col = i % D;
+#pragma unroll
+    for (int s = 0; s < OPS; ++s)
+      o_pre[y][s] = i < G * D && s < p.nsplit ? get_shared(parts + ((size_t)s * G + g) * (D + 2) + col) : 0.f;
   }
   uint4 knew_r = make_uint4(0, 0, 0, 0), vnew_r = knew_r;
   if (tid >= THREADS - LPR) {
-    knew_r = reinterpret_cast<const uint4*>(k_in + (size_t)unit * D)[tid - (THREADS - LPR)];
-    vnew_r = reinterpret_cast<const uint4*>(v_in + (size_t)unit * D)[tid - (THREADS - LPR)];
+    knew_r = reinterpret_cast<const uint4*>(knew)[tid - (THREADS - LPR)];
+    vnew_r = reinterpret_cast<const uint4*>(vnew)[tid - (THREADS - LPR)];
   }
-  load_scope(p, st, p.E + (size_t)unit * 2 * p.m, PEu, p.R + (size_t)unit * max(p.n_recent, 1));
-
-  const float* parts = p.partial + (size_t)unit * p.nsplit * G * (D + 2);
+  if (tid < p.nsplit * G) sm_ml[tid] = ml;
+  __syncthreads();
   float M[G], invL[G];
 #pragma unroll
   for (int g = 0; g < G; ++g) {
-    float L;
-    merge_stats(parts + (size_t)g * (D + 2) + D, parts + (size_t)g * (D + 2) + D + 1, p.nsplit, G * (D + 2), M[g], L);
-    invL[g] = 1.0f / L;
+    float mx = NEG_BIG, l = 0.f;
+    for (int s = 0; s < p.nsplit; ++s) mx = fmaxf(mx, sm_ml[s * G + g].x);
+    for (int s = 0; s < p.nsplit; ++s) l += sm_ml[s * G + g].y * fast_exp2(sm_ml[s * G + g].x - mx);
+    M[g] = mx;
+    invL[g] = 1.0f / l;
+  }
+  for (int base = 0; base < st.n1; base += EPB * THREADS) {
+    if (base > 0) request(base);
+#pragma unroll
+    for (int x = 0; x < EPB; ++x) {
+      if (base + x * THREADS >= st.n1) break;           // uniform
+      const int slot = base + x * THREADS + tid;
+      if (slot < st.n1) {
+        float sn = s_old[x];
+        float a = 0.f;
+#pragma unroll
+        for (int g = 0; g < G; ++g) a += fast_exp2(lo[x][g] - M[g]) * invL[g];
+        sn += a;
+        __builtin_nontemporal_store(sn, Su + slot);     // read again only a whole step later
+        if (slot == st.scope_l) sm_sc[0] = sn;
+        if (slot == st.scope_r) sm_sc[1] = sn;
+      }
+    }
+  }
+  if (tid >= THREADS - LPR) {                  // the new token's k, v become cache rows
+    T* Kw = (T*)p.K + ((size_t)unit * p.cap + st.fslot) * D;
+    T* Vw = (T*)p.V + ((size_t)unit * p.cap + st.fslot) * D;
+    reinterpret_cast<uint4*>(Kw)[tid - (THREADS - LPR)] = knew_r;
+    reinterpret_cast<uint4*>(Vw)[tid - (THREADS - LPR)] = vnew_r;
   }
   const int kvh = unit % p.Hkv, b = unit / p.Hkv;
-  for (int i = tid; i < G * D; i += THREADS) {
-    const int g = i / D, col = i % D;
-    float a = 0.f;
-    for (int s = 0; s < p.nsplit; ++s) {
-      const float* ps = parts + ((size_t)s * G + g) * (D + 2);
-      a += ps[col] * fast_exp2(ps[D] - M[g]);
-    }
-    out[((size_t)b * p.H + (size_t)kvh * G + g) * D + col] = a * invL[g];
-  }
-  // logits -> LDS, retained list (all but the entry the decision fills)
-  int32_t* ret = retained + (size_t)unit * p.budget;
 #pragma unroll
-  for (int x = 0; x < EP; ++x) {
-    const int slot = tid + x * THREADS;
-    if (slot < p.cap) {
+  for (int y = 0; y < OPT; ++y) {
+    const int i = tid + y * THREADS, g = i / D, col = i % D;
+    if (i < G * D) {
+      float mx = M[0], il = invL[0];
 #pragma unroll
-      for (int g = 0; g < G; ++g) smem[(size_t)g * p.cap + slot] = lreg[x][g];
+      for (int x = 1; x < G; ++x) { mx = g == x ? M[x] : mx; il = g == x ? invL[x] : il; }
+      float a = 0.f;
+#pragma unroll
+      for (int s = 0; s < OPS; ++s)
+        if (s < p.nsplit) a += o_pre[y][s] * fast_exp2(sm_ml[s * G + g].x - mx);
+      for (int s = OPS; s < p.nsplit; ++s)
+        a += get_shared(parts + ((size_t)s * G + g) * (D + 2) + col) * fast_exp2(sm_ml[s * G + g].x - mx);
+      out[((size_t)b * p.H + (size_t)kvh * G + g) * D + col] = a * il;
     }
-    if (slot < p.budget) ret[slot] = pe_pre[x];
   }
-  if constexpr (LOGITS_IN_LDS) {
-    for (int slot = tid + EP * THREADS; slot < st.n1; slot += THREADS)
-      for (int g = 0; g < G; ++g) smem[(size_t)g * p.cap + slot] = lg[(size_t)g * p.cap + slot];
-    for (int i = tid + EP * THREADS; i < p.budget; i += THREADS) ret[i] = position_of(p, st, PEu, i, -1, true);
-    __syncthreads();
-    epilogue<T, D, G, THREADS, EP>(p, unit, st, M, invL, [&](int g, int slot) { return smem[(size_t)g * p.cap + slot]; },
-                                   s_old, knew_r, vnew_r, sm_sc, smem, retained, n_retained, evicted, meta,
-                                   (p.n_sink + st.j0) % THREADS);
-  } else {
-    (void)ret;
-    epilogue<T, D, G, THREADS, 0>(p, unit, st, M, invL, [&](int g, int slot) { return lg[(size_t)g * p.cap + slot]; },
-                                  nullptr, knew_r, vnew_r, sm_sc, nullptr, retained, n_retained, evicted, meta, -1);
-  }
+  if (tid == 0) __hip_atomic_store(meta + META_ARRIVED, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();
+  if ((tid & 63) != 0 || tid >= 256) return;
+  settle(p, unit, st, sm_sc[0], sm_sc[1], retained, n_retained, evicted, meta, 192);
 }
 
 template <typename T, int D, int G, int ROPE>
@@ -1042,18 +1144,8 @@ int launch_decode_g(const Params& p, const void* q, const void* k, const void* v
     if (lds > 48 * 1024 &&
         hip_failed(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)))
       return TREEKV_EHIP;
-    hipLaunchKernelGGL(kern, dim3(p.nsplit, p.U), dim3(SPLIT_THREADS), lds, s, p, qt, kt, vt);
-    const size_t mlds = (size_t)G * p.cap * sizeof(float);
-    if (mlds <= LDS_LIMIT) {
-      auto merge = decode_merge_kernel<T, D, G, true>;
-      if (mlds > 48 * 1024 &&
-          hip_failed(hipFuncSetAttribute((const void*)merge, hipFuncAttributeMaxDynamicSharedMemorySize, (int)mlds)))
-        return TREEKV_EHIP;
-      hipLaunchKernelGGL(merge, dim3(p.U), dim3(MERGE_THREADS), mlds, s, p, kt, vt, out, retained, n_retained, evicted);
-    } else {
-      hipLaunchKernelGGL((decode_merge_kernel<T, D, G, false>), dim3(p.U), dim3(MERGE_THREADS), 0, s, p, kt, vt, out,
-                         retained, n_retained, evicted);
-    }
+    hipLaunchKernelGGL(kern, dim3(p.nsplit, p.U), dim3(SPLIT_THREADS), lds, s, p, qt, kt, vt, out, retained, n_retained,
+                       evicted);
   }
   return finish_launch();
 }

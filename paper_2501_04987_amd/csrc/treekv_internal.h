@@ -15,6 +15,7 @@ enum MetaField : int {
   META_J = 2,      // 0-based eviction index inside the tree region (the paper's idx - 1)
   META_RHEAD = 3,  // oldest entry of the recent-window ring
   META_T = 4,      // tokens processed so far == position of the next token
+  META_ARRIVED = 5,   // workgroups of the decode kernel in flight that are done with their slice (0 between kernels)
   META_STRIDE = 8
 };
 
@@ -45,8 +46,8 @@ struct Params {
   int* PE;                  // [U][2m] positions of the tree region
   int* R;                   // [U][max(n_recent,1)]
   int* meta;                // [U][META_STRIDE]
-  float* logits;            // [U][G][cap]   decode scratch: scaled logits (log2 domain)
-  float* partial;           // [U][nsplit][G][D+2] decode scratch: split-KV partial (acc, max, sum)
+  float* logits;            // [U][cap][G]   split decode scratch: scaled logits (log2 domain)
+  float* partial;           // [U][nsplit][G][D+2] split decode scratch: a slice's partial (acc, max, sum)
   // prefill scratch
   unsigned long long* pf_colacc;   // [U][cache columns | chunk columns, each rounded up to 128] column sums of the chunk in flight, fixed point
   float* pf_snew;           // [U][max_chunk] accumulated S of the chunk's tokens

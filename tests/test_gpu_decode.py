@@ -196,3 +196,47 @@ def test_accumulated_weight_criterion(binding, oracle):
              n_sink=3, n_recent=30, flags=binding.TREEKV_SCORE_ACCUMULATED, kv_splits=splits, seed=21)
     _run(binding, oracle, kind="iid", T=300, B=1, H=2, Hkv=2, d=64, dtype="f32", budget=40, n_sink=0, n_recent=0,
          flags=binding.TREEKV_SCORE_ACCUMULATED, seed=22)
+
+
+@pytest.mark.parametrize("G,d,dtype,budget,splits", [
+    (1, 128, "bf16", 1030, 12),      # more slices than a merging thread requests up front
+    (8, 128, "bf16", 2100, 3),       # two outputs per merging thread, slots beyond its first batch (2048)
+    (4, 64, "bf16", 4700, 2),        # slots beyond the first batch (4608)
+    (2, 64, "f32", 515, 5),          # a retained list no slice boundary divides evenly
+])
+def test_split_merge_edges(binding, oracle, G, d, dtype, budget, splits):
+    """Slices merged by the unit's last workgroup: every step's outputs, evictions and retained list."""
+    fill, steps = [512] * (budget // 512) + [budget % 512], 6
+    T = budget + steps
+    Q, K, V = inputs.batch_streams("lowrank" if dtype == "bf16" else "iid", 41, T, 1, 2, G, d, dtype=dtype)
+    kv = binding.TreeKV(budget, 2 * G, d, kv_heads=2, dtype=dtype, n_sink=3, n_recent=budget // 3, kv_splits=splits)
+    assert kv.cfg.kv_splits == splits
+    st = ph.run_schedule(oracle, kv, Q, K, V, fill + [0] * steps, dtype=dtype)
+    assert st["flagged"] <= 2
+    ph.compare_scores(kv, st["results"], dtype)
+
+
+def test_split_shape_in_a_captured_graph(binding):
+    """Replays count the slices in and out again: several of them, with other work between, equal the plain calls."""
+    import torch
+
+    T, B, H, d, budget = 60, 2, 4, 128, 40
+    Q, K, V = inputs.batch_streams("lowrank", 42, T, B, 2, 2, d, dtype="bf16")
+    Qd, Kd, Vd = (ph.to_device(x, "bf16") for x in (Q, K, V))
+    a, b = (binding.TreeKV(budget, H, d, kv_heads=2, batch=B, n_sink=2, n_recent=6, kv_splits=3) for _ in range(2))
+    oa, ob = a.new_outputs(), b.new_outputs()
+    x = [t[0].clone() for t in (Qd, Kd, Vd)]
+    g, s = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    b.decode_step(*x, *ob)                                    # token 0, not captured
+    a.decode_step(*x, *oa)
+    torch.cuda.synchronize()
+    with torch.cuda.graph(g, stream=s):
+        b.decode_step(*x, *ob)
+    for t in range(1, T):
+        for dst, src in zip(x, (Qd, Kd, Vd)):
+            dst.copy_(src[t])
+        a.decode_step(*x, *oa)
+        g.replay()
+        torch.cuda.synchronize()
+        for u, v in zip(oa, ob):
+            assert torch.equal(u, v), t
