@@ -9,7 +9,7 @@
 // magnitudes are averaged over the d columns (lane-local, then across the lanes that share a row) and leave
 // through a small LDS tile as whole rows of the output.
 //
-//   wavelet_components_kernel   grid (ceil(t / 512), heads) x 256 threads -> per_head [heads][levels][t]
+//   wavelet_components_kernel   grid (ceil(t / 128), heads) x 256 threads -> per_head [heads][levels][t]
 //   wavelet_mean_kernel         grid ceil(levels * t / 32) x 1024 threads -> mean [levels][t], heads added in a fixed order
 
 #include "treekv_internal.h"
@@ -21,12 +21,52 @@ constexpr int WV_THREADS = 256;
 constexpr int WV_WAVES = WV_THREADS / 64;
 constexpr int WV_BLOCK = 32;          // rows per wave pass = 2^5, the deepest level
 constexpr int WV_LEVELS = 5;
-constexpr int WV_ITERS = 4;           // 32-row blocks a wave takes, 128 rows apart
+
+template <int N> struct IntTag { static constexpr int value = N; };
+
+template <int CTRL>
+__device__ inline float dpp_add(float v) {
+  const int moved = __builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false);
+  return v + __int_as_float(moved);
+}
+// Sum over the LPR consecutive lanes that share rows; every lane of the group gets the total.
+template <int LPR>
+__device__ inline float group_sum(float v) {
+  if constexpr (LPR == 8) {
+    v = dpp_add<0x141>(v);           // row_half_mirror: i <-> 7-i
+    v = dpp_add<0x1B>(v);            // quad_perm [3,2,1,0]
+    v = dpp_add<0xB1>(v);            // quad_perm [1,0,3,2]
+  } else {
+    v = dpp_add<0x128>(v);           // row_ror:8 (rotate inside each 16-lane row)
+    v = dpp_add<0x124>(v);           // row_ror:4
+    v = dpp_add<0x122>(v);           // row_ror:2
+    v = dpp_add<0x121>(v);           // row_ror:1
+    if constexpr (LPR == 32) v += __shfl_xor(v, 16, 64);
+  }
+  return v;
+}
+// The value of this lane and of the lane STRIDE away (index xor STRIDE), without LDS where the chip can swap lane rows.
+template <int STRIDE>
+__device__ inline float2 lane_pair(float v) {
+  if constexpr (STRIDE == 16 || STRIDE == 32) {
+    const unsigned x = __float_as_uint(v);
+    const auto r = STRIDE == 16 ? __builtin_amdgcn_permlane16_swap(x, x, false, false)
+                                : __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    return make_float2(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  } else {
+    return make_float2(v, __shfl_xor(v, STRIDE, 64));
+  }
+}
 
 constexpr int ilog2(int x) { return x <= 1 ? 0 : 1 + ilog2(x / 2); }
 
+// Bound by the read of V.  What hides its latency is waves, not requests ahead within one: a wave takes one 32-row block,
+// registers are capped for 6 waves per SIMD (2 for 512-byte rows, whose lanes hold 16 rows each), V is read with the
+// non-temporal hint, and lanes exchange through DPP and row swaps instead of LDS.  8192 heads x 512 x 128 bf16, 5 levels:
+// 188 us = 6.2 TB/s; with four blocks per wave and the next one requested ahead, 3 waves per SIMD, 230 us (212 at 4 waves,
+// 201 with the hint and without LDS exchanges, 196 with two blocks per wave).
 template <typename T, int D>
-__global__ __launch_bounds__(WV_THREADS) void wavelet_components_kernel(const float* __restrict__ a,
+__global__ __launch_bounds__(WV_THREADS, sizeof(T) * D > 256 ? 2 : 6) void wavelet_components_kernel(const float* __restrict__ a,
                                                                         const T* __restrict__ V, int t, int levels,
                                                                         float* __restrict__ per_head) {
   constexpr int EPL = Storage<T>::EPL;
@@ -42,144 +82,153 @@ __global__ __launch_bounds__(WV_THREADS) void wavelet_components_kernel(const fl
   const int head = blockIdx.y;
   const T* Vh = V + (size_t)head * t * D;
   const float* ah = a + (size_t)head * t;
-  constexpr int STRIDE = WV_WAVES * WV_BLOCK;                      // rows a workgroup covers per iteration
-  const int first = blockIdx.x * WV_ITERS * STRIDE + wave * WV_BLOCK;   // wave uniform
+  const int base = (blockIdx.x * WV_WAVES + wave) * WV_BLOCK;      // wave uniform
+  if (base >= t) return;
 
-  // the rows of one block: 16 bytes of V and the weight per row, requested one block ahead of their use
-  uint4 raw[RPLN], raw_next[RPLN];
-  float w[RPLN], w_next[RPLN];
-  auto request = [&](uint4 (&r)[RPLN], float (&wt)[RPLN], int base) {
+  // 16 bytes of V and the weight of each of the lane's rows, all requested at once
+  uint4 raw[RPLN];
+  float w[RPLN];
 #pragma unroll
-    for (int j = 0; j < RPLN; ++j) {
-      const int row = base + ri * RPLN + j;
-      const int rc = min(row, t - 1);
-      r[j] = *reinterpret_cast<const uint4*>(Vh + (size_t)rc * D + li * EPL);
-      wt[j] = row < t ? ah[rc] : 0.f;                            // rows past the end count as zero
-    }
-  };
-  if (first < t) request(raw, w, first);
+  for (int j = 0; j < RPLN; ++j) {
+    typedef unsigned v4u __attribute__((ext_vector_type(4)));
+    const int row = base + ri * RPLN + j, rc = min(row, t - 1);
+    const v4u v = __builtin_nontemporal_load(reinterpret_cast<const v4u*>(Vh + (size_t)rc * D + li * EPL));
+    raw[j] = make_uint4(v.x, v.y, v.z, v.w);
+    w[j] = row < t ? ah[rc] : 0.f;                               // rows past the end count as zero
+  }
+  // s = a o V for this lane's rows and columns
+  float x[RPLN][EPL];
 #pragma unroll
-  for (int it = 0; it < WV_ITERS; ++it) {
-    const int base = first + it * STRIDE;
-    const bool live = base < t;                                    // wave uniform
-    if (it + 1 < WV_ITERS && base + STRIDE < t) request(raw_next, w_next, base + STRIDE);
-    if (live) {
-      // s = a o V for this lane's rows and columns
-      float x[RPLN][EPL];
+  for (int j = 0; j < RPLN; ++j) {
+    float vf[EPL];
+    Storage<T>::widen(raw[j], vf);
 #pragma unroll
-      for (int j = 0; j < RPLN; ++j) {
-        float vf[EPL];
-        Storage<T>::widen(raw[j], vf);
+    for (int e = 0; e < EPL; ++e) x[j][e] = w[j] * vf[e];
+  }
+  // levels inside the lane: pairwise differences and sums; |difference| added over the lane's columns
+  float mag_in[RPLN];                 // RPLN >> l entries per level l = 1.., one level after the other
 #pragma unroll
-        for (int e = 0; e < EPL; ++e) x[j][e] = w[j] * vf[e];
+  for (int i = 0; i < RPLN; ++i) mag_in[i] = 0.f;
+  float top[EPL];                     // sum of the lane's rows, per column
+#pragma unroll
+  for (int e = 0; e < EPL; ++e) {
+    float s[RPLN];
+#pragma unroll
+    for (int j = 0; j < RPLN; ++j) s[j] = x[j][e];
+    int off = 0;
+#pragma unroll
+    for (int l = 1; l <= IN; ++l) {
+      const int n = RPLN >> l;
+#pragma unroll
+      for (int m = 0; m < n; ++m) {
+        const float lo = s[2 * m], hi = s[2 * m + 1];
+        mag_in[off + m] += fabsf(lo - hi);
+        s[m] = lo + hi;
       }
-      // levels inside the lane: pairwise differences and sums; |difference| added over the lane's columns
-      float mag_in[RPLN];                 // RPLN >> l entries per level l = 1.., one level after the other
-#pragma unroll
-      for (int i = 0; i < RPLN; ++i) mag_in[i] = 0.f;
-      float top[EPL];                     // sum of the lane's rows, per column
+      off += n;
+    }
+    top[e] = s[0];
+  }
+  // levels across row groups
+  float mag_x[WV_LEVELS - IN];
+  auto cross = [&](auto level) {
+    constexpr int l = decltype(level)::value;
+    if constexpr (l < WV_LEVELS - IN) {
+      float acc = 0.f;
 #pragma unroll
       for (int e = 0; e < EPL; ++e) {
-        float s[RPLN];
-#pragma unroll
-        for (int j = 0; j < RPLN; ++j) s[j] = x[j][e];
-        int off = 0;
-#pragma unroll
-        for (int l = 1; l <= IN; ++l) {
-          const int n = RPLN >> l;
-#pragma unroll
-          for (int m = 0; m < n; ++m) {
-            const float lo = s[2 * m], hi = s[2 * m + 1];
-            mag_in[off + m] += fabsf(lo - hi);
-            s[m] = lo + hi;
-          }
-          off += n;
-        }
-        top[e] = s[0];
+        const float2 h = lane_pair<(LPR << l)>(top[e]);
+        acc += fabsf(h.x - h.y);
+        top[e] = h.x + h.y;
       }
-      // levels across row groups
-      float mag_x[WV_LEVELS - IN];
-#pragma unroll
-      for (int l = 0; l < WV_LEVELS - IN; ++l) {
-        float acc = 0.f;
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) {
-          const float other = __shfl_xor(top[e], LPR << l, 64);
-          acc += fabsf(top[e] - other);
-          top[e] += other;
-        }
-        mag_x[l] = acc;
-      }
-      // add over the lanes that share the rows
-#pragma unroll
-      for (int o = 1; o < LPR; o <<= 1) {
-#pragma unroll
-        for (int i = 0; i < RPLN - 1; ++i) mag_in[i] += __shfl_xor(mag_in[i], o, 64);
-#pragma unroll
-        for (int l = 0; l < WV_LEVELS - IN; ++l) mag_x[l] += __shfl_xor(mag_x[l], o, 64);
-      }
-      // |Rec(D_l)| = 2^-l |first half - second half|, the same for all 2^l rows of the block; mean over the D columns
-      if (li == 0) {
-        int off = 0;
-#pragma unroll
-        for (int l = 1; l <= IN; ++l) {
-          const int n = RPLN >> l;
-          const float f = 1.0f / (float)((1 << l) * D);
-#pragma unroll
-          for (int m = 0; m < n; ++m)
-#pragma unroll
-            for (int r = 0; r < (1 << l); ++r) tile[wave][l - 1][ri * RPLN + (m << l) + r] = mag_in[off + m] * f;
-          off += n;
-        }
-#pragma unroll
-        for (int l = 0; l < WV_LEVELS - IN; ++l) {
-          const float f = 1.0f / (float)((1 << (IN + 1 + l)) * D);
-#pragma unroll
-          for (int r = 0; r < RPLN; ++r) tile[wave][IN + l][ri * RPLN + r] = mag_x[l] * f;
-        }
-      }
-      // the tile is this wave's own: written and read by the same wave, in program order
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      for (int i = lane; i < levels * WV_BLOCK; i += 64) {
-        const int l = i / WV_BLOCK, r = i % WV_BLOCK;
-        if (base + r < t) per_head[((size_t)head * levels + l) * t + base + r] = tile[wave][l][r];
-      }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
+      mag_x[l] = acc;
     }
-    if (it + 1 < WV_ITERS) {
+  };
+  cross(IntTag<0>{}); cross(IntTag<1>{}); cross(IntTag<2>{}); cross(IntTag<3>{});
+  // add over the lanes that share the rows
 #pragma unroll
-      for (int j = 0; j < RPLN; ++j) { raw[j] = raw_next[j]; w[j] = w_next[j]; }
+  for (int i = 0; i < RPLN - 1; ++i) mag_in[i] = group_sum<LPR>(mag_in[i]);
+#pragma unroll
+  for (int l = 0; l < WV_LEVELS - IN; ++l) mag_x[l] = group_sum<LPR>(mag_x[l]);
+  // |Rec(D_l)| = 2^-l |first half - second half|, the same for all 2^l rows of the block; mean over the D columns
+  if (li == 0) {
+    int off = 0;
+#pragma unroll
+    for (int l = 1; l <= IN; ++l) {
+      const int n = RPLN >> l;
+      const float f = 1.0f / (float)((1 << l) * D);
+#pragma unroll
+      for (int m = 0; m < n; ++m)
+#pragma unroll
+        for (int r = 0; r < (1 << l); ++r) tile[wave][l - 1][ri * RPLN + (m << l) + r] = mag_in[off + m] * f;
+      off += n;
     }
+#pragma unroll
+    for (int l = 0; l < WV_LEVELS - IN; ++l) {
+      const float f = 1.0f / (float)((1 << (IN + 1 + l)) * D);
+#pragma unroll
+      for (int r = 0; r < RPLN; ++r) tile[wave][IN + l][ri * RPLN + r] = mag_x[l] * f;
+    }
+  }
+  // the tile is this wave's own: written and read by the same wave, in program order
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  for (int i = lane; i < levels * WV_BLOCK; i += 64) {
+    const int l = i / WV_BLOCK, r = i % WV_BLOCK;
+    if (base + r < t) per_head[((size_t)head * levels + l) * t + base + r] = tile[wave][l][r];
   }
 }
 
-// Mean over the heads: a workgroup owns 32 adjacent outputs (whole 128-byte lines); 32 head lanes each add every 32nd head, then a fixed
-// tree over the lanes: the order of the additions depends on nothing but `heads`.
-constexpr int MEAN_COLS = 32, MEAN_LANES = 32;
-__global__ __launch_bounds__(MEAN_COLS * MEAN_LANES) void wavelet_mean_kernel(const float* __restrict__ per_head,
-                                                                              int heads, int n, float* __restrict__ mean) {
-  __shared__ float red[MEAN_LANES][MEAN_COLS];
-  const int tx = threadIdx.x % MEAN_COLS, ty = threadIdx.x / MEAN_COLS;
-  const int i = blockIdx.x * MEAN_COLS + tx;
-  float acc = 0.f;
-  if (i < n)
-#pragma unroll 8
-    for (int h = ty; h < heads; h += MEAN_LANES) acc += per_head[(size_t)h * n + i];
-  red[ty][tx] = acc;
-  __syncthreads();
-  for (int half = MEAN_LANES / 2; half >= 1; half >>= 1) {
-    if (ty < half) red[ty][tx] += red[ty + half][tx];
-    __syncthreads();
+// Mean over the heads: a workgroup owns 32 adjacent outputs (whole 128-byte lines); its threads, VEC outputs each, share out the heads, then the
+// head lanes of a wave and the waves are added in a fixed order, which depends on nothing but `heads`.
+// Bound by the bytes a compute unit can have in flight (the grid is one workgroup per 32 outputs, 80 at 5 levels of 512):
+// with 16-byte loads, 16 of them per thread, 256 KB.  At 8192 heads 22 us (84 MB, most of it still in the memory-side cache,
+// because the components kernel reads V past it); 35 us with 4-byte loads, 31 us with 16 outputs (64-byte pieces of
+// a head's row) per workgroup.
+constexpr int MEAN_COLS = 32, MEAN_THREADS = 1024;
+template <int VEC>
+__global__ __launch_bounds__(MEAN_THREADS) void wavelet_mean_kernel(const float* __restrict__ per_head, int heads, int n,
+                                                                    float* __restrict__ mean) {
+  constexpr int TX = MEAN_COLS / VEC, LANES = MEAN_THREADS / TX, WAVES = MEAN_THREADS / 64;
+  __shared__ float red[WAVES][MEAN_COLS];
+  const int tid = threadIdx.x, tx = tid % TX, ty = tid / TX;
+  const int i = blockIdx.x * MEAN_COLS + tx * VEC;
+  float acc[VEC];
+#pragma unroll
+  for (int e = 0; e < VEC; ++e) acc[e] = 0.f;
+  if (i < n) {
+#pragma unroll 16
+    for (int h = ty; h < heads; h += LANES) {
+      const float* src = per_head + (size_t)h * n + i;
+      if constexpr (VEC == 4) {
+        const float4 v = *reinterpret_cast<const float4*>(src);
+        acc[0] += v.x; acc[1] += v.y; acc[2] += v.z; acc[3] += v.w;
+      } else {
+        acc[0] += *src;
+      }
+    }
   }
-  if (ty == 0 && i < n) mean[i] = red[0][tx] / (float)heads;
+#pragma unroll
+  for (int o = TX; o < 64; o <<= 1)
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) acc[e] += __shfl_xor(acc[e], o, 64);
+  if (tid % 64 < TX) {
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) red[tid / 64][tx * VEC + e] = acc[e];
+  }
+  __syncthreads();
+  if (tid < MEAN_COLS && blockIdx.x * MEAN_COLS + tid < n) {
+    float sum = 0.f;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) sum += red[w][tid];
+    mean[blockIdx.x * MEAN_COLS + tid] = sum / (float)heads;
+  }
 }
 
 template <typename T, int D>
 void launch_components(const float* a, const void* V, int heads, int t, int levels, float* per_head, hipStream_t s) {
-  const int rows = WV_BLOCK * WV_WAVES * WV_ITERS;
+  const int rows = WV_BLOCK * WV_WAVES;
   const int blocks = (t + rows - 1) / rows;
   hipLaunchKernelGGL((wavelet_components_kernel<T, D>), dim3(blocks, heads), dim3(WV_THREADS), 0, s, a, (const T*)V, t,
                      levels, per_head);
@@ -196,7 +245,9 @@ int launch_wavelet(const float* a, const void* V, int dtype, int heads, int t, i
   else return TREEKV_EUNSUPPORTED;
   if (mean) {
     const int n = levels * t;
-    hipLaunchKernelGGL(wavelet_mean_kernel, dim3((n + MEAN_COLS - 1) / MEAN_COLS), dim3(MEAN_COLS * MEAN_LANES), 0, s, per_head, heads, n, mean);
+    // 16-byte loads need whole groups of four outputs in every head's row
+    auto kern = n % 4 == 0 && (reinterpret_cast<uintptr_t>(per_head) & 15) == 0 ? wavelet_mean_kernel<4> : wavelet_mean_kernel<1>;
+    hipLaunchKernelGGL(kern, dim3((n + MEAN_COLS - 1) / MEAN_COLS), dim3(MEAN_THREADS), 0, s, per_head, heads, n, mean);
   }
   return finish_launch();
 }

@@ -96,3 +96,17 @@ def test_wavelet_benchmark_size_sampled(binding, oracle):
         want = oracle.wavelet_components(ah.astype(np.float64), Vh, levels)
         bound = 2e-6 * float(np.abs(ah[:, None] * Vh).max())
         np.testing.assert_allclose(per_head[h].cpu().numpy(), want, rtol=1e-5, atol=bound)
+
+
+@pytest.mark.parametrize("heads,t,levels", [(300, 6, 1), (33, 34, 1), (700, 32, 5)])
+def test_wavelet_mean_over_heads_edges(binding, heads, t, levels):
+    """Outputs that are no multiple of the mean's 16-byte loads or of its 32 columns, heads that end inside its lanes.
+    At most 1024 products are added in fp32, in a tree of short sums: 1e-5 relative is far above their rounding."""
+    import torch
+
+    g = torch.Generator(device="cuda").manual_seed(heads)
+    a = torch.rand(heads, t, device="cuda", generator=g)
+    V = torch.randn(heads, t, 64, device="cuda", generator=g)
+    per_head, mean = binding.wavelet_components(a, V, levels)
+    torch.cuda.synchronize()
+    assert torch.allclose(mean.double(), per_head.double().mean(0), rtol=1e-5, atol=0.0)
