@@ -95,6 +95,35 @@ __device__ inline float row16_sum(float v) {
   v = dpp_add<0x121>(v);           // row_ror:1
   return v;
 }
+// Sums of eight values over the 16 lanes of a DPP row, shared out: lane lr gets those of x[2 (lr / 4)] and x[2 (lr / 4) + 1].
+// Halving the values with the lanes (a masked add writes one value's sum into half of the lanes, another value's into
+// the other half) takes 16 adds where eight full sums take 32.  One statement, because the instructions' distances are
+// part of it: two wait states between the write of a register and its use through DPP.
+__device__ inline float2 row16_sum8(const float (&x)[8]) {
+  float s0, s1, r0, r1, r2, r3;
+  asm("s_nop 1\n\t"
+      "v_add_f32_dpp %2, %6, %6 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+      "v_add_f32_dpp %3, %7, %7 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+      "v_add_f32_dpp %4, %8, %8 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+      "v_add_f32_dpp %5, %9, %9 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+      "v_add_f32_dpp %2, %10, %10 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %3, %11, %11 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %4, %12, %12 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %5, %13, %13 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %0, %2, %2 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+      "v_add_f32_dpp %1, %3, %3 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+      "v_add_f32_dpp %0, %4, %4 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+      "v_add_f32_dpp %1, %5, %5 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+      "s_nop 0\n\t"
+      "v_add_f32_dpp %0, %0, %0 quad_perm:[3,2,1,0] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %1, %1, %1 quad_perm:[3,2,1,0] row_mask:0xf bank_mask:0xf\n\t"
+      "s_nop 0\n\t"
+      "v_add_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %1, %1, %1 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf"
+      : "=&v"(s0), "=&v"(s1), "=&v"(r0), "=&v"(r1), "=&v"(r2), "=&v"(r3)
+      : "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "v"(x[4]), "v"(x[5]), "v"(x[6]), "v"(x[7]));
+  return make_float2(s0, s1);
+}
 // max of three.  This file is compiled with -fno-honor-nans: otherwise every fmaxf operand that comes out of
 // an MFMA costs an extra instruction that quiets signalling NaNs, and the pair is not fused into v_max3_f32.
 __device__ inline float max3(float a, float b, float c) { return fmaxf(fmaxf(a, b), c); }
@@ -181,8 +210,12 @@ __device__ inline unsigned lds_address(const void* shared_ptr) {
 // product).  The staging memory then holds one tile pair (hi, lo) where the plain kernel holds two tiles: sweep 1
 // requests one tile ahead instead of three, and sweep 2 has a second barrier per tile (the K pair is requested once
 // every wave has formed its logits from it).  Everything after the logits is unchanged.
+//
+// head_dim 64 leaves room for two workgroups per compute unit (66 KB of LDS each) if the registers are held to 128, at the
+// price of a few spills: 8 KV heads x 4 x 2 sequences of 6000 tokens into 4096 slots 1406 -> 1343 us, and with the shorter
+// instruction stream 1057.
 template <int D, bool ROPE>
-__global__ __launch_bounds__(AT_THREADS) void prefill_attend_kernel(Params p, const uint16_t* __restrict__ Q,
+__global__ __launch_bounds__(AT_THREADS, D == 64 ? 4 : 2) void prefill_attend_kernel(Params p, const uint16_t* __restrict__ Q,
                                                                     const uint16_t* __restrict__ Kc,
                                                                     const uint16_t* __restrict__ Vc, int L,
                                                                     int row_tiles, float* __restrict__ out) {
@@ -217,7 +250,9 @@ __global__ __launch_bounds__(AT_THREADS) void prefill_attend_kernel(Params p, co
   const int cq = wave >> 1;                                // sweep 2: column quarter of every tile
   const int kvh = unit % p.Hkv, b = unit / p.Hkv;
   const int h = kvh * p.G + g;
-  const ChunkInfo ci = load_chunk_info(p.meta + (size_t)unit * META_STRIDE);
+  ChunkInfo ci = load_chunk_info(p.meta + (size_t)unit * META_STRIDE);
+  ci.n = __builtin_amdgcn_readfirstlane(ci.n);             // tile addresses are scalar arithmetic on these two
+  ci.fslot = __builtin_amdgcn_readfirstlane(ci.fslot);
   const int rbase = row_tile * ROW_TILE;                   // first chunk row of the workgroup
 
   // B operands: the Q rows of the four 16-row blocks (rows past the chunk repeat its last row)
@@ -262,45 +297,46 @@ __global__ __launch_bounds__(AT_THREADS) void prefill_attend_kernel(Params p, co
   // multiple of 16 rows, so the swizzle of a lane's row depends on x and a_lrow only.
   static_assert(CPW * RPC == 16, "a wave covers 16 rows of every tile");
   const int a_lrow = lane / PARTS, a_slot = lane % PARTS;
-  auto issue_tile = [&](const uint16_t* cache_src, const uint16_t* chunk_src, int chunk_stride, int tile, uint16_t* stage,
+  // A tile wholly inside the cache, whose 16 rows for this wave do not straddle the free slot, is one run of requests from
+  // one scalar base: nearly every tile, so its address costs some 20 scalar instructions (47 when all cases shared one
+  // computation; two waves per SIMD issue them all, and with the shorter column sums that is 64.8 -> 59.4 us for the
+  // kernel at 512 tokens into 2048 slots).
+  const int full_tiles = ci.n / AT_COLS;
+  const unsigned lds_wave = __builtin_amdgcn_readfirstlane(lds_address(pf_smem)) + wave * CPW * 1024;
+  auto issue_tile = [&](const uint16_t* cache_src, const uint16_t* chunk_src, int chunk_stride, int tile, int stage,
                         auto swz) {
+    const int cw = tile * AT_COLS + wave * 16;            // first column of this wave's 16 (wave uniform)
+    const unsigned m0 = lds_wave + stage * (Lds::TILE_ELEMS * 2);
+    auto piece = [&](int x) { return (unsigned)((a_slot ^ swz(x * RPC + a_lrow)) * 16); };
+    if (tile < full_tiles && (unsigned)(fslot - 1 - cw) >= 15u) {
+      // Cache rows are contiguous, like their LDS image: one scalar base and one M0 for the run of requests;
+      // the per-lane offsets differ only in the swizzled piece.
+      const unsigned lane_row = (unsigned)a_lrow * ROWB;
+      const int row = __builtin_amdgcn_readfirstlane(cw + (cw >= fslot ? 1 : 0));
+      const char* sbase = reinterpret_cast<const char*>(cache_src) + (size_t)row * ROWB;
+      if constexpr (CPW == 4) async_copy16_run(sbase, m0, lane_row + piece(0), lane_row + piece(1), lane_row + piece(2), lane_row + piece(3));
+      else async_copy16_run(sbase, m0, lane_row + piece(0), lane_row + piece(1));
+      return;
+    }
     const bool is_cache = tile < cache_tiles;
-    const int col0 = is_cache ? tile * AT_COLS : (tile - cache_tiles) * AT_COLS;
+    const int col_w = is_cache ? cw : cw - cache_tiles * AT_COLS;
     const uint16_t* base = is_cache ? cache_src : chunk_src;
     const int rstride = is_cache ? D : chunk_stride;
     const int lim = is_cache ? cache_lim : chunk_lim;
-    const int col_w = col0 + wave * 16;                   // first column of this wave's 16 (wave uniform)
-    // cache columns at and after the free slot sit one row further on
-    const int shift = (is_cache && col_w >= fslot) ? 1 : 0;
-    const bool straddles = is_cache && col_w < fslot && fslot <= col_w + 15;
-    const int row_w = col_w + shift;                      // first source row, unless the wave straddles the free slot
-    if (row_w + 15 <= lim && is_cache && !straddles) {
-      // Cache rows are contiguous, like their LDS image: one scalar base and one M0 for the run of requests;
-      // the per-lane offsets differ only in the swizzled piece.
-      const unsigned lane_row = (unsigned)(a_lrow * D) * 2;
-      const uint16_t* sbase = base + (size_t)row_w * D;
-      const unsigned m0 = __builtin_amdgcn_readfirstlane(lds_address(stage + wave * CPW * 512));
-      auto voff = [&](int x) { return lane_row + ((a_slot ^ swz(x * RPC + a_lrow)) * 16); };
-      if constexpr (CPW == 4) async_copy16_run(sbase, m0, voff(0), voff(1), voff(2), voff(3));
-      else async_copy16_run(sbase, m0, voff(0), voff(1));
-    } else if (row_w + 15 <= lim && !straddles) {
+    if (!is_cache && col_w + 15 <= lim) {
       // every row exists: a scalar base per instruction plus a per-lane byte offset
       const unsigned lane_row = (unsigned)(a_lrow * rstride) * 2;
 #pragma unroll
-      for (int x = 0; x < CPW; ++x) {
-        const unsigned voff = lane_row + ((a_slot ^ swz(x * RPC + a_lrow)) * 16);
-        const uint16_t* sbase = base + (size_t)(row_w + x * RPC) * rstride;
-        async_copy16_offset(sbase, voff, __builtin_amdgcn_readfirstlane(lds_address(stage + (wave * CPW + x) * 512)));
-      }
+      for (int x = 0; x < CPW; ++x)
+        async_copy16_offset(base + (size_t)(col_w + x * RPC) * rstride, lane_row + piece(x), m0 + x * 1024);
     } else {
-      // rows past the last one repeat it (they are masked later; what they must not be is unreadable)
+      // cache columns at and after the free slot sit one row further on; rows past the last one repeat it (they are
+      // masked later; what they must not be is unreadable)
 #pragma unroll
       for (int x = 0; x < CPW; ++x) {
-        const int r = x * RPC + a_lrow;
-        const int col = col_w + r;
+        const int col = col_w + x * RPC + a_lrow;
         const int row = col + ((is_cache && col >= fslot) ? 1 : 0);
-        const uint16_t* src = base + (size_t)min(row, lim) * rstride + (a_slot ^ swz(r)) * 8;
-        async_copy16(src, __builtin_amdgcn_readfirstlane(lds_address(stage + (wave * CPW + x) * 512)));
+        async_copy16(base + (size_t)min(row, lim) * rstride + piece(x) / 2, m0 + x * 1024);
       }
     }
   };
@@ -392,10 +428,10 @@ __global__ __launch_bounds__(AT_THREADS) void prefill_attend_kernel(Params p, co
     // ROPE: tile t sits in the stage pair (t & 1) * 2 (hi), + 1 (lo) and is requested two tiles ahead
     auto issue_k1 = [&](int t) {
       if constexpr (ROPE) {
-        issue_tile(Ku, Kcu, kchunk_row_stride, t, sK + ((t & 1) * 2) * Lds::TILE_ELEMS, kswz);
-        issue_tile(Ku + klo_off, Kcu + klo_off, kchunk_row_stride, t, sK + ((t & 1) * 2 + 1) * Lds::TILE_ELEMS, kswz);
+        issue_tile(Ku, Kcu, kchunk_row_stride, t, (t & 1) * 2, kswz);
+        issue_tile(Ku + klo_off, Kcu + klo_off, kchunk_row_stride, t, (t & 1) * 2 + 1, kswz);
       } else {
-        issue_tile(Ku, Kcu, kchunk_row_stride, t, sK + (t & 3) * Lds::TILE_ELEMS, kswz);
+        issue_tile(Ku, Kcu, kchunk_row_stride, t, t & 3, kswz);
       }
     };
     constexpr int AHEAD = ROPE ? 2 : 3;     // how many tiles ahead of the one being finished the requests run
@@ -498,7 +534,8 @@ __global__ __launch_bounds__(AT_THREADS) void prefill_attend_kernel(Params p, co
   const int cap_cols = (p.cap + AT_COLS - 1) / AT_COLS * AT_COLS;
   const int cs_stride = cap_cols + (p.max_chunk + AT_COLS - 1) / AT_COLS * AT_COLS;
   unsigned long long* cs_acc = p.pf_colacc + (size_t)unit * cs_stride;
-  float* cs_lds = sC + rg * AT_COLS + cq * 32 + q4 * 4;                  // + (tile & 1) * 2 * AT_COLS, + bk * 16
+  // lanes lr = 0, 4, 8, 12 leave columns 0-1, 2-3 of block 0 and 0-1, 2-3 of block 1 of their lane group's four
+  float* cs_lds = sC + rg * AT_COLS + cq * 32 + (lr >> 3) * 16 + q4 * 4 + ((lr >> 2) & 1) * 2;   // + (tile & 1) * 2 * AT_COLS
   // the waves of column quarter t & 3 pass tile t's sums on (during tile t+1): thread j of the pair owns column j
   auto drain = [&](int tile) {
     const bool is_cache = tile < cache_tiles;
@@ -612,25 +649,22 @@ __global__ __launch_bounds__(AT_THREADS) void prefill_attend_kernel(Params p, co
   };
   // column sums over this wave's 32 rows (s0 / s1 hold the probabilities by now)
   auto colsums = [&](const f32x4_t (&s0)[2], const f32x4_t (&s1)[2], int tile) {
-    float* dst = cs_lds + (tile & 1) * 2 * AT_COLS;
+    float x[8];
 #pragma unroll
-    for (int bk = 0; bk < 2; ++bk) {
-      float4 c;
-      c.x = row16_sum(s0[bk][0] + s1[bk][0]);
-      c.y = row16_sum(s0[bk][1] + s1[bk][1]);
-      c.z = row16_sum(s0[bk][2] + s1[bk][2]);
-      c.w = row16_sum(s0[bk][3] + s1[bk][3]);
-      if (lr == 0) *reinterpret_cast<float4*>(dst + bk * 16) = c;
-    }
+    for (int bk = 0; bk < 2; ++bk)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) x[bk * 4 + i] = s0[bk][i] + s1[bk][i];
+    const float2 c = row16_sum8(x);
+    if ((lr & 3) == 0) *reinterpret_cast<float2*>(cs_lds + (tile & 1) * 2 * AT_COLS) = c;
   };
 
   f32x4_t sa0[2], sa1[2], sb0[2], sb1[2];
   if constexpr (!ROPE) {
   // Iteration t: request K of tile t+2 and V of tile t+1, form the logits of tile t+1, finish tile t.
   // K stage t&1 held tile t, whose logits were formed in iteration t-1; V stage (t+1)&1 held tile t-1.
-  issue_tile(Ku, Kcu, kchunk_row_stride, 0, sK, kswz);
-  issue_tile(Vu, Vcu, chunk_row_stride, 0, sV, vswz);
-  if (ntiles > 1) issue_tile(Ku, Kcu, kchunk_row_stride, 1, sK + Lds::TILE_ELEMS, kswz);
+  issue_tile(Ku, Kcu, kchunk_row_stride, 0, 0, kswz);
+  issue_tile(Vu, Vcu, chunk_row_stride, 0, 2, vswz);
+  if (ntiles > 1) issue_tile(Ku, Kcu, kchunk_row_stride, 1, 1, kswz);
   wait_vmcnt<0>();
   __syncthreads();
   qk2(sa0, sa1, 0);
@@ -639,10 +673,8 @@ __global__ __launch_bounds__(AT_THREADS) void prefill_attend_kernel(Params p, co
     if (t > 0 && cq == ((t - 1) & 3)) drain(t - 1);
     // Requests of this iteration: K of tile t+2 into K stage t&1, V of tile t+1 into V stage (t+1)&1.
     const bool more_k = t + 2 < ntiles, more_v = t + 1 < ntiles;
-    uint16_t* k_stage = sK + (t & 1) * Lds::TILE_ELEMS;
-    uint16_t* v_stage = sV + ((t + 1) & 1) * Lds::TILE_ELEMS;
-    if (more_k) issue_tile(Ku, Kcu, kchunk_row_stride, t + 2, k_stage, kswz);
-    if (more_v) issue_tile(Vu, Vcu, chunk_row_stride, t + 1, v_stage, vswz);
+    if (more_k) issue_tile(Ku, Kcu, kchunk_row_stride, t + 2, t & 1, kswz);
+    if (more_v) issue_tile(Vu, Vcu, chunk_row_stride, t + 1, 2 + ((t + 1) & 1), vswz);
     // The two waves that share a SIMD take the four pieces in different orders, so that one is on the matrix pipe
     // while the other is on the vector ALU instead of both wanting the same unit at the same time:
     //   waves 0-3: logits(t+1)  probabilities(t)  PV(t)  column sums(t)
@@ -682,11 +714,11 @@ __global__ __launch_bounds__(AT_THREADS) void prefill_attend_kernel(Params p, co
   // landed, form its logits; once every wave has done so, request the pair of tile t+2 into the same two stages and
   // finish tile t while it is on its way.  V of tile t+1 goes into V stage (t+1)&1, which held tile t-1.
   auto issue_k2 = [&](int t) {
-    issue_tile(Ku, Kcu, kchunk_row_stride, t, sK, kswz);
-    issue_tile(Ku + klo_off, Kcu + klo_off, kchunk_row_stride, t, sK + Lds::TILE_ELEMS, kswz);
+    issue_tile(Ku, Kcu, kchunk_row_stride, t, 0, kswz);
+    issue_tile(Ku + klo_off, Kcu + klo_off, kchunk_row_stride, t, 1, kswz);
   };
   issue_k2(0);
-  issue_tile(Vu, Vcu, chunk_row_stride, 0, sV, vswz);
+  issue_tile(Vu, Vcu, chunk_row_stride, 0, 2, vswz);
   wait_vmcnt<0>();
   __syncthreads();
   qk2(sa0, sa1, 0);
@@ -695,7 +727,7 @@ __global__ __launch_bounds__(AT_THREADS) void prefill_attend_kernel(Params p, co
   auto step2 = [&](f32x4_t (&c0)[2], f32x4_t (&c1)[2], f32x4_t (&n0)[2], f32x4_t (&n1)[2], int t) {
     wait_vmcnt<0>();                   // the pair of tile t+1 and V of tile t
     __syncthreads();                   // ... for every wave; and every wave is done with V of tile t-1 and tile t-1's sums
-    if (t + 1 < ntiles) issue_tile(Vu, Vcu, chunk_row_stride, t + 1, sV + ((t + 1) & 1) * Lds::TILE_ELEMS, vswz);
+    if (t + 1 < ntiles) issue_tile(Vu, Vcu, chunk_row_stride, t + 1, 2 + ((t + 1) & 1), vswz);
     if (t > 0 && cq == ((t - 1) & 3)) drain(t - 1);
     if (t + 1 < ntiles) qk2(n0, n1, 0);
     __syncthreads();                   // every wave has read the pair
