@@ -302,24 +302,27 @@ __global__ __launch_bounds__(AT_THREADS, D == 64 ? 4 : 2) void prefill_attend_ke
   // computation; two waves per SIMD issue them all, and with the shorter column sums that is 64.8 -> 59.4 us for the
   // kernel at 512 tokens into 2048 slots).
   const int full_tiles = ci.n / AT_COLS;
+  const int fw = fslot - wave * 16;                        // the wave's columns reach the free slot ..
+  const int shift_tile = (fw + AT_COLS - 1) >> 7;          // .. before this tile,
+  const int straddle_tile = ((fw - 1) & (AT_COLS - 1)) < 15 ? fw >> 7 : -1;   // .. inside this one, or between two
+  static_assert(AT_COLS == 128, "shifts by 7");
   const unsigned lds_wave = __builtin_amdgcn_readfirstlane(lds_address(pf_smem)) + wave * CPW * 1024;
   auto issue_tile = [&](const uint16_t* cache_src, const uint16_t* chunk_src, int chunk_stride, int tile, int stage,
                         auto swz) {
-    const int cw = tile * AT_COLS + wave * 16;            // first column of this wave's 16 (wave uniform)
     const unsigned m0 = lds_wave + stage * (Lds::TILE_ELEMS * 2);
     auto piece = [&](int x) { return (unsigned)((a_slot ^ swz(x * RPC + a_lrow)) * 16); };
-    if (tile < full_tiles && (unsigned)(fslot - 1 - cw) >= 15u) {
+    if (tile < full_tiles && tile != straddle_tile) {
       // Cache rows are contiguous, like their LDS image: one scalar base and one M0 for the run of requests;
       // the per-lane offsets differ only in the swizzled piece.
       const unsigned lane_row = (unsigned)a_lrow * ROWB;
-      const int row = __builtin_amdgcn_readfirstlane(cw + (cw >= fslot ? 1 : 0));
+      const int row = __builtin_amdgcn_readfirstlane(tile * AT_COLS + wave * 16 + (tile >= shift_tile ? 1 : 0));
       const char* sbase = reinterpret_cast<const char*>(cache_src) + (size_t)row * ROWB;
       if constexpr (CPW == 4) async_copy16_run(sbase, m0, lane_row + piece(0), lane_row + piece(1), lane_row + piece(2), lane_row + piece(3));
       else async_copy16_run(sbase, m0, lane_row + piece(0), lane_row + piece(1));
       return;
     }
     const bool is_cache = tile < cache_tiles;
-    const int col_w = is_cache ? cw : cw - cache_tiles * AT_COLS;
+    const int col_w = (is_cache ? tile : tile - cache_tiles) * AT_COLS + wave * 16;    // first of this wave's 16 columns
     const uint16_t* base = is_cache ? cache_src : chunk_src;
     const int rstride = is_cache ? D : chunk_stride;
     const int lim = is_cache ? cache_lim : chunk_lim;
@@ -395,30 +398,28 @@ __global__ __launch_bounds__(AT_THREADS, D == 64 ? 4 : 2) void prefill_attend_ke
           }
         }
       }
-      // The reference m_run of a lane's sums only has to keep exp2 in range, so it is raised lazily: when some
-      // lane of the wave meets a logit more than 16 (log2 units) above its reference.  After the first tiles that
-      // is rare, and the common path has no rescaling and one exp2 per logit.
-      float tmax[4];
-      bool grow = false;
-#pragma unroll
-      for (int rb = 0; rb < 4; ++rb) {
-        tmax[rb] = max3(s[rb][0], s[rb][1], fmaxf(s[rb][2], s[rb][3])) * sc;
-        grow |= tmax[rb] - 16.0f > m_run[rb];
-      }
-      if (__any(grow)) {
-#pragma unroll
-        for (int rb = 0; rb < 4; ++rb) {
-          const float m_new = fmaxf(m_run[rb], tmax[rb]);     // scaled domain: exp2(0) is exactly 1 where nothing changes
-          l_run[rb] *= fast_exp2(m_run[rb] - m_new);
-          m_run[rb] = m_new;
-        }
-      }
+      // The reference m_run of a lane's sums only has to keep exp2 in range, so it is raised lazily: when some lane's
+      // sum passes 2^64 (or its exponentials overflow: the first tile it sees), the tile is taken again with the
+      // reference at the tile's maximum.  The common path has no maxima, no rescaling and one exp2 per logit.
+      float l_new[4];
 #pragma unroll
       for (int rb = 0; rb < 4; ++rb) {
         const float e0 = fast_exp2(fmaf(s[rb][0], sc, -m_run[rb])), e1 = fast_exp2(fmaf(s[rb][1], sc, -m_run[rb]));
         const float e2 = fast_exp2(fmaf(s[rb][2], sc, -m_run[rb])), e3 = fast_exp2(fmaf(s[rb][3], sc, -m_run[rb]));
-        l_run[rb] += (e0 + e1) + (e2 + e3);
+        l_new[rb] = l_run[rb] + ((e0 + e1) + (e2 + e3));
       }
+      if (__any(max3(l_new[0], l_new[1], fmaxf(l_new[2], l_new[3])) > 0x1p64f)) {
+#pragma unroll
+        for (int rb = 0; rb < 4; ++rb) {
+          const float m_new = fmaxf(m_run[rb], max3(s[rb][0], s[rb][1], fmaxf(s[rb][2], s[rb][3])) * sc);
+          const float e0 = fast_exp2(fmaf(s[rb][0], sc, -m_new)), e1 = fast_exp2(fmaf(s[rb][1], sc, -m_new));
+          const float e2 = fast_exp2(fmaf(s[rb][2], sc, -m_new)), e3 = fast_exp2(fmaf(s[rb][3], sc, -m_new));
+          l_new[rb] = fmaf(l_run[rb], fast_exp2(m_run[rb] - m_new), (e0 + e1) + (e2 + e3));
+          m_run[rb] = m_new;
+        }
+      }
+#pragma unroll
+      for (int rb = 0; rb < 4; ++rb) l_run[rb] = l_new[rb];
     };
     // Iteration t: request tile t+3, form the logits of tile t+1 while the statistics of tile t are updated.
     // Stage (t+3)&3 held tile t-1, last read in iteration t-2.  In this sweep a wave reads exactly the 16 rows
@@ -594,27 +595,57 @@ __global__ __launch_bounds__(AT_THREADS, D == 64 ? 4 : 2) void prefill_attend_ke
   // pattern of the fp32 inline constant -1.0, which a packed 16-bit operand does not read as these two halves.
   unsigned minus_one_lo = 0x0000BF80u, minus_one_hi = 0xBF800000u;
   asm volatile("" : "+s"(minus_one_lo), "+s"(minus_one_hi));
-  // probabilities of one row block's 8 logits: the packed hi / lo P^T operands; the values themselves in place of s
-  auto soft = [&](f32x4_t (&s)[2], float neg_ml, uint4& phi, uint4& plo) {
-    unsigned hi[4], lo[4];                    // k-slots 0-3 = block 0, i = 0..3; k-slots 4-7 = block 1
+  // probabilities in place of one row block's 8 logits
+  auto probs = [&](f32x4_t (&s)[2], float neg_ml) {
 #pragma unroll
-    for (int e2 = 0; e2 < 4; ++e2) {
-      const float p0 = fast_exp2(fmaf(s[e2 >> 1][(e2 & 1) * 2], sc, neg_ml));
-      const float p1 = fast_exp2(fmaf(s[e2 >> 1][(e2 & 1) * 2 + 1], sc, neg_ml));
-      s[e2 >> 1][(e2 & 1) * 2] = p0;
-      s[e2 >> 1][(e2 & 1) * 2 + 1] = p1;
-      hi[e2] = pack_bf16(p0, p1);
-      // p - hi in one instruction each: a bf16 dot product against (-1, 0) / (0, -1) added to p
-      const bf16x2_t hv = __builtin_bit_cast(bf16x2_t, hi[e2]);
-      const float l0 = __builtin_amdgcn_fdot2_f32_bf16(hv, __builtin_bit_cast(bf16x2_t, minus_one_lo), p0, false);
-      const float l1 = __builtin_amdgcn_fdot2_f32_bf16(hv, __builtin_bit_cast(bf16x2_t, minus_one_hi), p1, false);
-      lo[e2] = pack_bf16(l0, l1);
+    for (int bk = 0; bk < 2; ++bk)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) s[bk][i] = fast_exp2(fmaf(s[bk][i], sc, neg_ml));
+  };
+  // ... as the packed hi / lo P^T operands (k-slots 0-3 = block 0, i = 0..3; k-slots 4-7 = block 1); the values are used up.
+  // p - hi is one instruction each, a bf16 dot product against (-1, 0) / (0, -1) added to p.  One statement of the
+  // three-operand form: left to itself the compiler takes the two-operand one and a copy of p for each.  Three wait
+  // states between such a product and the first use of its result.
+  auto split = [&](const f32x4_t (&s)[2], uint4& phi, uint4& plo) {
+    phi = make_uint4(pack_bf16(s[0][0], s[0][1]), pack_bf16(s[0][2], s[0][3]), pack_bf16(s[1][0], s[1][1]),
+                     pack_bf16(s[1][2], s[1][3]));
+    if constexpr (D == 128) {
+      float l0 = s[0][0], l1 = s[0][1], l2 = s[0][2], l3 = s[0][3], l4 = s[1][0], l5 = s[1][1], l6 = s[1][2], l7 = s[1][3];
+      asm("v_dot2_f32_bf16 %0, %8, %12, %0\n\t"
+          "v_dot2_f32_bf16 %1, %8, %13, %1\n\t"
+          "v_dot2_f32_bf16 %2, %9, %12, %2\n\t"
+          "v_dot2_f32_bf16 %3, %9, %13, %3\n\t"
+          "v_dot2_f32_bf16 %4, %10, %12, %4\n\t"
+          "v_dot2_f32_bf16 %5, %10, %13, %5\n\t"
+          "v_dot2_f32_bf16 %6, %11, %12, %6\n\t"
+          "v_dot2_f32_bf16 %7, %11, %13, %7\n\t"
+          "s_nop 2"
+          : "+v"(l0), "+v"(l1), "+v"(l2), "+v"(l3), "+v"(l4), "+v"(l5), "+v"(l6), "+v"(l7)
+          : "v"(phi.x), "v"(phi.y), "v"(phi.z), "v"(phi.w), "s"(minus_one_lo), "s"(minus_one_hi));
+      plo = make_uint4(pack_bf16(l0, l1), pack_bf16(l2, l3), pack_bf16(l4, l5), pack_bf16(l6, l7));
+    } else {                                  // (at head_dim 64 the statement's eight live values do not fit the registers)
+      const unsigned h[4] = {phi.x, phi.y, phi.z, phi.w};
+      unsigned lo[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const bf16x2_t hv = __builtin_bit_cast(bf16x2_t, h[e]);
+        const float l0 = __builtin_amdgcn_fdot2_f32_bf16(hv, __builtin_bit_cast(bf16x2_t, minus_one_lo), s[e >> 1][(e & 1) * 2], false);
+        const float l1 = __builtin_amdgcn_fdot2_f32_bf16(hv, __builtin_bit_cast(bf16x2_t, minus_one_hi), s[e >> 1][(e & 1) * 2 + 1], false);
+        lo[e] = pack_bf16(l0, l1);
+      }
+      plo = make_uint4(lo[0], lo[1], lo[2], lo[3]);
     }
-    phi = make_uint4(hi[0], hi[1], hi[2], hi[3]);
-    plo = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+  };
+  // the two row blocks' probabilities added, per column
+  auto add_blocks = [&](const f32x4_t (&s0)[2], const f32x4_t (&s1)[2], float (&x)[8]) {
+#pragma unroll
+    for (int bk = 0; bk < 2; ++bk)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) x[bk * 4 + i] = s0[bk][i] + s1[bk][i];
   };
   // what follows the logits of tile t, in three pieces: mask + probabilities, O^T += V^T P^T, column sums
   auto mask_tile = [&](f32x4_t (&s0)[2], f32x4_t (&s1)[2], int tile) {
+    if (tile < full_tiles) return;
     const bool is_cache = tile < cache_tiles;
     const int col0 = is_cache ? tile * AT_COLS : (tile - cache_tiles) * AT_COLS;
     // only tiles that touch the end of the cache or the causal diagonal need a mask (wave uniform)
@@ -647,19 +678,42 @@ __global__ __launch_bounds__(AT_THREADS, D == 64 ? 4 : 2) void prefill_attend_ke
       o1[d] = mfma16(a, plo1, o1[d]);
     }
   };
-  // column sums over this wave's 32 rows (s0 / s1 hold the probabilities by now)
-  auto colsums = [&](const f32x4_t (&s0)[2], const f32x4_t (&s1)[2], int tile) {
-    float x[8];
-#pragma unroll
-    for (int bk = 0; bk < 2; ++bk)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) x[bk * 4 + i] = s0[bk][i] + s1[bk][i];
+  // column sums over this wave's 32 rows
+  auto colsums = [&](const float (&x)[8], int tile) {
     const float2 c = row16_sum8(x);
     if ((lr & 3) == 0) *reinterpret_cast<float2*>(cs_lds + (tile & 1) * 2 * AT_COLS) = c;
   };
 
   f32x4_t sa0[2], sa1[2], sb0[2], sb1[2];
-  if constexpr (!ROPE) {
+  if constexpr (!ROPE && D == 64) {
+  // Iteration t: request K and V of tile t+1 into the other stages, then tile t from its logits to its column sums.  Four
+  // waves per SIMD cover each other's waits; forming the logits a tile ahead, as below, takes registers that would be
+  // spilled here (77.0 us against 72.3 per chunk of 512 at 16 KV heads x 4, 4096 slots).
+  issue_tile(Ku, Kcu, kchunk_row_stride, 0, 0, kswz);
+  issue_tile(Vu, Vcu, chunk_row_stride, 0, 2, vswz);
+  wait_vmcnt<0>();
+  __syncthreads();
+  for (int t = 0; t < ntiles; ++t) {
+    if (t > 0 && cq == ((t - 1) & 3)) drain(t - 1);
+    if (t + 1 < ntiles) {
+      issue_tile(Ku, Kcu, kchunk_row_stride, t + 1, (t + 1) & 1, kswz);
+      issue_tile(Vu, Vcu, chunk_row_stride, t + 1, 2 + ((t + 1) & 1), vswz);
+    }
+    uint4 phi0, plo0, phi1, plo1;
+    float x[8];
+    qk2(sa0, sa1, t & 1);
+    mask_tile(sa0, sa1, t);
+    probs(sa0, neg_ml0);
+    probs(sa1, neg_ml1);
+    add_blocks(sa0, sa1, x);
+    colsums(x, t);
+    split(sa0, phi0, plo0);
+    split(sa1, phi1, plo1);
+    pv(t, phi0, plo0, phi1, plo1);
+    wait_vmcnt<0>();
+    __syncthreads();
+  }
+  } else if constexpr (!ROPE) {
   // Iteration t: request K of tile t+2 and V of tile t+1, form the logits of tile t+1, finish tile t.
   // K stage t&1 held tile t, whose logits were formed in iteration t-1; V stage (t+1)&1 held tile t-1.
   issue_tile(Ku, Kcu, kchunk_row_stride, 0, 0, kswz);
@@ -680,18 +734,25 @@ __global__ __launch_bounds__(AT_THREADS, D == 64 ? 4 : 2) void prefill_attend_ke
     //   waves 0-3: logits(t+1)  probabilities(t)  PV(t)  column sums(t)
     //   waves 4-7: probabilities(t)  column sums(t)  logits(t+1)  PV(t)
     uint4 phi0, plo0, phi1, plo1;
+    float x[8];
     if constexpr (decltype(matrix_first)::value) {
       if (t + 1 < ntiles) qk2(n0, n1, (t + 1) & 1);
       mask_tile(c0, c1, t);
-      soft(c0, neg_ml0, phi0, plo0);
-      soft(c1, neg_ml1, phi1, plo1);
+      probs(c0, neg_ml0);
+      probs(c1, neg_ml1);
+      add_blocks(c0, c1, x);
+      colsums(x, t);
+      split(c0, phi0, plo0);
+      split(c1, phi1, plo1);
       pv(t, phi0, plo0, phi1, plo1);
-      colsums(c0, c1, t);
     } else {
       mask_tile(c0, c1, t);
-      soft(c0, neg_ml0, phi0, plo0);
-      soft(c1, neg_ml1, phi1, plo1);
-      colsums(c0, c1, t);
+      probs(c0, neg_ml0);
+      probs(c1, neg_ml1);
+      add_blocks(c0, c1, x);
+      colsums(x, t);
+      split(c0, phi0, plo0);
+      split(c1, phi1, plo1);
       if (t + 1 < ntiles) qk2(n0, n1, (t + 1) & 1);
       pv(t, phi0, plo0, phi1, plo1);
     }
@@ -733,11 +794,15 @@ __global__ __launch_bounds__(AT_THREADS, D == 64 ? 4 : 2) void prefill_attend_ke
     __syncthreads();                   // every wave has read the pair
     if (t + 2 < ntiles) issue_k2(t + 2);
     uint4 phi0, plo0, phi1, plo1;
+    float x[8];
     mask_tile(c0, c1, t);
-    soft(c0, neg_ml0, phi0, plo0);
-    soft(c1, neg_ml1, phi1, plo1);
+    probs(c0, neg_ml0);
+    probs(c1, neg_ml1);
+    add_blocks(c0, c1, x);
+    colsums(x, t);
+    split(c0, phi0, plo0);
+    split(c1, phi1, plo1);
     pv(t, phi0, plo0, phi1, plo1);
-    colsums(c0, c1, t);
   };
   for (int t = 0; t < ntiles; t += 2) {
     step2(sa0, sa1, sb0, sb1, t);
