@@ -128,8 +128,6 @@ __device__ inline float2 row16_sum8(const float (&x)[8]) {
 // an MFMA costs an extra instruction that quiets signalling NaNs, and the pair is not fused into v_max3_f32.
 __device__ inline float max3(float a, float b, float c) { return fmaxf(fmaxf(a, b), c); }
 
-template <bool B> struct BoolTag { static constexpr bool value = B; };
-
 // s_waitcnt vmcnt(N) alone (the other counters not waited for), N < 16.  A statement the compiler moves no memory
 // access across: LDS reads that follow it read what the awaited copies wrote.
 template <int N>
@@ -194,9 +192,9 @@ __device__ inline unsigned lds_address(const void* shared_ptr) {
 // operand layout of P^T, so P never leaves the registers; it is split into two bf16 halves (hi + lo) so that
 // rounding P costs 2^-16, not 2^-9.  The A operand V^T[d][8 columns] is read from the row-major V tile with
 // the transposing LDS read (ds_read_b64_tr_b16: 16 lanes fetch a 4 x 16 block and each gets one column).
-// Both sweeps are software pipelined: the logits of tile t+1 are formed (matrix pipe) while the
-// probabilities of tile t are worked out (vector ALU).  The four quarters of a row group add their O through
-// LDS at the end.
+// Sweep 1 is software pipelined: the logits of tile t+1 are formed (matrix pipe) while the statistics of tile t are
+// worked out (vector ALU).  The four quarters of a row group add their O through LDS at the end.
+// Bound by instruction issue: two waves per SIMD (four at head_dim 64) issue every address, conversion and wait.
 //
 // Column sums: a wave adds its two row blocks, reduces over the 16 lanes that hold the 16 rows and
 // leaves the 32 sums of its columns in LDS.  During the next tile two of the waves add the two row groups
@@ -208,7 +206,7 @@ __device__ inline unsigned lds_address(const void* shared_ptr) {
 // two bf16 parts each, from the scratch prefill_turn_kernel fills (pf_qrot, pf_krot; the chunk's own keys lie behind
 // the cache rows there), and a logit is k_hi.q_hi + k_lo.q_hi + k_hi.q_lo (what is left out, lo.lo, is 2^-18 of the
 // product).  The staging memory then holds one tile pair (hi, lo) where the plain kernel holds two tiles: sweep 1
-// requests one tile ahead instead of three, and sweep 2 has a second barrier per tile (the K pair is requested once
+// requests two tiles ahead instead of three, and sweep 2 has a second barrier per tile (the K pair is requested once
 // every wave has formed its logits from it).  Everything after the logits is unchanged.
 //
 // head_dim 64 leaves room for two workgroups per compute unit (66 KB of LDS each) if the registers are held to 128, at the
@@ -664,19 +662,21 @@ __global__ __launch_bounds__(AT_THREADS, D == 64 ? 4 : 2) void prefill_attend_ke
     }
   };
   // O^T += V^T P^T : A = V^T[d][the quarter's 8 k-slot columns of this lane group], B = P^T (hi and lo parts)
-  auto pv = [&](int tile, const uint4& phi0, const uint4& plo0, const uint4& phi1, const uint4& plo1) {
+  auto read_v = [&](uint4 (&va)[DB], int tile) {
     const uint16_t* vp = sV + (tile & 1) * Lds::TILE_ELEMS;
 #pragma unroll
     for (int d = 0; d < DB; ++d) {
       const short4_t t0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_t*)(vp + v_off0 + ((d * 2) ^ v_swz0) * 8));
       const short4_t t1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_t*)(vp + v_off1 + ((d * 2) ^ v_swz1) * 8));
       const uint2 a0 = __builtin_bit_cast(uint2, t0), a1 = __builtin_bit_cast(uint2, t1);
-      const uint4 a = make_uint4(a0.x, a0.y, a1.x, a1.y);
-      o0[d] = mfma16(a, phi0, o0[d]);
-      o1[d] = mfma16(a, phi1, o1[d]);
-      o0[d] = mfma16(a, plo0, o0[d]);
-      o1[d] = mfma16(a, plo1, o1[d]);
+      va[d] = make_uint4(a0.x, a0.y, a1.x, a1.y);
     }
+  };
+  auto pv = [&](const uint4 (&va)[DB], const uint4& phi0, const uint4& plo0, const uint4& phi1, const uint4& plo1) {
+#pragma unroll
+    for (int d = 0; d < DB; ++d) { o0[d] = mfma16(va[d], phi0, o0[d]); o1[d] = mfma16(va[d], phi1, o1[d]); }
+#pragma unroll
+    for (int d = 0; d < DB; ++d) { o0[d] = mfma16(va[d], plo0, o0[d]); o1[d] = mfma16(va[d], plo1, o1[d]); }
   };
   // column sums over this wave's 32 rows
   auto colsums = [&](const float (&x)[8], int tile) {
@@ -684,131 +684,61 @@ __global__ __launch_bounds__(AT_THREADS, D == 64 ? 4 : 2) void prefill_attend_ke
     if ((lr & 3) == 0) *reinterpret_cast<float2*>(cs_lds + (tile & 1) * 2 * AT_COLS) = c;
   };
 
-  f32x4_t sa0[2], sa1[2], sb0[2], sb1[2];
-  if constexpr (!ROPE && D == 64) {
-  // Iteration t: request K and V of tile t+1 into the other stages, then tile t from its logits to its column sums.  Four
-  // waves per SIMD cover each other's waits; forming the logits a tile ahead, as below, takes registers that would be
-  // spilled here (77.0 us against 72.3 per chunk of 512 at 16 KV heads x 4, 4096 slots).
-  issue_tile(Ku, Kcu, kchunk_row_stride, 0, 0, kswz);
-  issue_tile(Vu, Vcu, chunk_row_stride, 0, 2, vswz);
-  wait_vmcnt<0>();
-  __syncthreads();
-  for (int t = 0; t < ntiles; ++t) {
-    if (t > 0 && cq == ((t - 1) & 3)) drain(t - 1);
-    if (t + 1 < ntiles) {
-      issue_tile(Ku, Kcu, kchunk_row_stride, t + 1, (t + 1) & 1, kswz);
-      issue_tile(Vu, Vcu, chunk_row_stride, t + 1, 2 + ((t + 1) & 1), vswz);
-    }
-    uint4 phi0, plo0, phi1, plo1;
+  // what follows the logits of tile t.  All of V's operands are requested before the probabilities are worked out, which
+  // hides their way from LDS (read as they are needed, two blocks at a time, they cost a wait each).
+  auto finish_tile = [&](f32x4_t (&s0)[2], f32x4_t (&s1)[2], int t) {
+    uint4 va[DB], phi0, plo0, phi1, plo1;
     float x[8];
-    qk2(sa0, sa1, t & 1);
-    mask_tile(sa0, sa1, t);
-    probs(sa0, neg_ml0);
-    probs(sa1, neg_ml1);
-    add_blocks(sa0, sa1, x);
+    read_v(va, t);
+    mask_tile(s0, s1, t);
+    probs(s0, neg_ml0);
+    probs(s1, neg_ml1);
+    add_blocks(s0, s1, x);
     colsums(x, t);
-    split(sa0, phi0, plo0);
-    split(sa1, phi1, plo1);
-    pv(t, phi0, plo0, phi1, plo1);
+    split(s0, phi0, plo0);
+    split(s1, phi1, plo1);
+    pv(va, phi0, plo0, phi1, plo1);
+  };
+  f32x4_t s0[2], s1[2];
+  if constexpr (!ROPE) {
+    // Iteration t: request K and V of tile t+1 into the other stages, then take tile t from its logits to its column sums.
+    // (Forming the logits a tile ahead took 254 registers instead of 204, left none for V's operands and was slower: 57.9 us
+    // against 55.5 at 512 tokens into 2048 slots; at head_dim 64 it spilled: 77.0 against 72.5.)
+    issue_tile(Ku, Kcu, kchunk_row_stride, 0, 0, kswz);
+    issue_tile(Vu, Vcu, chunk_row_stride, 0, 2, vswz);
     wait_vmcnt<0>();
     __syncthreads();
-  }
-  } else if constexpr (!ROPE) {
-  // Iteration t: request K of tile t+2 and V of tile t+1, form the logits of tile t+1, finish tile t.
-  // K stage t&1 held tile t, whose logits were formed in iteration t-1; V stage (t+1)&1 held tile t-1.
-  issue_tile(Ku, Kcu, kchunk_row_stride, 0, 0, kswz);
-  issue_tile(Vu, Vcu, chunk_row_stride, 0, 2, vswz);
-  if (ntiles > 1) issue_tile(Ku, Kcu, kchunk_row_stride, 1, 1, kswz);
-  wait_vmcnt<0>();
-  __syncthreads();
-  qk2(sa0, sa1, 0);
-  __syncthreads();                     // K stage 0 is requested again right below
-  auto step2 = [&](f32x4_t (&c0)[2], f32x4_t (&c1)[2], f32x4_t (&n0)[2], f32x4_t (&n1)[2], int t, auto matrix_first) {
-    if (t > 0 && cq == ((t - 1) & 3)) drain(t - 1);
-    // Requests of this iteration: K of tile t+2 into K stage t&1, V of tile t+1 into V stage (t+1)&1.
-    const bool more_k = t + 2 < ntiles, more_v = t + 1 < ntiles;
-    if (more_k) issue_tile(Ku, Kcu, kchunk_row_stride, t + 2, t & 1, kswz);
-    if (more_v) issue_tile(Vu, Vcu, chunk_row_stride, t + 1, 2 + ((t + 1) & 1), vswz);
-    // The two waves that share a SIMD take the four pieces in different orders, so that one is on the matrix pipe
-    // while the other is on the vector ALU instead of both wanting the same unit at the same time:
-    //   waves 0-3: logits(t+1)  probabilities(t)  PV(t)  column sums(t)
-    //   waves 4-7: probabilities(t)  column sums(t)  logits(t+1)  PV(t)
-    uint4 phi0, plo0, phi1, plo1;
-    float x[8];
-    if constexpr (decltype(matrix_first)::value) {
-      if (t + 1 < ntiles) qk2(n0, n1, (t + 1) & 1);
-      mask_tile(c0, c1, t);
-      probs(c0, neg_ml0);
-      probs(c1, neg_ml1);
-      add_blocks(c0, c1, x);
-      colsums(x, t);
-      split(c0, phi0, plo0);
-      split(c1, phi1, plo1);
-      pv(t, phi0, plo0, phi1, plo1);
-    } else {
-      mask_tile(c0, c1, t);
-      probs(c0, neg_ml0);
-      probs(c1, neg_ml1);
-      add_blocks(c0, c1, x);
-      colsums(x, t);
-      split(c0, phi0, plo0);
-      split(c1, phi1, plo1);
-      if (t + 1 < ntiles) qk2(n0, n1, (t + 1) & 1);
-      pv(t, phi0, plo0, phi1, plo1);
-    }
-    wait_vmcnt<0>();                   // this iteration's requests are the next one's operands
-    __syncthreads();
-  };
-  if (wave < 4) {                      // (the choice is made outside the loop: inside, the two bodies would share registers badly)
-    for (int t = 0; t < ntiles; t += 2) {
-      step2(sa0, sa1, sb0, sb1, t, BoolTag<true>{});
-      if (t + 1 < ntiles) step2(sb0, sb1, sa0, sa1, t + 1, BoolTag<true>{});
+    for (int t = 0; t < ntiles; ++t) {
+      if (t > 0 && cq == ((t - 1) & 3)) drain(t - 1);
+      if (t + 1 < ntiles) {
+        issue_tile(Ku, Kcu, kchunk_row_stride, t + 1, (t + 1) & 1, kswz);
+        issue_tile(Vu, Vcu, chunk_row_stride, t + 1, 2 + ((t + 1) & 1), vswz);
+      }
+      qk2(s0, s1, t & 1);
+      finish_tile(s0, s1, t);
+      wait_vmcnt<0>();                   // this iteration's requests are the next one's operands
+      __syncthreads();
     }
   } else {
-    for (int t = 0; t < ntiles; t += 2) {
-      step2(sa0, sa1, sb0, sb1, t, BoolTag<false>{});
-      if (t + 1 < ntiles) step2(sb0, sb1, sa0, sa1, t + 1, BoolTag<false>{});
+    // ROPE: one K pair (hi in K stage 0, lo in K stage 1) and two V stages.  Iteration t: with the pair of tile t landed,
+    // form its logits; once every wave has done so, request the pair of tile t+1 into the same two stages and V of tile
+    // t+1 into V stage (t+1)&1, which held tile t-1, and finish tile t while they are on their way.
+    auto issue_pair = [&](int t) {
+      issue_tile(Ku, Kcu, kchunk_row_stride, t, 0, kswz);
+      issue_tile(Ku + klo_off, Kcu + klo_off, kchunk_row_stride, t, 1, kswz);
+      issue_tile(Vu, Vcu, chunk_row_stride, t, 2 + (t & 1), vswz);
+    };
+    issue_pair(0);
+    for (int t = 0; t < ntiles; ++t) {
+      wait_vmcnt<0>();                   // the pair and V of tile t
+      __syncthreads();                   // ... for every wave; and every wave is done with V of tile t-1 and tile t-1's sums
+      if (t > 0 && cq == ((t - 1) & 3)) drain(t - 1);
+      qk2(s0, s1, 0);
+      __syncthreads();                   // every wave has read the pair
+      if (t + 1 < ntiles) issue_pair(t + 1);
+      finish_tile(s0, s1, t);
     }
-  }
-  } else {
-  // ROPE: one K pair (hi in K stage 0, lo in K stage 1) and two V stages.  Iteration t: with the pair of tile t+1
-  // landed, form its logits; once every wave has done so, request the pair of tile t+2 into the same two stages and
-  // finish tile t while it is on its way.  V of tile t+1 goes into V stage (t+1)&1, which held tile t-1.
-  auto issue_k2 = [&](int t) {
-    issue_tile(Ku, Kcu, kchunk_row_stride, t, 0, kswz);
-    issue_tile(Ku + klo_off, Kcu + klo_off, kchunk_row_stride, t, 1, kswz);
-  };
-  issue_k2(0);
-  issue_tile(Vu, Vcu, chunk_row_stride, 0, 2, vswz);
-  wait_vmcnt<0>();
-  __syncthreads();
-  qk2(sa0, sa1, 0);
-  __syncthreads();                     // the pair is requested again right below
-  if (ntiles > 1) issue_k2(1);
-  auto step2 = [&](f32x4_t (&c0)[2], f32x4_t (&c1)[2], f32x4_t (&n0)[2], f32x4_t (&n1)[2], int t) {
-    wait_vmcnt<0>();                   // the pair of tile t+1 and V of tile t
-    __syncthreads();                   // ... for every wave; and every wave is done with V of tile t-1 and tile t-1's sums
-    if (t + 1 < ntiles) issue_tile(Vu, Vcu, chunk_row_stride, t + 1, 2 + ((t + 1) & 1), vswz);
-    if (t > 0 && cq == ((t - 1) & 3)) drain(t - 1);
-    if (t + 1 < ntiles) qk2(n0, n1, 0);
-    __syncthreads();                   // every wave has read the pair
-    if (t + 2 < ntiles) issue_k2(t + 2);
-    uint4 phi0, plo0, phi1, plo1;
-    float x[8];
-    mask_tile(c0, c1, t);
-    probs(c0, neg_ml0);
-    probs(c1, neg_ml1);
-    add_blocks(c0, c1, x);
-    colsums(x, t);
-    split(c0, phi0, plo0);
-    split(c1, phi1, plo1);
-    pv(t, phi0, plo0, phi1, plo1);
-  };
-  for (int t = 0; t < ntiles; t += 2) {
-    step2(sa0, sa1, sb0, sb1, t);
-    if (t + 1 < ntiles) step2(sb0, sb1, sa0, sa1, t + 1);
-  }
-  __syncthreads();                     // the last tile's sums are in LDS
+    __syncthreads();                     // the last tile's sums are in LDS
   }
   if (cq == ((ntiles - 1) & 3)) drain(ntiles - 1);     // the last tile's sums (its barrier has passed)
 
