@@ -695,8 +695,11 @@ size_t prompt_blocks_lds(int T, int b, int cb, int sink_b, int recent_b) {
   return ((size_t)(T / b) + 1 + 4 * (size_t)(cb - sink_b - recent_b)) * 4;
 }
 
-int launch_prompt(const Params& p, const void* Qw, const void* K, const void* V, int T, int b, int32_t* retained,
+int launch_prompt(const Params& ctx_params, const void* Qw, const void* K, const void* V, int T, int b, int32_t* retained,
                   int32_t* n_retained, int32_t* evicted_blocks, float* token_scores, hipStream_t s) {
+  // the caller's token scores are written where they belong and read back from there (a copy at the end is 5 us of the call)
+  Params p = ctx_params;
+  if (token_scores) p.pp_tok = token_scores;
   const int cb = p.budget / b, sink_b = (p.n_sink + b - 1) / b, recent_b = (p.n_recent + b - 1) / b;
   int block_means = 0;
   if (p.dtype == TREEKV_F32) {
@@ -730,9 +733,6 @@ int launch_prompt(const Params& p, const void* Qw, const void* K, const void* V,
   const int n = T < p.budget ? T : p.budget;
   hipLaunchKernelGGL(prompt_handoff_kernel, dim3((p.budget + per_wg - 1) / per_wg, p.U), dim3(256), 0, s, p,
                      (const uint4*)K, (const uint4*)V, T, b, n, row_vec, retained, n_retained);
-  if (token_scores &&
-      hip_failed(hipMemcpyAsync(token_scores, p.pp_tok, (size_t)p.U * T * sizeof(float), hipMemcpyDeviceToDevice, s)))
-    return TREEKV_EHIP;
   return finish_launch();
 }
 
