@@ -479,7 +479,7 @@ def main():
     torch.cuda.empty_cache()
     peaks = measure_peaks(torch, binding, dev)
     roof = roofline("hbm", r["achieved_GBs"], HBM_PEAK_GBS, "GB/s", peaks["hbm_read_GBs"],
-                    kernel="decode_fused_kernel<bf16,128,1>" if r["kv_splits"] == 1 else "decode_split_kernel + decode_merge_kernel",
+                    kernel="decode_fused_kernel<bf16,128,1>" if r["kv_splits"] == 1 else "decode_split_kernel",
                     bytes_per_launch=r["bytes_per_launch"], launch_us=r["launch_us"], single_call_us=r["single_call_us"],
                     note="launch_us = HIP-event time of the timed region / number of layer launches, calls enqueued back "
                          "to back (gaps between launches included): achieved and frac refer to it; single_call_us = "

@@ -209,9 +209,9 @@ __device__ inline unsigned lds_address(const void* shared_ptr) {
 // requests two tiles ahead instead of three, and sweep 2 has a second barrier per tile (the K pair is requested once
 // every wave has formed its logits from it).  Everything after the logits is unchanged.
 //
-// head_dim 64 leaves room for two workgroups per compute unit (66 KB of LDS each) if the registers are held to 128, at the
-// price of a few spills: 8 KV heads x 4 x 2 sequences of 6000 tokens into 4096 slots 1406 -> 1343 us, and with the shorter
-// instruction stream 1057.
+// head_dim 64 leaves room for two workgroups per compute unit (66 KB of LDS each) if the registers are held to 128: two
+// sequences of 6000 tokens, 8 KV heads x 4, into 4096 slots take 945 us in chunks of 512 (1406 with one workgroup of 165
+// registers and the longer instruction stream).
 template <int D, bool ROPE>
 __global__ __launch_bounds__(AT_THREADS, D == 64 ? 4 : 2) void prefill_attend_kernel(Params p, const uint16_t* __restrict__ Q,
                                                                     const uint16_t* __restrict__ Kc,
