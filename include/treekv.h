@@ -151,8 +151,8 @@ int treekv_decode_step(treekv_ctx* ctx, const void* q, const void* k, const void
  * neither allocate device memory nor hand the library scratch of their own for this: code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc.  The only scratch a decode step uses -- the scaled logits
  * [U][c+1][G] float32 and the per-slice partial results [U][kv_splits][G][d+2] float32 that the split shape
- * (kv_splits > 1) passes from its first kernel to its second -- lives in a fixed array of
- * TREEKV_STATIC_SCRATCH_BYTES inside the library's device image instead of the bound workspace (the one-kernel
+ * (kv_splits > 1) passes between its workgroups -- lives in a fixed array of
+ * TREEKV_STATIC_SCRATCH_BYTES inside the library's device image instead of the bound workspace (the fused
  * shape, kv_splits = 1, uses none).  Each GPU holds one such array until the process ends; every call on a GPU,
  * from any context, shares it: calls that may overlap on one GPU (different streams without ordering) race and
  * must not both use this entry point.  Nothing in the array has to survive from one call to the next and nothing
