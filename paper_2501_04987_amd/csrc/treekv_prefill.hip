@@ -124,6 +124,8 @@ __device__ inline float2 row16_sum8(const float (&x)[8]) {
       : "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "v"(x[4]), "v"(x[5]), "v"(x[6]), "v"(x[7]));
   return make_float2(s0, s1);
 }
+// Neither an infinity nor a NaN.  From the bits: this file is compiled with -fno-honor-nans.
+__device__ inline int is_finite(float v) { return (__float_as_uint(v) & 0x7f800000u) != 0x7f800000u; }
 // max of three.  This file is compiled with -fno-honor-nans: otherwise every fmaxf operand that comes out of
 // an MFMA costs an extra instruction that quiets signalling NaNs, and the pair is not fused into v_max3_f32.
 __device__ inline float max3(float a, float b, float c) { return fmaxf(fmaxf(a, b), c); }
@@ -924,15 +926,49 @@ __global__ __launch_bounds__(F32_THREADS) void prefill_attend_f32_kernel(Params 
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i) s[i] = fast_exp2(s[i] - M) * inv;
+    // A block that reaches past what the tile's first row sees: a column some row does not see must stay without effect
+    // on that row whatever the inputs hold, and 0 times an infinity or a NaN is a NaN.  The probabilities are cleared
+    // (a NaN row has none that are 0), and if some v is not finite the block is taken without the matrix instructions.
+    bool matrix = true;
+    if (blk * 16 + 15 > n + r0) {
+      int finite = 1;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < 4; ++i) {
+        if (blk * 16 + q4 * 4 + i > n + my_row) s[i] = 0.f;
 #pragma unroll
-      for (int x = 0; x < VX; ++x) {
-        o[x][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(vv[i][x].x, s[i], o[x][0], 0, 0, 0);
-        o[x][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(vv[i][x].y, s[i], o[x][1], 0, 0, 0);
-        o[x][2] = __builtin_amdgcn_mfma_f32_16x16x4f32(vv[i][x].z, s[i], o[x][2], 0, 0, 0);
-        o[x][3] = __builtin_amdgcn_mfma_f32_16x16x4f32(vv[i][x].w, s[i], o[x][3], 0, 0, 0);
+        for (int x = 0; x < VX; ++x)
+          finite &= is_finite(vv[i][x].x) & is_finite(vv[i][x].y) & is_finite(vv[i][x].z) & is_finite(vv[i][x].w);
       }
+      matrix = __all(finite);
+    }
+    if (matrix) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int x = 0; x < VX; ++x) {
+          o[x][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(vv[i][x].x, s[i], o[x][0], 0, 0, 0);
+          o[x][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(vv[i][x].y, s[i], o[x][1], 0, 0, 0);
+          o[x][2] = __builtin_amdgcn_mfma_f32_16x16x4f32(vv[i][x].z, s[i], o[x][2], 0, 0, 0);
+          o[x][3] = __builtin_amdgcn_mfma_f32_16x16x4f32(vv[i][x].w, s[i], o[x][3], 0, 0, 0);
+        }
+    } else {
+      for (int c = 0; c < 16; ++c) {
+        const int i = c & 3;
+        const float pc = __shfl(i == 0 ? s[0] : i == 1 ? s[1] : i == 2 ? s[2] : s[3], (c >> 2) * 16 + lr, 64);
+        const float* row = row_of(Vu, Vcu, cstride, blk * 16 + c) + q4 * 16;
+        if (blk * 16 + c > n + my_row) continue;
+#pragma unroll
+        for (int x = 0; x < VX; ++x)
+#pragma unroll
+          for (int y = 0; y < 4; ++y) {
+            const float4 v = *reinterpret_cast<const float4*>(row + x * 64 + y * 4);
+            o[x][0][y] = fmaf(pc, v.x, o[x][0][y]);
+            o[x][1][y] = fmaf(pc, v.y, o[x][1][y]);
+            o[x][2][y] = fmaf(pc, v.z, o[x][2][y]);
+            o[x][3][y] = fmaf(pc, v.w, o[x][3][y]);
+          }
+      }
+    }
     // lane lr < 4 of every lane group passes on column 4 q4 + lr (integer adds: the order does not matter)
     const float c0 = row16_sum(s[0]), c1 = row16_sum(s[1]), c2 = row16_sum(s[2]), c3 = row16_sum(s[3]);
     const float cs = lr == 0 ? c0 : lr == 1 ? c1 : lr == 2 ? c2 : c3;

@@ -164,3 +164,38 @@ def test_prefill_fp32_degenerate_and_keep_left(binding, oracle):
 def test_prefill_fp32_tile_edges(binding, oracle, d, budget, schedule):
     _run(binding, oracle, schedule, B=1, H=2, Hkv=1, d=d, budget=budget, n_sink=1, n_recent=budget // 3,
          max_chunk=max(schedule), seed=17, kind="iid", dtype="f32")
+
+
+@pytest.mark.parametrize("d,n0", [(64, 50), (128, 48), (64, 2060)])
+def test_prefill_fp32_non_finite_rows_stay_their_own(binding, d, n0):
+    """A token whose v holds an infinity or a NaN reaches the rows that see it and no other, and a query of NaNs spoils
+    the scores of the tokens it sees and no other's.  (Column blocks at, inside and past the end of a row tile; at
+    2060 cached tokens the logits of the chunk's columns are formed twice.)"""
+    import torch
+
+    L, H, inf_at, nan_at, bad_query = 40, 2, 20, 39, 10
+    g = torch.Generator(device="cuda").manual_seed(d + n0)
+    Q, K, V = (torch.randn(1, n0 + L, H, d, device="cuda", generator=g) for _ in range(3))
+
+    def run(q, v):
+        kv = binding.TreeKV(n0 + L + 8, H, d, kv_heads=H, dtype="f32", n_sink=2, n_recent=8, max_chunk=1024)
+        for a in list(range(0, n0, 1024)) + [n0]:
+            b = min(a + 1024, n0) if a < n0 else n0 + L
+            res = kv.new_outputs(b - a)
+            kv.prefill_chunk(q[:, a:b].contiguous(), K[:, a:b].contiguous(), v[:, a:b].contiguous(), b - a, *res)
+        scores = kv.scores()
+        torch.cuda.synchronize()
+        return res[0][0].cpu(), scores[0, :, n0:n0 + L].cpu()
+
+    want, want_s = run(Q, V)
+    q, v = Q.clone(), V.clone()
+    v[:, n0 + inf_at, :, 3] = float("inf")
+    v[:, n0 + nan_at, :, 5] = float("nan")
+    q[:, n0 + bad_query] = float("nan")
+    got, got_s = run(q, v)
+    want[inf_at:, :, 3] = float("inf")
+    want[nan_at:, :, 5] = float("nan")
+    rows = [i for i in range(L) if i != bad_query]
+    torch.testing.assert_close(got[rows], want[rows], rtol=1e-5, atol=1e-5, equal_nan=True)
+    assert torch.isnan(got[bad_query]).all()
+    torch.testing.assert_close(got_s[:, bad_query + 1:], want_s[:, bad_query + 1:], rtol=1e-5, atol=1e-6)
