@@ -312,7 +312,8 @@ __global__ __launch_bounds__(PP_THREADS) void prompt_stats_kernel(Params p, cons
 template <int D, int NB, bool ROPE>
 __global__ __launch_bounds__(PP_THREADS) void prompt_scores_kernel(Params p, const uint16_t* __restrict__ Qw,
                                                                    const uint16_t* __restrict__ K, int T, int W,
-                                                                   int rows_per_split, int nsplit, int block_means) {
+                                                                   int rows_per_split, int nsplit, int block_means,
+                                                                   float* __restrict__ token_scores) {
   using PS = PromptStream<D, NB, ROPE>;
   using KB = typename PS::KB;
   __shared__ float sm_ML[NB * 16];
@@ -383,9 +384,13 @@ __global__ __launch_bounds__(PP_THREADS) void prompt_scores_kernel(Params p, con
     if (base + PP_TILE > lim_all) { block(BoolTag<true>{}, k0, base, 0); block(BoolTag<true>{}, k1, base, 1); }
     else { block(BoolTag<false>{}, k0, base, 0); block(BoolTag<false>{}, k1, base, 1); }
   }
-  // a block's score is the mean over its W tokens (the blocks of this slice lie wholly inside it)
+  // A block's score is the mean over its W tokens (the blocks of this slice lie wholly inside it).  The scores also leave
+  // for the caller's buffer, which is only written (what the next kernels read is the workspace's copy), in whole lines:
+  // as a second scattered store per key of the loop they cost 7 us of a 32k prompt's 125.
   if (block_means) {
     __syncthreads();
+    if (token_scores)
+      for (int j = st.begin + tid; j < st.end; j += PP_THREADS) token_scores[(size_t)unit * T + j] = sm_tok[j - st.begin];
     float* beta = p.pp_beta + (size_t)unit * (T / W);
     for (int k = tid; k < (st.end - st.begin) / W; k += PP_THREADS) {
       float acc = 0.f;
@@ -641,7 +646,7 @@ __global__ __launch_bounds__(256) void prompt_handoff_kernel(Params p, const uin
 
 template <int D, int NB, bool ROPE>
 int launch_streams(const Params& p, const uint16_t* Qw, const uint16_t* K, int T, int W, int rows_per_split,
-                   int nsplit, int block_means, hipStream_t s) {
+                   int nsplit, int block_means, float* token_scores, hipStream_t s) {
   constexpr size_t q_lds = PromptStream<D, NB, ROPE>::Q_LDS_BYTES;
   const size_t lds = q_lds + (block_means ? (size_t)rows_per_split * 4 : 0);
   if (q_lds > 48 * 1024 && hip_failed(hipFuncSetAttribute((const void*)prompt_stats_kernel<D, NB, ROPE>,
@@ -654,24 +659,24 @@ int launch_streams(const Params& p, const uint16_t* Qw, const uint16_t* K, int T
   hipLaunchKernelGGL((prompt_stats_kernel<D, NB, ROPE>), dim3(nsplit, p.U), dim3(PP_THREADS), q_lds, s, p, Qw, K, T, W,
                      rows_per_split, nsplit);
   hipLaunchKernelGGL((prompt_scores_kernel<D, NB, ROPE>), dim3(nsplit, p.U), dim3(PP_THREADS), lds, s, p, Qw, K, T, W,
-                     rows_per_split, nsplit, block_means);
+                     rows_per_split, nsplit, block_means, token_scores);
   return TREEKV_OK;
 }
 
 template <int D, bool ROPE>
 int launch_streams_r(const Params& p, const uint16_t* Qw, const uint16_t* K, int T, int W, int rows_per_split,
-                     int nsplit, int block_means, hipStream_t s) {
+                     int nsplit, int block_means, float* token_scores, hipStream_t s) {
   const int nb = (W * p.G + 15) / 16;
-  if (nb <= 2) return launch_streams<D, 2, ROPE>(p, Qw, K, T, W, rows_per_split, nsplit, block_means, s);
-  if (nb <= 4) return launch_streams<D, 4, ROPE>(p, Qw, K, T, W, rows_per_split, nsplit, block_means, s);
-  return launch_streams<D, 8, ROPE>(p, Qw, K, T, W, rows_per_split, nsplit, block_means, s);
+  if (nb <= 2) return launch_streams<D, 2, ROPE>(p, Qw, K, T, W, rows_per_split, nsplit, block_means, token_scores, s);
+  if (nb <= 4) return launch_streams<D, 4, ROPE>(p, Qw, K, T, W, rows_per_split, nsplit, block_means, token_scores, s);
+  return launch_streams<D, 8, ROPE>(p, Qw, K, T, W, rows_per_split, nsplit, block_means, token_scores, s);
 }
 
 template <int D>
 int launch_streams_d(const Params& p, const uint16_t* Qw, const uint16_t* K, int T, int W, int rows_per_split,
-                     int nsplit, int block_means, hipStream_t s) {
-  if (p.flags & TREEKV_POSITION_RERANK) return launch_streams_r<D, true>(p, Qw, K, T, W, rows_per_split, nsplit, block_means, s);
-  return launch_streams_r<D, false>(p, Qw, K, T, W, rows_per_split, nsplit, block_means, s);
+                     int nsplit, int block_means, float* token_scores, hipStream_t s) {
+  if (p.flags & TREEKV_POSITION_RERANK) return launch_streams_r<D, true>(p, Qw, K, T, W, rows_per_split, nsplit, block_means, token_scores, s);
+  return launch_streams_r<D, false>(p, Qw, K, T, W, rows_per_split, nsplit, block_means, token_scores, s);
 }
 
 }  // namespace
@@ -695,11 +700,8 @@ size_t prompt_blocks_lds(int T, int b, int cb, int sink_b, int recent_b) {
   return ((size_t)(T / b) + 1 + 4 * (size_t)(cb - sink_b - recent_b)) * 4;
 }
 
-int launch_prompt(const Params& ctx_params, const void* Qw, const void* K, const void* V, int T, int b, int32_t* retained,
+int launch_prompt(const Params& p, const void* Qw, const void* K, const void* V, int T, int b, int32_t* retained,
                   int32_t* n_retained, int32_t* evicted_blocks, float* token_scores, hipStream_t s) {
-  // the caller's token scores are written where they belong and read back from there (a copy at the end is 5 us of the call)
-  Params p = ctx_params;
-  if (token_scores) p.pp_tok = token_scores;
   const int cb = p.budget / b, sink_b = (p.n_sink + b - 1) / b, recent_b = (p.n_recent + b - 1) / b;
   int block_means = 0;
   if (p.dtype == TREEKV_F32) {
@@ -718,8 +720,8 @@ int launch_prompt(const Params& ctx_params, const void* Qw, const void* K, const
     // the scores kernel also takes the block means when no block straddles two slices and a slice's scores fit
     // in 40 KB of LDS (slices start at multiples of what a workgroup takes per iteration)
     block_means = (PP_STEP % b == 0 && (size_t)rows_per_split * 4 <= 40 * 1024) ? 1 : 0;
-    const int rc = p.D == 128 ? launch_streams_d<128>(p, (const uint16_t*)Qw, (const uint16_t*)K, T, b, rows_per_split, nsplit, block_means, s)
-                              : launch_streams_d<64>(p, (const uint16_t*)Qw, (const uint16_t*)K, T, b, rows_per_split, nsplit, block_means, s);
+    const int rc = p.D == 128 ? launch_streams_d<128>(p, (const uint16_t*)Qw, (const uint16_t*)K, T, b, rows_per_split, nsplit, block_means, token_scores, s)
+                              : launch_streams_d<64>(p, (const uint16_t*)Qw, (const uint16_t*)K, T, b, rows_per_split, nsplit, block_means, token_scores, s);
     if (rc != TREEKV_OK) return rc;
   }
   const size_t lds = prompt_blocks_lds(T, b, cb, sink_b, recent_b);
@@ -733,6 +735,10 @@ int launch_prompt(const Params& ctx_params, const void* Qw, const void* K, const
   const int n = T < p.budget ? T : p.budget;
   hipLaunchKernelGGL(prompt_handoff_kernel, dim3((p.budget + per_wg - 1) / per_wg, p.U), dim3(256), 0, s, p,
                      (const uint4*)K, (const uint4*)V, T, b, n, row_vec, retained, n_retained);
+  // (with block means the scores kernel has written the caller's token scores)
+  if (token_scores && !block_means &&
+      hip_failed(hipMemcpyAsync(token_scores, p.pp_tok, (size_t)p.U * T * sizeof(float), hipMemcpyDeviceToDevice, s)))
+    return TREEKV_EHIP;
   return finish_launch();
 }
 

@@ -244,3 +244,32 @@ def test_prompt_fp32_that_fits_and_accumulated(binding, oracle):
          kind="iid", dtype="f32")
     _run(binding, oracle, T=320, block=16, steps=20, B=1, H=2, Hkv=1, d=128, budget=96, n_sink=0, n_recent=16, seed=19,
          kind="iid", dtype="f32", flags=binding.TREEKV_SCORE_ACCUMULATED)
+
+
+@pytest.mark.parametrize("dtype,block", [("bf16", 16), ("bf16", 24), ("f32", 16)])
+def test_prompt_token_scores_are_an_output(binding, dtype, block):
+    """The state a call leaves does not depend on the buffer its token scores go to: none, one of 4-byte alignment, one
+    that something else writes meanwhile (here: the call's own list of evicted blocks).  Block means taken with the
+    scores (16) and afterwards (24 does not divide a workgroup's step)."""
+    import torch
+
+    B, H, d, T, budget = 2, 2, 64, block * 100, block * 20
+    Q, K, V = inputs.batch_streams("lowrank" if dtype == "bf16" else "iid", 51, T, B, H, 1, d, dtype=dtype)
+    Qd, Kd, Vd = (ph.to_device(x, dtype).transpose(0, 1).contiguous() for x in (Q, K, V))
+    n, N = B * H * T, B * H * (T // block)
+
+    def run(scores, evicted=None):
+        kv = binding.TreeKV(budget, H, d, kv_heads=H, batch=B, dtype=dtype, n_sink=4, n_recent=block, max_prompt=T)
+        _, ret, nret, _ = kv.new_outputs()
+        kv.prefill_prompt(Qd[:, T - block:].contiguous(), Kd, Vd, T, block, ret, nret, evicted, scores)
+        snap = kv.export_state()
+        torch.cuda.synchronize()
+        return ret, snap
+
+    ret, snap = run(None)
+    plain, odd, shared = (torch.full((n + 1,), -7.0, device="cuda") for _ in range(3))
+    for scores, evicted in ((plain[:n], None), (odd[1:], None), (shared[:n], shared[:N].view(torch.int32))):
+        r, s = run(scores, evicted)
+        assert torch.equal(r, ret) and torch.equal(s, snap)
+    assert torch.equal(plain[:n], odd[1:]) and plain[n] == -7.0 and odd[0] == -7.0
+    assert float(plain[:n].min()) >= 0.0
