@@ -180,49 +180,74 @@ __global__ __launch_bounds__(WV_THREADS, sizeof(T) * D > 256 ? 2 : 6) void wavel
   }
 }
 
-// Mean over the heads: a workgroup owns 32 adjacent outputs (whole 128-byte lines); its threads, VEC outputs each, share out the heads, then the
-// head lanes of a wave and the waves are added in a fixed order, which depends on nothing but `heads`.
+// Mean over the heads: a workgroup owns 32 adjacent outputs (whole 128-byte lines) and adds up the heads of every output in
+// an order that depends on nothing but `heads`: 128 head lanes take every 128th head each, eight lanes' sums go up a tree,
+// the 16 results are added one after the other.
+//   QUADS   a thread is one head lane of four outputs (16-byte loads), the tree is lane exchanges.
+//   else    (per_head not 16-byte aligned, or rows that are no whole groups of four outputs) a thread is four head lanes of
+//           one output, the tree goes through LDS.
 // Bound by the bytes a compute unit can have in flight (the grid is one workgroup per 32 outputs, 80 at 5 levels of 512):
 // with 16-byte loads, 16 of them per thread, 256 KB.  At 8192 heads 22 us (84 MB, most of it still in the memory-side cache,
 // because the components kernel reads V past it); 35 us with 4-byte loads, 31 us with 16 outputs (64-byte pieces of
 // a head's row) per workgroup.
-constexpr int MEAN_COLS = 32, MEAN_THREADS = 1024;
-template <int VEC>
+constexpr int MEAN_COLS = 32, MEAN_THREADS = 1024, MEAN_LANES = 128;
+template <bool QUADS>
 __global__ __launch_bounds__(MEAN_THREADS) void wavelet_mean_kernel(const float* __restrict__ per_head, int heads, int n,
                                                                     float* __restrict__ mean) {
-  constexpr int TX = MEAN_COLS / VEC, LANES = MEAN_THREADS / TX, WAVES = MEAN_THREADS / 64;
-  __shared__ float red[WAVES][MEAN_COLS];
-  const int tid = threadIdx.x, tx = tid % TX, ty = tid / TX;
-  const int i = blockIdx.x * MEAN_COLS + tx * VEC;
-  float acc[VEC];
-#pragma unroll
-  for (int e = 0; e < VEC; ++e) acc[e] = 0.f;
-  if (i < n) {
+  constexpr int GROUPS = MEAN_LANES / 8;
+  __shared__ float red[GROUPS][MEAN_COLS];
+  const int tid = threadIdx.x, first = blockIdx.x * MEAN_COLS;
+  if constexpr (QUADS) {
+    constexpr int TX = MEAN_COLS / 4;
+    const int tx = tid % TX, lane = tid / TX, i = first + tx * 4;
+    float acc[4] = {0.f, 0.f, 0.f, 0.f};
+    if (i < n) {
 #pragma unroll 16
-    for (int h = ty; h < heads; h += LANES) {
-      const float* src = per_head + (size_t)h * n + i;
-      if constexpr (VEC == 4) {
-        const float4 v = *reinterpret_cast<const float4*>(src);
+      for (int h = lane; h < heads; h += MEAN_LANES) {
+        const float4 v = *reinterpret_cast<const float4*>(per_head + (size_t)h * n + i);
         acc[0] += v.x; acc[1] += v.y; acc[2] += v.z; acc[3] += v.w;
-      } else {
-        acc[0] += *src;
       }
     }
-  }
 #pragma unroll
-  for (int o = TX; o < 64; o <<= 1)
+    for (int o = TX; o < 64; o <<= 1)
 #pragma unroll
-    for (int e = 0; e < VEC; ++e) acc[e] += __shfl_xor(acc[e], o, 64);
-  if (tid % 64 < TX) {
+      for (int e = 0; e < 4; ++e) acc[e] += __shfl_xor(acc[e], o, 64);
+    if (tid % 64 < TX) {
 #pragma unroll
-    for (int e = 0; e < VEC; ++e) red[tid / 64][tx * VEC + e] = acc[e];
+      for (int e = 0; e < 4; ++e) red[tid / 64][tx * 4 + e] = acc[e];
+    }
+  } else {
+    constexpr int STEP = MEAN_THREADS / MEAN_COLS;
+    __shared__ float sums[MEAN_LANES][MEAN_COLS];
+    const int tx = tid % MEAN_COLS, ty = tid / MEAN_COLS;
+    float acc[4] = {0.f, 0.f, 0.f, 0.f};                 // head lanes ty, ty + 32, ty + 64, ty + 96
+    if (first + tx < n) {
+      const float* src = per_head + first + tx;
+      int h = ty;
+#pragma unroll 4
+      for (; h + 3 * STEP < heads; h += MEAN_LANES)
+#pragma unroll
+        for (int y = 0; y < 4; ++y) acc[y] += src[(size_t)(h + y * STEP) * n];
+#pragma unroll
+      for (int y = 0; y < 3; ++y)
+        if (h + y * STEP < heads) acc[y] += src[(size_t)(h + y * STEP) * n];
+    }
+#pragma unroll
+    for (int y = 0; y < 4; ++y) sums[ty + y * STEP][tx] = acc[y];
+    __syncthreads();
+    if (tid < GROUPS * MEAN_COLS) {
+      float s[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) s[k] = sums[ty * 8 + k][tx];
+      red[ty][tx] = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
+    }
   }
   __syncthreads();
-  if (tid < MEAN_COLS && blockIdx.x * MEAN_COLS + tid < n) {
+  if (tid < MEAN_COLS && first + tid < n) {
     float sum = 0.f;
 #pragma unroll
-    for (int w = 0; w < WAVES; ++w) sum += red[w][tid];
-    mean[blockIdx.x * MEAN_COLS + tid] = sum / (float)heads;
+    for (int w = 0; w < GROUPS; ++w) sum += red[w][tid];
+    mean[first + tid] = sum / (float)heads;
   }
 }
 
@@ -246,7 +271,7 @@ int launch_wavelet(const float* a, const void* V, int dtype, int heads, int t, i
   if (mean) {
     const int n = levels * t;
     // 16-byte loads need whole groups of four outputs in every head's row
-    auto kern = n % 4 == 0 && (reinterpret_cast<uintptr_t>(per_head) & 15) == 0 ? wavelet_mean_kernel<4> : wavelet_mean_kernel<1>;
+    auto kern = n % 4 == 0 && (reinterpret_cast<uintptr_t>(per_head) & 15) == 0 ? wavelet_mean_kernel<true> : wavelet_mean_kernel<false>;
     hipLaunchKernelGGL(kern, dim3((n + MEAN_COLS - 1) / MEAN_COLS), dim3(MEAN_THREADS), 0, s, per_head, heads, n, mean);
   }
   return finish_launch();

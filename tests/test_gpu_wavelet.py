@@ -110,3 +110,21 @@ def test_wavelet_mean_over_heads_edges(binding, heads, t, levels):
     per_head, mean = binding.wavelet_components(a, V, levels)
     torch.cuda.synchronize()
     assert torch.allclose(mean.double(), per_head.double().mean(0), rtol=1e-5, atol=0.0)
+
+
+@pytest.mark.parametrize("heads", [5, 130, 700, 5000])
+def test_wavelet_mean_depends_on_the_heads_alone(binding, heads):
+    """The heads are added in an order that depends on their number only: neither the alignment of `per_head` nor the
+    number of outputs (a multiple of four or not) changes a bit of the mean."""
+    import torch
+
+    g = torch.Generator(device="cuda").manual_seed(heads)
+    a = torch.rand(heads, 8, device="cuda", generator=g)
+    V = torch.randn(heads, 8, 64, device="cuda", generator=g)
+    per_head, mean = binding.wavelet_components(a, V, 1)
+    buf = torch.empty(heads * 8 + 1, device="cuda")
+    per_head1, mean1 = binding.wavelet_components(a, V, 1, per_head=buf[1:].view(heads, 1, 8))
+    per_head6, mean6 = binding.wavelet_components(a[:, :6].contiguous(), V[:, :6].contiguous(), 1)
+    torch.cuda.synchronize()
+    assert torch.equal(per_head1, per_head) and torch.equal(per_head6, per_head[:, :, :6])
+    assert torch.equal(mean1, mean) and torch.equal(mean6, mean[:, :6])
