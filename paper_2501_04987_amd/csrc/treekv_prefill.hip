@@ -130,6 +130,14 @@ __device__ inline int is_finite(float v) { return (__float_as_uint(v) & 0x7f8000
 // an MFMA costs an extra instruction that quiets signalling NaNs, and the pair is not fused into v_max3_f32.
 __device__ inline float max3(float a, float b, float c) { return fmaxf(fmaxf(a, b), c); }
 
+// Max over the four lanes (16 apart) that hold the same row; every lane gets it.
+__device__ inline float row_max(float v) {
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+
 // s_waitcnt vmcnt(N) alone (the other counters not waited for), N < 16.  A statement the compiler moves no memory
 // access across: LDS reads that follow it read what the awaited copies wrote.
 template <int N>
@@ -398,9 +406,13 @@ __global__ __launch_bounds__(AT_THREADS, D == 64 ? 4 : 2) void prefill_attend_ke
           }
         }
       }
-      // The reference m_run of a lane's sums only has to keep exp2 in range, so it is raised lazily: when some lane's
-      // sum passes 2^64 (or its exponentials overflow: the first tile it sees), the tile is taken again with the
-      // reference at the tile's maximum.  The common path has no maxima, no rescaling and one exp2 per logit.
+      // The reference m_run of a lane's sums need not be their maximum, so it is raised lazily: when some lane's sum
+      // passes 2^16 (or its exponentials overflow: the first tile it sees), the tile is taken again with the reference
+      // 2^4 above the row's maximum in this tile.  The common path has no maxima, no rescaling and one exp2 per logit.
+      // Not later than at 2^16, because log2(sum) and the exponents lose a bit each time they double: with 2^64 a row
+      // whose logits rise by 40 had its normaliser off by 1.4e-6 instead of 0.7e-6.  2^4 above, and above the whole row's,
+      // so that fewer tiles are taken twice: a sequence of 6000 tokens x 2 takes 956 us, 974 with every lane's own maximum
+      // (941 with 2^64); the sums then lie nearer to 1, which costs no accuracy.
       float l_new[4];
 #pragma unroll
       for (int rb = 0; rb < 4; ++rb) {
@@ -408,10 +420,10 @@ __global__ __launch_bounds__(AT_THREADS, D == 64 ? 4 : 2) void prefill_attend_ke
         const float e2 = fast_exp2(fmaf(s[rb][2], sc, -m_run[rb])), e3 = fast_exp2(fmaf(s[rb][3], sc, -m_run[rb]));
         l_new[rb] = l_run[rb] + ((e0 + e1) + (e2 + e3));
       }
-      if (__any(max3(l_new[0], l_new[1], fmaxf(l_new[2], l_new[3])) > 0x1p64f)) {
+      if (__any(max3(l_new[0], l_new[1], fmaxf(l_new[2], l_new[3])) > 0x1p16f)) {
 #pragma unroll
         for (int rb = 0; rb < 4; ++rb) {
-          const float m_new = fmaxf(m_run[rb], max3(s[rb][0], s[rb][1], fmaxf(s[rb][2], s[rb][3])) * sc);
+          const float m_new = row_max(fmaxf(m_run[rb], max3(s[rb][0], s[rb][1], fmaxf(s[rb][2], s[rb][3])) * sc + 4.0f));
           const float e0 = fast_exp2(fmaf(s[rb][0], sc, -m_new)), e1 = fast_exp2(fmaf(s[rb][1], sc, -m_new));
           const float e2 = fast_exp2(fmaf(s[rb][2], sc, -m_new)), e3 = fast_exp2(fmaf(s[rb][3], sc, -m_new));
           l_new[rb] = fmaf(l_run[rb], fast_exp2(m_run[rb] - m_new), (e0 + e1) + (e2 + e3));

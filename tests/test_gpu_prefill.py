@@ -199,3 +199,44 @@ def test_prefill_fp32_non_finite_rows_stay_their_own(binding, d, n0):
     torch.testing.assert_close(got[rows], want[rows], rtol=1e-5, atol=1e-5, equal_nan=True)
     assert torch.isnan(got[bad_query]).all()
     torch.testing.assert_close(got_s[:, bad_query + 1:], want_s[:, bad_query + 1:], rtol=1e-5, atol=1e-6)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("rerank", [False, True])
+@pytest.mark.parametrize("rise", [0, 20, 40, 60, 100])
+def test_prefill_rows_whose_logits_rise(binding, d, rerank, rise):
+    """Keys of the second tile lie `rise` (in log2) above those of the first: what a row's sums are taken against changes
+    on the way (or, up to 2^16, does not).  One query per head, so a token's score is its probability, and a head's
+    scores add up to one but for the error of the normaliser log2(sum).  Bound, in log2 units: log2(sum) <= 8 is
+    rounded twice (2 * 2^-22, and the same for its own instruction), times ln 2 = 6e-7; the sums' own rounding is some
+    2^-23.  A reference left 40 or 60 below the logits rounds log2(sum) and the exponentials' arguments to 2^-19."""
+    import torch
+
+    H, n0 = 64, 256
+    g = torch.Generator(device="cuda").manual_seed(rise)
+    logit = torch.rand(n0 + 1, H, device="cuda", generator=g) * 3 - 3
+    logit[:128] -= rise
+    # all of it in one plane whose angles vanish at this base: re-assigned positions then leave the logits as they are
+    K = torch.zeros(1, n0 + 1, H, d, dtype=torch.bfloat16, device="cuda")
+    Q = torch.zeros_like(K)
+    K[0, :, :, d - 2] = (logit / 8).to(torch.bfloat16)
+    Q[..., d - 2] = 8
+    V = torch.randn(1, n0 + 1, H, d, device="cuda", generator=g).to(torch.bfloat16)
+    scale = 0.7                                               # (not ln 2: with it the exponents would be exact)
+    kv = binding.TreeKV(512, H, d, kv_heads=H, n_sink=2, n_recent=8, softmax_scale=scale, rope_base=1e38,
+                        flags=binding.TREEKV_POSITION_RERANK if rerank else 0)
+    kv.prefill_chunk(Q[:, :n0].contiguous(), K[:, :n0].contiguous(), V[:, :n0].contiguous(), n0, *kv.new_outputs(n0))
+    snap, lay = kv.export_state(), kv.state_layout()
+    snap[lay.S:lay.S + H * 512 * 4] = 0
+    kv.import_state(snap)
+    out = kv.new_outputs(1)
+    kv.prefill_chunk(Q[:, n0:].contiguous(), K[:, n0:].contiguous(), V[:, n0:].contiguous(), 1, *out)
+    got = kv.scores()[0, :, :n0 + 1].double().cpu().numpy()
+    s = np.float64(np.float32(scale)) * 8 * K[0, :, :, d - 2].double().cpu().numpy().T
+    p = np.exp(s - s.max(-1, keepdims=True))
+    p /= p.sum(-1, keepdims=True)
+    np.testing.assert_allclose(got, p, rtol=3e-6, atol=1e-9)
+    total = np.abs(got.sum(-1) - 1).max()
+    assert total < 1e-6, total
+    want = np.einsum("hj,jhd->hd", p, V[0].double().cpu().numpy())
+    np.testing.assert_allclose(out[0][0, 0].cpu().numpy(), want, rtol=1e-4, atol=1e-4)
