@@ -220,10 +220,13 @@ __device__ inline unsigned lds_address(const void* shared_ptr) {
 // every wave has formed its logits from it).  Everything after the logits is unchanged.
 //
 // head_dim 64 leaves room for two workgroups per compute unit (66 KB of LDS each) if the registers are held to 128: two
-// sequences of 6000 tokens, 8 KV heads x 4, into 4096 slots take 945 us in chunks of 512 (1406 with one workgroup of 165
-// registers and the longer instruction stream).
+// sequences of 6000 tokens, 8 KV heads x 4, into 4096 slots take 956 us in chunks of 512 (1406 with one workgroup of 165
+// registers and the longer instruction stream).  With ROPE 128 registers are not enough: 28 spill, and the wait for a reload
+// in sweep 1 waits for the tiles requested ahead too.  One workgroup of 150 registers: 74.5 us a call at 32 heads, 512 into
+// 2048 slots (87.7 with two of 128), 36.7 at 8 heads, 17 into 1024 (45.1), 468 at batch 8 (479); one case is slower, two
+// sequences of 8 KV heads x 4 into 1024 slots, 86.3 (84.4).
 template <int D, bool ROPE>
-__global__ __launch_bounds__(AT_THREADS, D == 64 ? 4 : 2) void prefill_attend_kernel(Params p, const uint16_t* __restrict__ Q,
+__global__ __launch_bounds__(AT_THREADS, D == 64 && !ROPE ? 4 : 2) void prefill_attend_kernel(Params p, const uint16_t* __restrict__ Q,
                                                                     const uint16_t* __restrict__ Kc,
                                                                     const uint16_t* __restrict__ Vc, int L,
                                                                     int row_tiles, float* __restrict__ out) {

@@ -93,6 +93,15 @@ def test_prefill_len1_equals_decode(binding, oracle):
     assert (a.scores() - b.scores()).abs().max().item() < 1e-3
 
 
+@pytest.mark.parametrize("free", [127, 128, 129, 143, 255, 399])
+@pytest.mark.parametrize("d", [64, 128])
+def test_prefill_free_slot_at_a_tile_edge(binding, oracle, d, free):
+    """A full cache of 400 slots (three whole tiles and a part) whose free slot lies at the edge of a 128-column tile, of a
+    wave's 16 columns, or at the end: two tree slots, the right one of which the decode step frees (keep-left)."""
+    _run(binding, oracle, [400, 0, 130, 0, 64], B=1, H=2, Hkv=2, d=d, budget=400, n_sink=free - 1,
+         n_recent=400 - free - 1, max_chunk=400, seed=24, flags=binding.TREEKV_KEEP_LEFT)
+
+
 def test_prefill_argument_errors(binding):
     import torch
 
