@@ -150,7 +150,7 @@ int treekv_decode_step(treekv_ctx* ctx, const void* q, const void* k, const void
  * treekv_decode_step_static - treekv_decode_step with the same arguments, results and kernels, for callers that can
  * neither allocate device memory nor hand the library scratch of their own for this: code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc.  The only scratch a decode step uses -- the scaled logits
- * [U][c+1][G] float32 and the per-slice partial results [U][kv_splits][G][d+2] float32 that the split shape
+ * [U * G * (c+1)] float32 and the per-slice partial results [U][kv_splits][G][d+2] float32 that the split shape
  * (kv_splits > 1) passes between its workgroups -- lives in a fixed array of
  * TREEKV_STATIC_SCRATCH_BYTES inside the library's device image instead of the bound workspace (the fused
  * shape, kv_splits = 1, uses none).  Each GPU holds one such array until the process ends; every call on a GPU,

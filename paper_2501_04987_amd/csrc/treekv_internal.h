@@ -46,7 +46,7 @@ struct Params {
   int* PE;                  // [U][2m] positions of the tree region
   int* R;                   // [U][max(n_recent,1)]
   int* meta;                // [U][META_STRIDE]
-  float* logits;            // [U][cap][G]   split decode scratch: scaled logits (log2 domain)
+  float* logits;            // split decode scratch: scaled logits (log2 domain), [U][cap][G]; G = 8: [U][2][cap][4]
   float* partial;           // [U][nsplit][G][D+2] split decode scratch: a slice's partial (acc, max, sum)
   // prefill scratch
   unsigned long long* pf_colacc;   // [U][cache columns | chunk columns, each rounded up to 128] column sums of the chunk in flight, fixed point
