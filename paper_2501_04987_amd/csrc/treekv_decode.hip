@@ -6,10 +6,10 @@
 //          in LDS, scores and tree positions are prefetched into registers before the streaming
 //          starts, so the epilogue (score update, eviction, retained list) waits for no global
 //          load.  Used when U alone fills the chip.
-//   SPLIT  one kernel too.  grid = (nsplit, U) workgroups of 512 threads each stream a slice of the unit's
+//   SPLIT  grid = (nsplit, U) workgroups of 512 threads each stream a slice of the unit's
 //          slots and write a partial (output accumulator, max, sum) plus the slice's logits to scratch; the workgroup
-//          of a unit that is done last merges the slices and runs the epilogue (see decode_split_kernel).  No
-//          workgroup ever waits for another one.
+//          of a unit that is done last merges the slices and runs the epilogue (see decode_split_kernel), or, with more
+//          workgroups than the chip holds at once, a second kernel does.  No workgroup ever waits for another one.
 //
 // Streaming.  Rows are 16-byte lane loads: LPR lanes cover one row, a wave load covers 64/LPR
 // whole rows, a tile is KU wave loads of K and of V, double buffered.  q.k is reduced inside
@@ -929,103 +929,19 @@ __device__ inline float4 get_shared4(__amdgpu_buffer_rsrc_t r, int float_index) 
   return make_float4(__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w));
 }
 
-// SPLIT shape.  Every workgroup streams its slice, leaves its partial result and its logits ([slot][G]) in scratch, counts
-// itself in and writes its share of the retained list (all but the entry the decision fills in); the one that finds
-// all others counted merges.  Order: a wave's scratch stores have reached memory (s_waitcnt vmcnt(0)) before
-// the workgroup's barrier, the barrier is before the count, and the count's old value is known before the last
-// workgroup's first load; every access to the scratch and the counter is an agent-scope atomic.  All reads of state the
-// epilogue overwrites (rows, bookkeeping words, order arrays) are over when the unit's last workgroup counts itself in.
-// The merge is latency and the length of one workgroup's instruction stream: everything it needs is requested in one go,
-// and code that would spare it loads (the own slice's logits from LDS, the old scores requested mid-stream) was slower by
-// more than it saved.  32 units x 1024 slots: 9.6 us per step, of which the merge is 2.7 (13.1 with the merge as a second
-// kernel of one workgroup per unit); 128 units x 4096 slots x G = 4: 53.0 us, merge 5 (56.3).
-template <typename T, int D, int G, int ROPE>
-__global__ __launch_bounds__(SPLIT_THREADS) void decode_split_kernel(Params p, const T* __restrict__ q_in,
-                                                                     const T* __restrict__ k_in,
-                                                                     const T* __restrict__ v_in,
-                                                                     float* __restrict__ out,
-                                                                     int32_t* __restrict__ retained,
-                                                                     int32_t* __restrict__ n_retained,
-                                                                     int32_t* __restrict__ evicted) {
-  constexpr int THREADS = SPLIT_THREADS;
-  using St = typename PickStream<T, D, G, THREADS, ROPE>::type;
-  constexpr int WAVES = St::WAVES;
-  constexpr int LPR = D / Storage<T>::EPL;
-  constexpr int MAX_SPLITS = 64;
-  extern __shared__ __attribute__((aligned(16))) float smem[];
-  float* sm_acc = smem;
-  float* sm_wm = sm_acc + WAVES * G * D;
-  float* sm_wl = sm_wm + WAVES * G;
-  float* sm_s = smem + St::LDS_FLOATS_FIXED;   // [G][rows_per_split]
-  __shared__ float2 sm_ml[MAX_SPLITS * G];
-  __shared__ float sm_sc[2];
-  __shared__ int sm_last;
-
-  const int split = blockIdx.x, unit = blockIdx.y, tid = threadIdx.x;
-  int* meta = p.meta + (size_t)unit * META_STRIDE;
-  const int* PEu = p.PE + (size_t)unit * 2 * p.m;
-  const T* knew = k_in + (size_t)unit * D;
-  const T* vnew = v_in + (size_t)unit * D;
-  Step st;
-  int begin, end;
-  St::run(p, unit, split * p.rows_per_split, q_in, knew, vnew, meta, sm_s, p.rows_per_split, sm_acc, sm_wm, sm_wl, st, begin,
-          end, false, [](const Step&) {}, []() {});
-  // the eviction scope, and this slice's share of the retained list: on their way while the waves' results are merged
-  load_scope(p, st, p.E + (size_t)unit * 2 * p.m, PEu, p.R + (size_t)unit * max(p.n_recent, 1));
-  const int ret_n = (p.budget + p.nsplit - 1) / p.nsplit, ret_0 = split * ret_n, ret_1 = min(ret_0 + ret_n, p.budget);
-  constexpr int RET = 4;                       // entries a thread requests up front
-  int pe_pre[RET];
-#pragma unroll
-  for (int x = 0; x < RET; ++x) {
-    const int i = ret_0 + tid + x * THREADS;
-    if (i < ret_1) pe_pre[x] = position_of(p, st, PEu, i, -1, true);
-  }
-  __syncthreads();
-
-  // ---- this slice's results -> scratch ----
-  float* parts = p.partial + (size_t)unit * p.nsplit * G * (D + 2);
-  float* lg = p.logits + (size_t)unit * G * p.cap;
+// A unit's slices merged by one workgroup, then the step's epilogue: every load, then the arithmetic.  The caller has
+// written the retained list except for the entry the decision fills in.  Everything is requested in one go; code that would
+// spare loads (the own slice's logits from LDS, the old scores requested mid-stream) was slower by more than it saved.
+constexpr int MAX_SPLITS = 64;
+template <typename T, int D, int G>
+__device__ inline void merge_slices(const Params& p, int unit, const Step& st, const T* knew, const T* vnew, int* meta,
+                                    float2* sm_ml, float* sm_sc, float* __restrict__ out, int32_t* __restrict__ retained,
+                                    int32_t* __restrict__ n_retained, int32_t* __restrict__ evicted) {
+  constexpr int THREADS = SPLIT_THREADS, LPR = D / Storage<T>::EPL;
+  const int tid = threadIdx.x;
+  const float* parts = p.partial + (size_t)unit * p.nsplit * G * (D + 2);
+  const float* lg = p.logits + (size_t)unit * G * p.cap;
   const __amdgpu_buffer_rsrc_t lg_rsrc = shared_rsrc(lg, (size_t)G * p.cap);
-  for (int r = tid; r < end - begin; r += THREADS) {
-    float* dst = lg + (size_t)(begin + r) * G;
-    if constexpr (G == 1) put_shared(dst, sm_s[r]);
-    else if constexpr (G == 2) put_shared2(dst, sm_s[r], sm_s[(size_t)p.rows_per_split + r]);
-    else
-#pragma unroll
-      for (int g = 0; g < G; g += 4) {
-        const float* src = sm_s + (size_t)g * p.rows_per_split + r;
-        put_shared4(lg_rsrc, g * p.cap + (begin + r) * 4, src[0], src[p.rows_per_split], src[2 * p.rows_per_split], src[3 * p.rows_per_split]);
-      }
-  }
-  for (int i = tid; i < G * D; i += THREADS) {
-    const int g = i / D, col = i % D;
-    float M, L;
-    merge_stats(sm_wm + g, sm_wl + g, WAVES, G, M, L);
-    float a = 0.f;
-    for (int w = 0; w < WAVES; ++w) a += sm_acc[(w * G + g) * D + col] * fast_exp2(sm_wm[w * G + g] - M);
-    float* part = parts + ((size_t)split * G + g) * (D + 2);
-    put_shared(part + col, a);
-    if (col == 0) put_shared2(part + D, M, L);
-  }
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  __syncthreads();
-  if (tid == 0)
-    sm_last = __hip_atomic_fetch_add(meta + META_ARRIVED, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == p.nsplit - 1;
-  {
-    int32_t* ret = retained + (size_t)unit * p.budget;
-    const int open = st.evict ? p.n_sink + st.j0 : -1;       // the last workgroup's to write, and nobody else's
-#pragma unroll
-    for (int x = 0; x < RET; ++x) {
-      const int i = ret_0 + tid + x * THREADS;
-      if (i < ret_1 && i != open) ret[i] = pe_pre[x];
-    }
-    for (int i = ret_0 + RET * THREADS + tid; i < ret_1; i += THREADS)
-      if (i != open) ret[i] = position_of(p, st, PEu, i, -1, true);   // (no entry the last workgroup writes is read here)
-  }
-  __syncthreads();
-  if (!sm_last) return;
-
-  // ---- the unit's last workgroup: every load of the merge, then its arithmetic ----
   float* Su = p.S + (size_t)unit * p.cap;
   float2 ml = make_float2(NEG_BIG, 0.f);
   if (tid < p.nsplit * G) ml = get_shared2(parts + (size_t)tid * (D + 2) + D);     // entry tid is slice tid / G, head tid % G
@@ -1117,10 +1033,145 @@ __global__ __launch_bounds__(SPLIT_THREADS) void decode_split_kernel(Params p, c
       out[((size_t)b * p.H + (size_t)kvh * G + g) * D + col] = a * il;
     }
   }
-  if (tid == 0) __hip_atomic_store(meta + META_ARRIVED, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __syncthreads();
   if ((tid & 63) != 0 || tid >= 256) return;
   settle(p, unit, st, sm_sc[0], sm_sc[1], retained, n_retained, evicted, meta, 192);
+}
+
+// SPLIT shape.  Every workgroup streams its slice, leaves its partial result and its logits ([slot][G]) in scratch, counts
+// itself in and writes its share of the retained list (all but the entry the decision fills in); the one that finds
+// all others counted merges.  Order: a wave's scratch stores have reached memory (s_waitcnt vmcnt(0)) before
+// the workgroup's barrier, the barrier is before the count, and the count's old value is known before the last
+// workgroup's first load; every access to the scratch and the counter is an agent-scope atomic.  All reads of state the
+// epilogue overwrites (rows, bookkeeping words, order arrays) are over when the unit's last workgroup counts itself in.
+// The merge is latency and the length of one workgroup's instruction stream.  32 units x 1024 slots: 9.6 us per step, of
+// which the merge is 2.7 (13.1 with the merge as a second kernel of one workgroup per unit); 128 units x 4096 slots x G = 4:
+// 53.0 us, merge 5 (56.3).
+//
+// MERGE = false: the merge is a kernel of its own.  The drain and the count at the end of a workgroup are time in which the
+// next one does not run, and the merge's registers leave room for fewer, so once workgroups take turns on the compute units
+// two kernels are faster: from split_one_kernel on.
+template <typename T, int D, int G, int ROPE>
+constexpr int split_one_kernel() {
+  // Workgroups the 256 compute units hold at once: two each where a thread has at most 128 registers, else one; in the
+  // instance that spills (8 heads, positions re-assigned) fewer than that already.  Measured, one kernel against two, us:
+  //   G = 1, 128: 256 units x 512 slots, 2 slices 16.7 / 17.6; 3 slices (2048 slots) 55.9 / 50.7; 16 slices 62.0 / 34.5
+  //   G = 4, 128: 128 units x 1024, 2 slices 20.4 / 21.6; 152 units x 2048, 2 slices 52.8 / 49.9; 64 x 4096, 8 slices 41.9 / 38.3
+  //   G = 4, 64:  256 units x 1024, 2 slices 21.2 / 21.8; 128 x 2048, 4 slices 22.7 / 23.1
+  //   G = 8, 128, re-assigned: 64 units x 8192, 3 slices 252.6 / 263.5; 128 x 4096, 2 slices 200.2 / 188.6
+  constexpr bool two = G == 1 || (sizeof(T) == 4 ? G == 2 : G <= 4 && D == 64 && ROPE == ROPE_OFF);
+  return two ? 512 : G == 8 && ROPE != ROPE_OFF ? 255 : 256;
+}
+template <typename T, int D, int G, int ROPE, bool MERGE>
+__global__ __launch_bounds__(SPLIT_THREADS) void decode_split_kernel(Params p, const T* __restrict__ q_in,
+                                                                     const T* __restrict__ k_in,
+                                                                     const T* __restrict__ v_in,
+                                                                     float* __restrict__ out,
+                                                                     int32_t* __restrict__ retained,
+                                                                     int32_t* __restrict__ n_retained,
+                                                                     int32_t* __restrict__ evicted) {
+  constexpr int THREADS = SPLIT_THREADS;
+  using St = typename PickStream<T, D, G, THREADS, ROPE>::type;
+  constexpr int WAVES = St::WAVES;
+  extern __shared__ __attribute__((aligned(16))) float smem[];
+  float* sm_acc = smem;
+  float* sm_wm = sm_acc + WAVES * G * D;
+  float* sm_wl = sm_wm + WAVES * G;
+  float* sm_s = smem + St::LDS_FLOATS_FIXED;   // [G][rows_per_split]
+  __shared__ float2 sm_ml[MERGE ? MAX_SPLITS * G : 1];
+  __shared__ float sm_sc[2];
+  __shared__ int sm_last;
+
+  const int split = blockIdx.x, unit = blockIdx.y;
+  int* meta = p.meta + (size_t)unit * META_STRIDE;
+  const int* PEu = p.PE + (size_t)unit * 2 * p.m;
+  const T* knew = k_in + (size_t)unit * D;
+  const T* vnew = v_in + (size_t)unit * D;
+  Step st;
+  int begin, end;
+  St::run(p, unit, split * p.rows_per_split, q_in, knew, vnew, meta, sm_s, p.rows_per_split, sm_acc, sm_wm, sm_wl, st, begin,
+          end, false, [](const Step&) {}, []() {});
+  int tid = threadIdx.x;
+  if constexpr (!MERGE) asm volatile("" : "+v"(tid));    // nothing of what follows is held in registers through the stream
+  // the eviction scope, and this slice's share of the retained list: on their way while the waves' results are merged
+  if constexpr (MERGE) load_scope(p, st, p.E + (size_t)unit * 2 * p.m, PEu, p.R + (size_t)unit * max(p.n_recent, 1));
+  const int ret_n = (p.budget + p.nsplit - 1) / p.nsplit, ret_0 = split * ret_n, ret_1 = min(ret_0 + ret_n, p.budget);
+  constexpr int RET = 4;                       // entries a thread requests up front
+  int pe_pre[RET];
+#pragma unroll
+  for (int x = 0; x < RET; ++x) {
+    const int i = ret_0 + tid + x * THREADS;
+    if (MERGE && i < ret_1) pe_pre[x] = position_of(p, st, PEu, i, -1, true);
+  }
+  __syncthreads();
+
+  // ---- this slice's results -> scratch ----
+  float* parts = p.partial + (size_t)unit * p.nsplit * G * (D + 2);
+  float* lg = p.logits + (size_t)unit * G * p.cap;
+  const __amdgpu_buffer_rsrc_t lg_rsrc = shared_rsrc(lg, (size_t)G * p.cap);
+  for (int r = tid; r < end - begin; r += THREADS) {
+    float* dst = lg + (size_t)(begin + r) * G;
+    if constexpr (G == 1) put_shared(dst, sm_s[r]);
+    else if constexpr (G == 2) put_shared2(dst, sm_s[r], sm_s[(size_t)p.rows_per_split + r]);
+    else
+#pragma unroll
+      for (int g = 0; g < G; g += 4) {
+        const float* src = sm_s + (size_t)g * p.rows_per_split + r;
+        put_shared4(lg_rsrc, g * p.cap + (begin + r) * 4, src[0], src[p.rows_per_split], src[2 * p.rows_per_split], src[3 * p.rows_per_split]);
+      }
+  }
+  for (int i = tid; i < G * D; i += THREADS) {
+    const int g = i / D, col = i % D;
+    float M, L;
+    merge_stats(sm_wm + g, sm_wl + g, WAVES, G, M, L);
+    float a = 0.f;
+    for (int w = 0; w < WAVES; ++w) a += sm_acc[(w * G + g) * D + col] * fast_exp2(sm_wm[w * G + g] - M);
+    float* part = parts + ((size_t)split * G + g) * (D + 2);
+    put_shared(part + col, a);
+    if (col == 0) put_shared2(part + D, M, L);
+  }
+  if constexpr (!MERGE) return;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (tid == 0)
+    sm_last = __hip_atomic_fetch_add(meta + META_ARRIVED, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == p.nsplit - 1;
+  {
+    int32_t* ret = retained + (size_t)unit * p.budget;
+    const int open = st.evict ? p.n_sink + st.j0 : -1;       // the last workgroup's to write, and nobody else's
+#pragma unroll
+    for (int x = 0; x < RET; ++x) {
+      const int i = ret_0 + tid + x * THREADS;
+      if (i < ret_1 && i != open) ret[i] = pe_pre[x];
+    }
+    for (int i = ret_0 + RET * THREADS + tid; i < ret_1; i += THREADS)
+      if (i != open) ret[i] = position_of(p, st, PEu, i, -1, true);   // (no entry the last workgroup writes is read here)
+  }
+  __syncthreads();
+  if (!sm_last) return;
+  if (tid == 0) __hip_atomic_store(meta + META_ARRIVED, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  merge_slices<T, D, G>(p, unit, st, knew, vnew, meta, sm_ml, sm_sc, out, retained, n_retained, evicted);
+}
+
+// The merge as a kernel of its own, behind a decode_split_kernel with MERGE = false.
+template <typename T, int D, int G>
+__global__ __launch_bounds__(SPLIT_THREADS) void decode_merge_kernel(Params p, const T* __restrict__ k_in,
+                                                                     const T* __restrict__ v_in, float* __restrict__ out,
+                                                                     int32_t* __restrict__ retained,
+                                                                     int32_t* __restrict__ n_retained,
+                                                                     int32_t* __restrict__ evicted) {
+  __shared__ float2 sm_ml[MAX_SPLITS * G];
+  __shared__ float sm_sc[2];
+  const int unit = blockIdx.x, tid = threadIdx.x;
+  int* meta = p.meta + (size_t)unit * META_STRIDE;
+  const int* PEu = p.PE + (size_t)unit * 2 * p.m;
+  Step st = load_meta(p, meta);
+  load_scope(p, st, p.E + (size_t)unit * 2 * p.m, PEu, p.R + (size_t)unit * max(p.n_recent, 1));
+  const int open = st.evict ? p.n_sink + st.j0 : -1;
+#pragma unroll 4
+  for (int i = tid; i < p.budget; i += SPLIT_THREADS)
+    if (i != open) retained[(size_t)unit * p.budget + i] = position_of(p, st, PEu, i, -1, true);
+  merge_slices<T, D, G>(p, unit, st, k_in + (size_t)unit * D, v_in + (size_t)unit * D, meta, sm_ml, sm_sc, out, retained,
+                        n_retained, evicted);
 }
 
 template <typename T, int D, int G, int ROPE>
@@ -1142,12 +1193,16 @@ int launch_decode_g(const Params& p, const void* q, const void* k, const void* v
     using St = typename PickStream<T, D, G, SPLIT_THREADS, ROPE>::type;
     const size_t lds = St::lds_floats(p.cap, p.rows_per_split) * sizeof(float);
     if (lds > LDS_LIMIT) return TREEKV_EUNSUPPORTED;
-    auto kern = decode_split_kernel<T, D, G, ROPE>;
+    const bool one_kernel = p.nsplit * p.U <= split_one_kernel<T, D, G, ROPE>();
+    auto kern = one_kernel ? decode_split_kernel<T, D, G, ROPE, true> : decode_split_kernel<T, D, G, ROPE, false>;
     if (lds > 48 * 1024 &&
         hip_failed(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)))
       return TREEKV_EHIP;
     hipLaunchKernelGGL(kern, dim3(p.nsplit, p.U), dim3(SPLIT_THREADS), lds, s, p, qt, kt, vt, out, retained, n_retained,
                        evicted);
+    if (!one_kernel)
+      hipLaunchKernelGGL((decode_merge_kernel<T, D, G>), dim3(p.U), dim3(SPLIT_THREADS), 0, s, p, kt, vt, out, retained,
+                         n_retained, evicted);
   }
   return finish_launch();
 }

@@ -240,3 +240,38 @@ def test_split_shape_in_a_captured_graph(binding):
         torch.cuda.synchronize()
         for u, v in zip(oa, ob):
             assert torch.equal(u, v), t
+
+
+@pytest.mark.parametrize("G,d,dtype,budget,splits,rerank", [
+    (1, 128, "bf16", 70, 64, False),     # 640 workgroups, most of them without a slot
+    (1, 64, "bf16", 1030, 52, True),     # 520, eight more than are held at once
+    (2, 64, "f32", 515, 52, False),
+    (4, 128, "bf16", 4700, 26, False),   # 260, four more; slots beyond the merge's first batch
+    (8, 128, "bf16", 2100, 26, True),    # two outputs per merging thread
+])
+def test_split_merge_as_a_second_kernel(binding, oracle, G, d, dtype, budget, splits, rerank):
+    """More workgroups than the chip holds at once: the slices are merged by a kernel of their own.  Every step's outputs,
+    evictions and retained list; the entry point with the library's own scratch takes the same steps bit for bit."""
+    import torch
+
+    B, fill, steps = 5, [512] * (budget // 512) + [budget % 512], 6
+    T = budget + steps
+    Q, K, V = inputs.batch_streams("lowrank" if dtype == "bf16" else "iid", 43, T, B, 2, G, d, dtype=dtype)
+    kw = dict(kv_heads=2, batch=B, dtype=dtype, n_sink=3, n_recent=budget // 3, kv_splits=splits,
+              flags=binding.TREEKV_POSITION_RERANK if rerank else 0)
+    kv = binding.TreeKV(budget, 2 * G, d, **kw)
+    assert kv.cfg.kv_splits == splits
+    st = ph.run_schedule(oracle, kv, Q, K, V, fill + [0] * steps, dtype=dtype, units=[(0, 0), (B - 1, 1)])
+    assert st["flagged"] <= 2
+    ph.compare_scores(kv, st["results"], dtype)
+    other = binding.TreeKV(budget, 2 * G, d, **kw)
+    other.import_state(kv.export_state())
+    x = [ph.to_device(t[0], dtype) for t in (Q, K, V)]
+    oa, ob = kv.new_outputs(), other.new_outputs()
+    for _ in range(3):
+        kv.decode_step(*x, *oa)
+        other.decode_step_static(*x, *ob)
+    torch.cuda.synchronize()
+    for u, v in zip(oa, ob):
+        assert torch.equal(u, v)
+    assert torch.equal(kv.export_state(), other.export_state())
