@@ -238,7 +238,7 @@ def side_shape(torch, binding, inputs, dev, name, peaks, rerank=False, steps=40,
             "roofline": roofline("hbm", r["achieved_GBs"], HBM_PEAK_GBS, "GB/s", peaks and peaks["hbm_read_GBs"],
                                  bytes_per_launch=r["bytes_per_launch"],
                                  note="per layer-step: HIP-event time of the timed region / (steps x layers); "
-                                      + ("one kernel per layer-step" if r["kv_splits"] == 1 else "two kernels per layer-step (slices, then merge)"))}
+                                      + ("one kernel per layer-step" if r["kv_splits"] == 1 else "one kernel per layer-step: slices, merged by the last workgroup of a unit"))}
 
 
 # ------------------------------------------------------------------------------------------------------------

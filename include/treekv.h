@@ -151,12 +151,12 @@ int treekv_decode_step(treekv_ctx* ctx, const void* q, const void* k, const void
  * neither allocate device memory nor hand the library scratch of their own for this: code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc.  The only scratch a decode step uses -- the scaled logits
  * [U * G * (c+1)] float32 and the per-slice partial results [U][kv_splits][G][d+2] float32 that the split shape
- * (kv_splits > 1) passes between its workgroups -- lives in a fixed array of
+ * (kv_splits > 1) passes from its slices' workgroups to the one that merges a unit -- lives in a fixed array of
  * TREEKV_STATIC_SCRATCH_BYTES inside the library's device image instead of the bound workspace (the fused
  * shape, kv_splits = 1, uses none).  Each GPU holds one such array until the process ends; every call on a GPU,
  * from any context, shares it: calls that may overlap on one GPU (different streams without ordering) race and
  * must not both use this entry point.  Nothing in the array has to survive from one call to the next and nothing
- * has to start at zero (the first kernel writes every word the second reads).  No hipMalloc, hipFree or other
+ * has to start at zero (whoever merges a unit reads only words its slices' workgroups wrote in the same call).  No hipMalloc, hipFree or other
  * allocating call is made; the array's address is looked up once per device, on the first call there.
  * Errors: as treekv_decode_step, and TREEKV_ESCRATCH (nothing enqueued) if the context's logits and partials
  * exceed TREEKV_STATIC_SCRATCH_BYTES.
@@ -204,7 +204,7 @@ int treekv_prefill_chunk(treekv_ctx* ctx, const void* Q, const void* K, const vo
  *   n_retained [B, Hkv] int32 (may be NULL)
  *   evicted_blocks [B, Hkv, len / block] int32 (may be NULL): the block evicted when block i was
  *              appended, or -1
- *   token_scores [B, Hkv, len] float32 (may be NULL): the tokens' averaged window attention
+ *   token_scores [B, Hkv, len] float32 (may be NULL): the tokens' averaged window attention; written only
  * With fp32 storage the window's scores are computed on the vector ALUs, one window query at a time (not a
  * fast path), for len <= 32768.
  * Errors: TREEKV_EINVAL unless 1 <= block <= len <= max_prompt, block divides len and budget, and

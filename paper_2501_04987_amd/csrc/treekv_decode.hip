@@ -47,29 +47,6 @@ constexpr size_t LDS_LIMIT = 150 * 1024;   // of the 160 KB a workgroup can have
 
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
 
-template <int CTRL>
-__device__ inline float dpp_add(float v) {
-  const int moved = __builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false);
-  return v + __int_as_float(moved);
-}
-
-// Sum over the LPR consecutive lanes that hold one row; every lane of the group gets the total.
-template <int LPR>
-__device__ inline float group_sum(float v) {
-  if constexpr (LPR == 8) {
-    v = dpp_add<0x141>(v);           // row_half_mirror: i <-> 7-i
-    v = dpp_add<0x1B>(v);            // quad_perm [3,2,1,0]
-    v = dpp_add<0xB1>(v);            // quad_perm [1,0,3,2]
-  } else {
-    v = dpp_add<0x128>(v);           // row_ror:8 (rotate inside each 16-lane row)
-    v = dpp_add<0x124>(v);           // row_ror:4
-    v = dpp_add<0x122>(v);           // row_ror:2
-    v = dpp_add<0x121>(v);           // row_ror:1
-    if constexpr (LPR == 32) v += __shfl_xor(v, 16, 64);
-  }
-  return v;
-}
-
 // q.k over one lane's 16 bytes.
 template <typename T> struct Dot;
 template <> struct Dot<uint16_t> {

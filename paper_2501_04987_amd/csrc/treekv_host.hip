@@ -381,9 +381,9 @@ int static_scratch(void** out) {
 int pick_splits(const treekv_config& c) {
   // With about 200 units or more, one 512-thread workgroup per unit fills the 256 compute units and
   // keeps the whole step in one kernel.  Below that, split every unit's slots over a few 512-thread
-  // workgroups (about 160 workgroups in all: 128 units -> 2 slices, 32 units -> 5, where 1, 2, 4, 5, 6, 8 and 12 slices
-  // of 1024 slots take 17.6, 12.8, 10.2, 9.6, 9.2, 9.5 and 10.4 us), but keep a slice at 128 slots or more (below that
-  // the merge costs more than the streaming it spreads).
+  // workgroups, about 160 in all (128 units -> 2 slices, 32 units -> 5), but keep a slice at 128 slots or more.  The
+  // constants were fitted when the merge was a second kernel of 7-10 us and have not been since: at 32 units x 1024 slots
+  // 1, 2, 4, 5, 6, 8 and 12 slices take 17.6, 12.8, 10.2, 9.6, 9.2, 9.5 and 10.4 us.
   const int units = c.batch * c.kv_heads;
   if (units >= 192) return 1;
   int splits = (160 + units - 1) / units;
@@ -505,7 +505,7 @@ int treekv_decode_step_static(treekv_ctx* ctx, const void* q, const void* k, con
   if (!ctx->bound) return TREEKV_ENOWS;
   tkv::Params p = ctx->p;
   size_t lg = 0;
-  if (p.nsplit > 1) {                       // the one-kernel shape keeps its logits in LDS and needs no scratch
+  if (p.nsplit > 1) {                       // the fused shape keeps its logits in LDS and needs no scratch
     lg = tkv::align_up((size_t)p.U * p.G * p.cap * sizeof(float));
     const size_t pt = tkv::align_up((size_t)p.U * p.nsplit * p.G * (size_t)(p.D + 2) * sizeof(float));
     if (lg + pt > (size_t)TREEKV_STATIC_SCRATCH_BYTES) return TREEKV_ESCRATCH;

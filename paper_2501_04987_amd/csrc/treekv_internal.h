@@ -119,6 +119,29 @@ template <> struct Storage<float> {
 
 __device__ inline float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
+template <int CTRL>
+__device__ inline float dpp_add(float v) {
+  const int moved = __builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false);
+  return v + __int_as_float(moved);
+}
+
+// Sum over LPR consecutive lanes (8, 16 or 32); every lane of the group gets the total.
+template <int LPR>
+__device__ inline float group_sum(float v) {
+  if constexpr (LPR == 8) {
+    v = dpp_add<0x141>(v);           // row_half_mirror: i <-> 7-i
+    v = dpp_add<0x1B>(v);            // quad_perm [3,2,1,0]
+    v = dpp_add<0xB1>(v);            // quad_perm [1,0,3,2]
+  } else {
+    v = dpp_add<0x128>(v);           // row_ror:8 (rotate inside each 16-lane row)
+    v = dpp_add<0x124>(v);           // row_ror:4
+    v = dpp_add<0x122>(v);           // row_ror:2
+    v = dpp_add<0x121>(v);           // row_ror:1
+    if constexpr (LPR == 32) v += __shfl_xor(v, 16, 64);
+  }
+  return v;
+}
+
 // Tree-region index k (0 <= k < m) -> index into E / PE, after j_done evictions of the
 // current round (0 <= j_done <= m; a round that just ended reads the same either way).
 __device__ inline int tree_index(int k, int j_done) { return k < j_done ? k : k + j_done; }

@@ -5,7 +5,7 @@
 // scores are then frozen and Algorithm 1's append / compare / evict / advance
 // is replayed for the L tokens.  L = 1 gives the decode step.
 //
-// Two launches per chunk:
+// Three launches per chunk (with re-assigned positions a fourth before them, which turns keys and queries):
 //   attend   grid row tiles x G x U (ids remapped so that a unit's row tiles share an XCD's L2).  Two passes
 //            over all visible columns with MFMA (16x16x32 bf16): the first finds the row statistics, the
 //            second forms the final probabilities, O^T += V^T P^T with P split into two bf16 halves
@@ -17,8 +17,9 @@
 //            accumulators, then Algorithm 1's eviction for the chunk's tokens with frozen scores.  Inside one
 //            sweep of idx over the tree region the scopes are disjoint pairs, so a sweep is one
 //            parallel pass; sweeps run one after the other.  Then surviving chunk tokens are
-//            matched with freed slots (ballot ranks), the order arrays are rewritten, the retained
-//            positions emitted and the surviving chunk rows copied into their slots.
+//            matched with freed slots (ballot ranks), the order arrays are rewritten and the retained
+//            positions emitted.
+//   scatter  one wave per chunk token: the surviving rows are copied into their slots.
 //
 // Token ids during the replay: a slot number (< cap) for a cached token, cap + i for chunk
 // token i that has no slot yet.
@@ -82,19 +83,8 @@ struct AttendLds {
   static constexpr size_t BYTES = 4 * (size_t)TILE_ELEMS * sizeof(uint16_t) + COLBUF_FLOATS * sizeof(float);
 };
 
-template <int CTRL>
-__device__ inline float dpp_add(float v) {
-  const int moved = __builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false);
-  return v + __int_as_float(moved);
-}
 // Sum over the 16 lanes of a DPP row; every lane gets the total.
-__device__ inline float row16_sum(float v) {
-  v = dpp_add<0x128>(v);           // row_ror:8
-  v = dpp_add<0x124>(v);           // row_ror:4
-  v = dpp_add<0x122>(v);           // row_ror:2
-  v = dpp_add<0x121>(v);           // row_ror:1
-  return v;
-}
+__device__ inline float row16_sum(float v) { return group_sum<16>(v); }
 // Sums of eight values over the 16 lanes of a DPP row, shared out: lane lr gets those of x[2 (lr / 4)] and x[2 (lr / 4) + 1].
 // Halving the values with the lanes (a masked add writes one value's sum into half of the lanes, another value's into
 // the other half) takes 16 adds where eight full sums take 32.  One statement, because the instructions' distances are
@@ -191,8 +181,8 @@ __device__ inline unsigned lds_address(const void* shared_ptr) {
 //
 // Sweep 1 finds every row's softmax statistics (max, sum).  Wave w takes the 16-column block w of every
 // tile against all 64 rows (four 16-row MFMA blocks): S^T = K Q^T, K rows from LDS as A operands.  Each
-// lane keeps a running (max, sum) for its own columns of its four rows; lanes and waves are merged once,
-// at the end.  Four K stages, so tiles are requested three iterations before they are used.
+// lane keeps a (reference, sum) for its own columns of its four rows, the reference raised lazily; lanes and waves are
+// merged once, at the end.  Four K stages, so tiles are requested three iterations before they are used.
 //
 // Sweep 2 recomputes the logits and, knowing the statistics, forms the normalised probabilities
 // directly: p = exp2(s*scale - max - log2(sum)), no running maximum and nothing to rescale.  They feed

@@ -67,19 +67,8 @@ __device__ inline void turn_pair(unsigned w, float c, float s, unsigned& hi, uns
 }
 __device__ inline int q_swz(int D, int row) { return D == 128 ? (row & 15) : ((row >> 1) & 7); }
 
-template <int CTRL>
-__device__ inline float dpp_add(float v) {
-  const int moved = __builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false);
-  return v + __int_as_float(moved);
-}
 // Sum over the 16 lanes of a DPP row; every lane gets the total.
-__device__ inline float row16_sum(float v) {
-  v = dpp_add<0x128>(v);
-  v = dpp_add<0x124>(v);
-  v = dpp_add<0x122>(v);
-  v = dpp_add<0x121>(v);
-  return v;
-}
+__device__ inline float row16_sum(float v) { return group_sum<16>(v); }
 
 // What the two streaming kernels share: the window queries as MFMA operands, the slice of keys a
 // workgroup owns, and the loop that turns 32 keys into NB x 2 accumulators of scaled logits.

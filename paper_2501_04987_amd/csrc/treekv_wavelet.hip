@@ -24,27 +24,6 @@ constexpr int WV_LEVELS = 5;
 
 template <int N> struct IntTag { static constexpr int value = N; };
 
-template <int CTRL>
-__device__ inline float dpp_add(float v) {
-  const int moved = __builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false);
-  return v + __int_as_float(moved);
-}
-// Sum over the LPR consecutive lanes that share rows; every lane of the group gets the total.
-template <int LPR>
-__device__ inline float group_sum(float v) {
-  if constexpr (LPR == 8) {
-    v = dpp_add<0x141>(v);           // row_half_mirror: i <-> 7-i
-    v = dpp_add<0x1B>(v);            // quad_perm [3,2,1,0]
-    v = dpp_add<0xB1>(v);            // quad_perm [1,0,3,2]
-  } else {
-    v = dpp_add<0x128>(v);           // row_ror:8 (rotate inside each 16-lane row)
-    v = dpp_add<0x124>(v);           // row_ror:4
-    v = dpp_add<0x122>(v);           // row_ror:2
-    v = dpp_add<0x121>(v);           // row_ror:1
-    if constexpr (LPR == 32) v += __shfl_xor(v, 16, 64);
-  }
-  return v;
-}
 // The value of this lane and of the lane STRIDE away (index xor STRIDE), without LDS where the chip can swap lane rows.
 template <int STRIDE>
 __device__ inline float2 lane_pair(float v) {

@@ -148,7 +148,7 @@ def test_benchmark_launch_configuration_sampled(binding, oracle):
 
 def test_gqa_long_budget_split_path_sampled(binding, oracle):
     """32 query heads on 8 KV heads, head_dim 128, bf16, budget 4096, batch 16: 128 units, so the slots of a unit
-    are split over several workgroups and merged by the second kernel; scores add up the group's 4 query heads."""
+    are split over several workgroups and merged by the last of them; scores add up the group's 4 query heads."""
     B, H, Hkv, d, budget = 16, 32, 8, 128, 4096
     sched = [512] * 9 + [0] * 40
     T = 512 * 9 + 40

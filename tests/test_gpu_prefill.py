@@ -116,7 +116,7 @@ def test_prefill_argument_errors(binding):
     xf = torch.zeros(1, 512, 2, 64, dtype=torch.float32, device="cuda")
     outf, retf, nretf, evf = big.new_outputs(512)
     with pytest.raises(binding.TreeKVError) as e:
-        big.prefill_chunk(xf, xf, xf, 512, outf, retf, nretf, evf)  # fp32 storage: more columns than a thread's sums cover
+        big.prefill_chunk(xf, xf, xf, 512, outf, retf, nretf, evf)  # fp32 storage: more columns than the fp32 path takes
     assert e.value.status == binding.TREEKV_EUNSUPPORTED
 
 
@@ -146,7 +146,7 @@ def test_prefill_accumulated_weight_criterion(binding, oracle):
 
 @pytest.mark.parametrize("G,d", [(1, 64), (2, 128), (4, 64)])
 def test_prefill_fp32_storage(binding, oracle, G, d):
-    """fp32 storage: the chunk's attention runs on the vector ALUs (the matrix pipe takes bf16) and is held to 1e-5;
+    """fp32 storage: the chunk's attention runs on the fp32 matrix instructions and is held to 1e-5;
     chunks that fill, cross the budget and span sweeps, decode steps in between, ragged lengths."""
     _run(binding, oracle, [40, 17, 64, 1, 0, 100, 33, 0, 0, 128, 7], B=2, H=2 * G, Hkv=2, d=d, budget=96, n_sink=2,
          n_recent=30, max_chunk=128, seed=14, kind="iid", dtype="f32")

@@ -124,7 +124,7 @@ def test_rerank_chunks_grouped_queries(binding, oracle, G, d):
 
 @pytest.mark.parametrize("G,d", [(1, 128), (2, 64), (4, 128)])
 def test_rerank_chunks_fp32_storage(binding, oracle, G, d):
-    """fp32 storage: keys and queries turned to their ranks in fp32, the vector-ALU attention, held to 1e-5; chunks
+    """fp32 storage: keys and queries turned to their ranks in fp32, the fp32 matrix instructions, held to 1e-5; chunks
     that fill the cache, cross the budget, interleave with decode steps."""
     _chunks(binding, oracle, [30, 0, 64, 9, 0, 0, 100, 1, 47], B=2, H=2 * G, Hkv=2, d=d, budget=56, n_sink=2,
             n_recent=17, max_chunk=100, seed=66, dtype="f32", rope_base=300.0)
