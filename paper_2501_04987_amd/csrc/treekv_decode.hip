@@ -184,6 +184,41 @@ struct Stream {
     const T* Ku = (const T*)p.K + (size_t)unit * p.cap * D;
     const T* Vu = (const T*)p.V + (size_t)unit * p.cap * D;
 
+    // ROPE: what the ranks and the two small tables are made of, requested ahead of the rows.  Loads of a wave come back in
+    // the order they were asked for: behind the rows they held up the first tile until both of its tiles and then a further
+    // round trip (bookkeeping words -> order arrays) were over, with nothing else on its way from memory (256 units x 2048
+    // slots: 49.6 us a launch, 48.4 so).  The order arrays are therefore read whole and not through the words, and the
+    // tables go to LDS without a stop in registers (through registers they cost 10 of them and the split kernel its second
+    // workgroup per compute unit).
+    constexpr bool lds_tab = ROPE == ROPE_LDS;
+    constexpr int RV = D / 4;                             // 16-byte pieces of a table row
+    constexpr int E_PRE = ROPE ? 4 : 0, R_PRE = ROPE ? 2 : 0;
+    const int tab_a = (p.cap - 1) / TAB_STEP + 1;         // rows 0, 64, .. come first, rows 0 .. 63 after them
+    uint4* sm_tab = reinterpret_cast<uint4*>(sm_s - LDS_FLOATS_FIXED + tab_offset(lds_rows));
+    const int* Eu = p.E + (size_t)unit * 2 * p.m;
+    const int* Ru = p.R + (size_t)unit * max(p.n_recent, 1);
+    int ev[ROPE ? E_PRE : 1], rv[ROPE ? R_PRE : 1];
+    int words[META_STRIDE];              // the bookkeeping words: scalar loads as long as no statement before them writes memory
+    if constexpr (ROPE) {
+#pragma unroll
+      for (int x = 0; x < META_STRIDE; ++x) words[x] = meta[x];
+#pragma unroll
+      for (int x = 0; x < E_PRE; ++x) ev[x] = Eu[min(tid + x * THREADS, 2 * p.m - 1)];
+#pragma unroll
+      for (int x = 0; x < R_PRE; ++x) rv[x] = Ru[max(min(tid + x * THREADS, p.n_recent - 1), 0)];
+      if constexpr (lds_tab) {
+        // a table row is laid out so that the LPR lanes of a row read consecutive 16-byte pieces: piece x of lane l at
+        // [x][l]; 64 pieces at a time, the last 64 overlapping those before
+        const int total = tab_rows(p.cap) * RV;
+        const unsigned lds_tab_base = __builtin_amdgcn_readfirstlane(lds_address(sm_tab));
+        for (int e0 = __builtin_amdgcn_readfirstlane(wave) * 64; e0 < total; e0 += THREADS) {
+          const int s0 = min(e0, total - 64), e = s0 + lane, r = e / RV, c = e % LPR * TV + e % RV / LPR;
+          const int pos = min(r < tab_a ? r * TAB_STEP : r - tab_a, p.cap - 1);   // rows past cap - 1 are never looked up
+          async_copy16(reinterpret_cast<const uint4*>(p.rope_tab + (size_t)pos * (D / 2)) + c, lds_tab_base + s0 * 16);
+        }
+      }
+    }
+
     // first two tiles, requested before the bookkeeping words are known (rows clamped to the allocation)
     uint4 ka[KU], va[KU], kb[KU], vb[KU];
     int base = begin_spec + wave * TILE;
@@ -204,27 +239,14 @@ struct Stream {
     for (int g = 0; g < G; ++g)
       qr[g] = *reinterpret_cast<const uint4*>(q_in + ((size_t)b * p.H + (size_t)kvh * G + g) * D + li * EPL);
 
-    // ROPE: the two small tables, copied while the first rows are on their way.  A table row is laid out so that
-    // the LPR lanes of a row read consecutive 16-byte pieces: piece x of lane l at [x][l].
-    uint4* sm_tab = reinterpret_cast<uint4*>(sm_s - LDS_FLOATS_FIXED + tab_offset(lds_rows));
-    const int tab_a = (p.cap - 1) / TAB_STEP + 1;         // rows 0, 64, .. come first, rows 0 .. 63 after them
-    constexpr bool lds_tab = ROPE == ROPE_LDS;
-    if constexpr (lds_tab) {
-      constexpr int RV = D / 4;                           // 16-byte pieces of a table row
-      for (int e = tid; e < tab_rows(p.cap) * RV; e += THREADS) {
-        const int r = e / RV, c = e % RV;
-        const int pos = min(r < tab_a ? r * TAB_STEP : r - tab_a, p.cap - 1);   // rows past cap - 1 are never looked up
-        sm_tab[r * RV + (c % TV) * LPR + c / TV] = reinterpret_cast<const uint4*>(p.rope_tab + (size_t)pos * (D / 2))[c];
-      }
-    }
-
-    st = load_meta(p, meta);
+    st = load_meta(p, ROPE ? words : meta);
     begin = begin_spec;
     end = fused ? st.n1 : min(st.n1, begin + p.rows_per_split);
     const int fslot = st.fslot;
     after_meta(st);
 
-    // position re-assignment: rank of every streamed slot, then the table rows of the two tiles in flight
+    // position re-assignment: rank of every streamed slot and the two tables, then the table rows of the two tiles in
+    // flight.
     int* sm_rank = reinterpret_cast<int*>(sm_s + (size_t)G * lds_rows);
     uint4 ta[ROPE ? KU : 1][ROPE ? TV : 1], tb2[ROPE ? KU : 1][ROPE ? TV : 1];
     auto load_tab = [&](uint4 (&td)[ROPE ? KU : 1][ROPE ? TV : 1], int tb) {
@@ -254,17 +276,32 @@ struct Stream {
     };
     if constexpr (ROPE) {
       const int n = st.n1 - 1;                  // cached tokens; the new one takes rank n
+      auto put = [&](int slot, int rank) {
+        if (slot >= begin && slot < end) sm_rank[slot - begin] = rank;
+      };
       if (n < p.budget) {                       // still filling: token i sits in slot i
         for (int r = begin + tid; r < end; r += THREADS) sm_rank[r - begin] = r;
       } else {
-        const int* Eu = p.E + (size_t)unit * 2 * p.m;
-        const int* Ru = p.R + (size_t)unit * max(p.n_recent, 1);
-        for (int i = tid; i < n; i += THREADS) {
-          const int slot = logical_to_slot(p, Eu, Ru, st.rhead, st.j0, i);
-          if (slot >= begin && slot < end) sm_rank[slot - begin] = i;
-        }
-        if (tid == 0 && fslot >= begin && fslot < end) sm_rank[fslot - begin] = n;
+        // entry e of the order array is tree index e before the round's evictions j0, e - j0 behind what they consumed
+        const int j0 = st.j0;
+        auto put_tree = [&](int e, int slot) {
+          const bool before = e < j0;
+          if (before || (e >= 2 * j0 && e < p.m + j0)) put(slot, p.n_sink + (before ? e : e - j0));
+        };
+        auto put_recent = [&](int r, int slot) {
+          if (r < p.n_recent) put(slot, p.n_sink + p.m + (r >= st.rhead ? r - st.rhead : r - st.rhead + p.n_recent));
+        };
+#pragma unroll
+        for (int x = 0; x < E_PRE; ++x) put_tree(tid + x * THREADS, ev[x]);
+        for (int e = max(2 * j0, E_PRE * THREADS) + tid; e < p.m + j0; e += THREADS) put(Eu[e], p.n_sink + e - j0);
+        for (int e = E_PRE * THREADS + tid; e < j0; e += THREADS) put(Eu[e], p.n_sink + e);
+#pragma unroll
+        for (int x = 0; x < R_PRE; ++x) put_recent(tid + x * THREADS, rv[x]);
+        for (int r = tid + R_PRE * THREADS; r < p.n_recent; r += THREADS) put_recent(r, Ru[r]);
+        for (int i = tid; i < p.n_sink; i += THREADS) put(i, i);
+        if (tid == 0) put(fslot, n);
       }
+      if constexpr (lds_tab) wait_vmcnt<4 * KU>();      // the tables have landed: at least the two tiles were asked for after them
       __syncthreads();
       if (base < end) load_tab(ta, base);
       if (base + STEP < end) load_tab(tb2, base + STEP);

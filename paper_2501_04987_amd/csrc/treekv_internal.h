@@ -142,6 +142,27 @@ __device__ inline float group_sum(float v) {
   return v;
 }
 
+typedef __attribute__((address_space(3))) void lds_void_t;
+
+// s_waitcnt vmcnt(N) alone (the other counters not waited for), N < 16.  A statement the compiler moves no memory
+// access across: LDS reads that follow it read what the awaited copies wrote.
+template <int N>
+__device__ inline void wait_vmcnt() { asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory"); }
+
+// Asynchronous copy of 16 bytes per lane from global memory into LDS: lane i's bytes land at
+// lds_base + 16 * i (lds_base: wave-uniform LDS byte address, taken from M0).  Written as assembly on
+// purpose: issued through the compiler's builtin, every later LDS read is preceded by a wait for all
+// outstanding copies (it cannot tell which LDS bytes they fill), which would undo the prefetching.
+// Completion is tracked by vmcnt like any load; the callers wait explicitly (wait_vmcnt) before the
+// barrier that publishes a tile.
+__device__ inline void async_copy16(const void* src, unsigned lds_base) {
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
+               :: "v"(src), "s"(lds_base) : "memory");   // M0 is reserved: the compiler keeps nothing in it across statements
+}
+__device__ inline unsigned lds_address(const void* shared_ptr) {
+  return (unsigned)(uintptr_t)(lds_void_t*)shared_ptr;
+}
+
 // Tree-region index k (0 <= k < m) -> index into E / PE, after j_done evictions of the
 // current round (0 <= j_done <= m; a round that just ended reads the same either way).
 __device__ inline int tree_index(int k, int j_done) { return k < j_done ? k : k + j_done; }

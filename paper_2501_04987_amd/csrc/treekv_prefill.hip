@@ -71,7 +71,6 @@ constexpr int AT_THREADS = 512;   // 8 waves
 constexpr int AT_COLS = 128;      // columns per staged tile of the attend kernel
 
 typedef short short4_t __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) void lds_void_t;
 typedef __attribute__((address_space(3))) short4_t lds_short4_t;
 
 // LDS of the attend kernel: K and V tiles exactly as they lie in memory (row-major, 128 rows each),
@@ -128,21 +127,6 @@ __device__ inline float row_max(float v) {
   return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
 
-// s_waitcnt vmcnt(N) alone (the other counters not waited for), N < 16.  A statement the compiler moves no memory
-// access across: LDS reads that follow it read what the awaited copies wrote.
-template <int N>
-__device__ inline void wait_vmcnt() { asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory"); }
-
-// Asynchronous copy of 16 bytes per lane from global memory into LDS: lane i's bytes land at
-// lds_base + 16 * i (lds_base: wave-uniform LDS byte address, taken from M0).  Written as assembly on
-// purpose: issued through the compiler's builtin, every later LDS read is preceded by a wait for all
-// outstanding copies (it cannot tell which LDS bytes they fill), which would undo the prefetching.
-// Completion is tracked by vmcnt like any load; the callers wait explicitly (wait_vmcnt) before the
-// barrier that publishes a tile.
-__device__ inline void async_copy16(const void* src, unsigned lds_base) {
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
-               :: "v"(src), "s"(lds_base) : "memory");   // M0 is reserved: the compiler keeps nothing in it across statements
-}
 // The same with the source given as a wave-uniform base and a per-lane byte offset.
 __device__ inline void async_copy16_offset(const void* uniform_base, unsigned lane_offset, unsigned lds_base) {
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
@@ -165,9 +149,6 @@ __device__ inline void async_copy16_run(const void* uniform_base, unsigned lds_b
                "global_load_lds_dwordx4 %2, %4 offset:2048\n\t"
                "global_load_lds_dwordx4 %3, %4 offset:3072"
                :: "v"(off0), "v"(off1), "v"(off2), "v"(off3), "s"(uniform_base), "s"(lds_base) : "memory");
-}
-__device__ inline unsigned lds_address(const void* shared_ptr) {
-  return (unsigned)(uintptr_t)(lds_void_t*)shared_ptr;
 }
 
 // One workgroup owns 64 query rows of one head and passes over the visible columns twice, in tiles of 128.
