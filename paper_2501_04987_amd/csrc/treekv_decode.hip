@@ -947,6 +947,8 @@ __device__ inline float4 get_shared4(__amdgpu_buffer_rsrc_t r, int float_index) 
 // written the retained list except for the entry the decision fills in.  Everything is requested in one go; code that would
 // spare loads (the own slice's logits from LDS, the old scores requested mid-stream) was slower by more than it saved.
 constexpr int MAX_SPLITS = 64;
+constexpr int MERGE_BATCH = 8;
+static_assert(MAX_SPLITS % MERGE_BATCH == 0, "the slices' statistics are padded to whole batches");
 template <typename T, int D, int G>
 __device__ inline void merge_slices(const Params& p, int unit, const Step& st, const T* knew, const T* vnew, int* meta,
                                     float2* sm_ml, float* sm_sc, float* __restrict__ out, int32_t* __restrict__ retained,
@@ -995,17 +997,32 @@ __device__ inline void merge_slices(const Params& p, int unit, const Step& st, c
     knew_r = reinterpret_cast<const uint4*>(knew)[tid - (THREADS - LPR)];
     vnew_r = reinterpret_cast<const uint4*>(vnew)[tid - (THREADS - LPR)];
   }
-  if (tid < p.nsplit * G) sm_ml[tid] = ml;
+  // Slices are taken eight at a time, those past the last one empty (no weight), so that the reads of a batch are one
+  // wait: slice by slice, every one costs its latency in each of these loops
+  // (32 units x 1024 slots in 5 slices: 9.8 us a step, 9.0 so; with 4 query heads 14.7 and 12.9, with 8 18.7 and 15.4).
+  const int padded = (p.nsplit + MERGE_BATCH - 1) / MERGE_BATCH * MERGE_BATCH;
+  if (tid < padded * G) sm_ml[tid] = ml;
   __syncthreads();
   float M[G], invL[G];
 #pragma unroll
-  for (int g = 0; g < G; ++g) {
-    float mx = NEG_BIG, l = 0.f;
-    for (int s = 0; s < p.nsplit; ++s) mx = fmaxf(mx, sm_ml[s * G + g].x);
-    for (int s = 0; s < p.nsplit; ++s) l += sm_ml[s * G + g].y * fast_exp2(sm_ml[s * G + g].x - mx);
-    M[g] = mx;
-    invL[g] = 1.0f / l;
-  }
+  for (int g = 0; g < G; ++g) M[g] = NEG_BIG;
+  for (int s0 = 0; s0 < padded; s0 += MERGE_BATCH)
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+      for (int s = 0; s < MERGE_BATCH; ++s) M[g] = fmaxf(M[g], sm_ml[(s0 + s) * G + g].x);
+#pragma unroll
+  for (int g = 0; g < G; ++g) invL[g] = 0.f;
+  for (int s0 = 0; s0 < padded; s0 += MERGE_BATCH)
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+      for (int s = 0; s < MERGE_BATCH; ++s) {
+        const float2 v = sm_ml[(s0 + s) * G + g];
+        invL[g] += v.y * fast_exp2(v.x - M[g]);
+      }
+#pragma unroll
+  for (int g = 0; g < G; ++g) invL[g] = 1.0f / invL[g];
   for (int base = 0; base < st.n1; base += EPB * THREADS) {
     if (base > 0) request(base);
 #pragma unroll
@@ -1040,10 +1057,15 @@ __device__ inline void merge_slices(const Params& p, int unit, const Step& st, c
       for (int x = 1; x < G; ++x) { mx = g == x ? M[x] : mx; il = g == x ? invL[x] : il; }
       float a = 0.f;
 #pragma unroll
-      for (int s = 0; s < OPS; ++s)
-        if (s < p.nsplit) a += o_pre[y][s] * fast_exp2(sm_ml[s * G + g].x - mx);
-      for (int s = OPS; s < p.nsplit; ++s)
-        a += get_shared(parts + ((size_t)s * G + g) * (D + 2) + col) * fast_exp2(sm_ml[s * G + g].x - mx);
+      for (int s = 0; s < OPS; ++s) a += o_pre[y][s] * fast_exp2(sm_ml[s * G + g].x - mx);
+      for (int s0 = OPS; s0 < p.nsplit; s0 += OPS) {
+        float o[OPS];
+#pragma unroll
+        for (int s = 0; s < OPS; ++s)
+          o[s] = s0 + s < p.nsplit ? get_shared(parts + ((size_t)(s0 + s) * G + g) * (D + 2) + col) : 0.f;
+#pragma unroll
+        for (int s = 0; s < OPS; ++s) a += o[s] * fast_exp2(sm_ml[(s0 + s) * G + g].x - mx);
+      }
       out[((size_t)b * p.H + (size_t)kvh * G + g) * D + col] = a * il;
     }
   }
@@ -1058,9 +1080,8 @@ __device__ inline void merge_slices(const Params& p, int unit, const Step& st, c
 // the workgroup's barrier, the barrier is before the count, and the count's old value is known before the last
 // workgroup's first load; every access to the scratch and the counter is an agent-scope atomic.  All reads of state the
 // epilogue overwrites (rows, bookkeeping words, order arrays) are over when the unit's last workgroup counts itself in.
-// The merge is latency and the length of one workgroup's instruction stream.  32 units x 1024 slots: 9.6 us per step, of
-// which the merge is 2.7 (13.1 with the merge as a second kernel of one workgroup per unit); 128 units x 4096 slots x G = 4:
-// 53.0 us, merge 5 (56.3).
+// The merge is latency and the length of one workgroup's instruction stream.  32 units x 1024 slots: 9.1 us per step (13.1
+// with the merge as a second kernel of one workgroup per unit); 128 units x 4096 slots x G = 4: 53 us, merge 5 (56.3).
 //
 // MERGE = false: the merge is a kernel of its own.  The drain and the count at the end of a workgroup are time in which the
 // next one does not run, and the merge's registers leave room for fewer, so once workgroups take turns on the compute units

@@ -441,7 +441,7 @@ int treekv_init_ex(treekv_ctx** out, const treekv_config* cfg_in) {
   p.scale_log2e = c.softmax_scale * 1.4426950408889634f;
   // a unit whose logits do not fit one workgroup's LDS is split further
   for (;;) {
-    p.rows_per_split = ((p.cap + p.nsplit - 1) / p.nsplit + 63) / 64 * 64;
+    p.rows_per_split = ((p.cap + p.nsplit - 1) / p.nsplit + 15) / 16 * 16;
     if (tkv::decode_shape_fits(p) || p.nsplit >= 64) break;
     p.nsplit = p.nsplit < 2 ? 2 : p.nsplit + (p.nsplit + 1) / 2;
     if (p.nsplit > 64) p.nsplit = 64;

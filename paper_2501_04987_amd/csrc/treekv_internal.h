@@ -37,7 +37,7 @@ struct Params {
   int budget, cap, n_sink, n_recent, m;
   int B, H, Hkv, G, D, U;   // U = B * Hkv units
   int dtype, flags, nsplit, max_chunk;
-  int rows_per_split;       // decode: slots one workgroup streams (a multiple of 64)
+  int rows_per_split;       // decode: slots one workgroup streams (a multiple of 16)
   float scale_log2e;        // softmax_scale * log2(e): probabilities are exp2 of scaled logits
   void* K;                  // [U][cap][D] storage dtype
   void* V;                  // [U][cap][D]

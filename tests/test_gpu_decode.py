@@ -3,6 +3,7 @@ import numpy as np
 import pytest
 
 from paper_2501_04987_amd import inputs
+from paper_2501_04987_amd.binding import TREEKV_POSITION_RERANK
 from tests import parity_harness as ph
 
 pytestmark = pytest.mark.gpu
@@ -210,6 +211,26 @@ def test_split_merge_edges(binding, oracle, G, d, dtype, budget, splits):
     T = budget + steps
     Q, K, V = inputs.batch_streams("lowrank" if dtype == "bf16" else "iid", 41, T, 1, 2, G, d, dtype=dtype)
     kv = binding.TreeKV(budget, 2 * G, d, kv_heads=2, dtype=dtype, n_sink=3, n_recent=budget // 3, kv_splits=splits)
+    assert kv.cfg.kv_splits == splits
+    st = ph.run_schedule(oracle, kv, Q, K, V, fill + [0] * steps, dtype=dtype)
+    assert st["flagged"] <= 2
+    ph.compare_scores(kv, st["results"], dtype)
+
+
+@pytest.mark.parametrize("G,d,dtype,budget,splits,flags", [
+    (1, 128, "bf16", 300, 7, 0),     # one padded batch of slices, their length a multiple of 16 only
+    (8, 64, "bf16", 200, 8, 0),      # a whole batch; four slices' outputs requested at a time
+    (4, 128, "bf16", 257, 17, 0),    # three batches, the last of one slice and that one row
+    (2, 64, "f32", 130, 24, 0),      # empty slices inside the last batch
+    (1, 64, "bf16", 2060, 9, TREEKV_POSITION_RERANK),   # ranks beyond the entries requested up front
+])
+def test_split_merge_batches(binding, oracle, G, d, dtype, budget, splits, flags):
+    """Slices merged eight at a time, whatever number there is; the order arrays longer than a thread's first requests."""
+    fill, steps = [512] * (budget // 512) + [budget % 512], 6
+    T = budget + steps
+    Q, K, V = inputs.batch_streams("lowrank" if dtype == "bf16" else "iid", 43, T, 1, 2, G, d, dtype=dtype)
+    kv = binding.TreeKV(budget, 2 * G, d, kv_heads=2, dtype=dtype, n_sink=1, n_recent=budget // 2 + 5, kv_splits=splits,
+                        flags=flags, max_chunk=512)
     assert kv.cfg.kv_splits == splits
     st = ph.run_schedule(oracle, kv, Q, K, V, fill + [0] * steps, dtype=dtype)
     assert st["flagged"] <= 2
