@@ -378,19 +378,44 @@ int static_scratch(void** out) {
   return TREEKV_OK;
 }
 
+// Scratch of the split shape: its logits, then the slices' partial results.
+size_t split_logits_bytes(int units, int group, int cap) { return tkv::align_up((size_t)units * group * cap * sizeof(float)); }
+size_t split_scratch_bytes(int units, int group, int cap, int head_dim, int splits) {
+  return split_logits_bytes(units, group, cap) + tkv::align_up((size_t)units * splits * group * (size_t)(head_dim + 2) * sizeof(float));
+}
+
+// One 512-thread workgroup per unit (one kernel, the fused shape) or several slices of the unit's slots: as many as give
+// every one of the 256 compute units a workgroup, at 128 slots or more each.  Measured, us per step, bf16 x 128 unless noted:
+//   units x slots  G   1 slice   2      3      4      5      6      7      8     other
+//   32 x 1024      1    17.8   12.1   10.3    9.5    9.0    9.0    8.9    9.1   16: 11.5   (fp32: 5 11.6, 8 11.3)
+//   32 x 1024      4    22.0   16.9   14.6   14.0   12.9   12.2   12.0   12.0   16: 18.5   (8 heads: 5 15.4, 8 14.9)
+//   32 x 4096      4    41.3   41.4   31.9   27.6   24.5   23.3   21.9   21.8   16: 29.8
+//   64 x 4096      1    58.4   38.3   29.8   29.1   33.6   32.5   30.6   31.2
+//   128 x 1024     1    21.9   17.2   18.3   17.6
+// From 129 units two slices leave workgroups of a second round behind; three come out even again up to 170 units (two
+// workgroups per compute unit, or two full rounds), if a slice is long enough for its fixed cost: 160 x 4096 one slice 69.3,
+// two 73.5, three 63.6, G = 4 91.9, 92.1, 74.5; 160 x 1536 30.4, 32.0, 28.0, G = 4 36.5, 41.7, 36.9; 144 x 512 13.2, 14.7,
+// 12.8, G = 4 17.8, 22.7, 20.7.  From 171 units one is best nearly everywhere (192 x 1536: 32.3, 34.8, 35.9).
 int pick_splits(const treekv_config& c) {
-  // With about 200 units or more, one 512-thread workgroup per unit fills the 256 compute units and
-  // keeps the whole step in one kernel.  Below that, split every unit's slots over a few 512-thread
-  // workgroups, about 160 in all (128 units -> 2 slices, 32 units -> 5), but keep a slice at 128 slots or more.  The
-  // constants were fitted when the merge was a second kernel of 7-10 us and have not been since: at 32 units x 1024 slots
-  // 1, 2, 4, 5, 6, 8 and 12 slices take 17.6, 12.8, 10.2, 9.6, 9.2, 9.5 and 10.4 us.
-  const int units = c.batch * c.kv_heads;
-  if (units >= 192) return 1;
-  int splits = (160 + units - 1) / units;
-  const int max_by_len = (c.budget + 1 + 127) / 128;
-  if (splits > max_by_len) splits = max_by_len;
-  if (splits > 32) splits = 32;
-  if (splits < 1) splits = 1;
+  const int units = c.batch * c.kv_heads, group = c.q_heads / c.kv_heads;
+  int splits = 1;
+  if (units > 128) {
+    if (units <= 170 && c.budget >= (group == 1 ? 512 : 1536)) splits = 3;
+  } else {
+    splits = 256 / units;
+    // The merge takes slices eight at a time, so beyond eight the number goes up in eights: 8 x 1024 slots 8 slices 7.8, 9
+    // 8.1; 8 x 4096 16 slices 10.9, 20 10.9, 24 11.1, 32 11.6, G = 4 16.4, 16.8, 16.3, 17.6.  With eight query heads it
+    // takes longest, and a slice is then 256 slots: 8 x 2048 x 64 8 slices 13.4, 16 14.3.
+    int by_length = c.budget / 128 + 1;
+    if (by_length > 8) by_length = group < 8 ? by_length / 8 * 8 : c.budget / 256 < 16 ? 8 : 16;
+    if (by_length > 24) by_length = 24;
+    if (splits > by_length) splits = by_length;
+    // two short slices: 128 x 256 9.1, one 8.6; 96 x 256 8.3, 8.2
+    if (units > 64 && group == 1 && c.budget <= 256) splits = 1;
+  }
+  // The entry point with static scratch takes every context that the longer slices used before would have let it take.
+  if (splits > 1 && split_scratch_bytes(units, group, c.budget + 1, c.head_dim, splits) > (size_t)TREEKV_STATIC_SCRATCH_BYTES)
+    return units >= 160 ? 1 : (160 + units - 1) / units;
   return splits;
 }
 
@@ -506,9 +531,8 @@ int treekv_decode_step_static(treekv_ctx* ctx, const void* q, const void* k, con
   tkv::Params p = ctx->p;
   size_t lg = 0;
   if (p.nsplit > 1) {                       // the fused shape keeps its logits in LDS and needs no scratch
-    lg = tkv::align_up((size_t)p.U * p.G * p.cap * sizeof(float));
-    const size_t pt = tkv::align_up((size_t)p.U * p.nsplit * p.G * (size_t)(p.D + 2) * sizeof(float));
-    if (lg + pt > (size_t)TREEKV_STATIC_SCRATCH_BYTES) return TREEKV_ESCRATCH;
+    lg = split_logits_bytes(p.U, p.G, p.cap);
+    if (split_scratch_bytes(p.U, p.G, p.cap, p.D, p.nsplit) > (size_t)TREEKV_STATIC_SCRATCH_BYTES) return TREEKV_ESCRATCH;
   }
   fresh();
   if (p.nsplit > 1) {

@@ -111,6 +111,20 @@ def test_splits_follow_lds_capacity(binding):
     binding.load().treekv_destroy(h)
 
 
+@pytest.mark.parametrize("units,group,budget,splits", [
+    (32, 1, 1024, 8), (32, 8, 2048, 8), (2, 4, 4096, 24), (2, 8, 4096, 16), (96, 1, 256, 1), (96, 4, 256, 2), (128, 4, 4096, 2),
+    (129, 1, 512, 3), (170, 4, 1536, 3), (170, 4, 1535, 1), (171, 1, 4096, 1), (192, 1, 2048, 1), (1, 1, 64, 1),
+    (160, 1, 26000, 1),            # three slices' scratch would not fit the static array; one slice needs none
+])
+def test_splits_chosen(binding, units, group, budget, splits):
+    rc, h = _init(binding, budget=budget, q_heads=units * group, kv_heads=units)
+    assert rc == 0
+    cfg = binding.treekv_config()
+    binding.load().treekv_get_config(h, C.byref(cfg))
+    binding.load().treekv_destroy(h)
+    assert cfg.kv_splits == splits
+
+
 def test_prompt_compression_host_checks(binding):
     """treekv_prefill_prompt refuses what does not fit before anything is enqueued, and its scratch is part of the
     workspace only when max_prompt asks for it."""
