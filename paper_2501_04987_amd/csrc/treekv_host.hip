@@ -66,7 +66,6 @@ size_t carve(Params& p, char* base) {
   }
   if (p.flags & TREEKV_POSITION_RERANK) {
     p.rope_tab = (float2*)take(rope_rows(p) * (size_t)(p.D / 2) * sizeof(float2));
-    if (p.max_prompt > 0) p.pp_qrot = (uint16_t*)take(U * 2 * 128 * (size_t)p.D * 2);
     p.pf_krot = (uint16_t*)take(U * 2 * ext * p.D * 2);
     p.pf_qrot = (uint16_t*)take(2 * (size_t)p.B * p.max_chunk * p.H * p.D * 2);
   }

@@ -63,7 +63,6 @@ struct Params {
   float rope_base;
   float2* rope_tab;         // [max(cap + max_chunk, max_prompt)][D/2] (cos, sin) of n * rope_base^(-2i/D): n a distance between
                             // two cached tokens (decode), a rank (prefill chunk) or a prompt position (prompt compression)
-  uint16_t* pp_qrot;        // [U][hi, lo][128][D] bf16: the window's queries turned to their positions (max_prompt > 0)
   uint16_t* pf_krot;        // [U][hi, lo][cap + max_chunk][D] bf16: a prefill chunk's keys (cache rows by slot, then the
                             // chunk's own) turned to their ranks, split into two bf16 parts
   uint16_t* pf_qrot;        // [hi, lo][B][max_chunk][H][D] bf16: the chunk's queries, likewise

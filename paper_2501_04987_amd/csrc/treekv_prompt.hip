@@ -27,7 +27,7 @@
 // With positions re-assigned (TREEKV_POSITION_RERANK) the keys and queries come without positional encoding and
 // nothing has been evicted yet, so key j is at position j and window query i at T - W + i.  The keys are turned
 // in registers (fp32, angles from the table) right after they arrive and split into two bf16 parts, hi + lo; the
-// window's queries are turned and split once per call by a small kernel and sit in LDS; a logit is then
+// window's queries are turned and split by every workgroup for itself and sit in LDS; a logit is then
 // k_hi.q_hi + k_lo.q_hi + k_hi.q_lo (the missing lo.lo term is 2^-18 of the product).  Same four launches after that.
 
 #include "treekv_internal.h"
@@ -117,14 +117,39 @@ struct PromptStream {
           qa[nb][ks] = *reinterpret_cast<const uint4*>(Qw + (((size_t)b * W + iq) * p.H + (size_t)kvh * p.G + gq) * D + ks * 32 + q4 * 8);
       }
     }
-    if constexpr (ROPE) {
-      // the turned queries of this unit (hi rows, then lo rows) -> LDS; the caller's barrier publishes them
-      constexpr int PIECES = D / 8;
-      const uint4* src = reinterpret_cast<const uint4*>(p.pp_qrot + (size_t)unit * 2 * 128 * D);
-      for (int x = tid; x < 2 * NB * 16 * PIECES; x += PP_THREADS) {
-        const int piece = x % PIECES, row = (x / PIECES) % (NB * 16), half = x / (PIECES * NB * 16);
-        *reinterpret_cast<uint4*>(sm_q + ((size_t)(half * NB * 16 + row) * D + ((piece ^ q_swz(D, row)) * 8))) =
-            src[((size_t)half * 128 + row) * PIECES + piece];
+  }
+  // ROPE: the unit's queries, turned to their positions (window query i at T - W + i) and split into hi rows, then lo rows,
+  // -> LDS, rows past W * G zero.  Every workgroup turns them for itself, 4 planes x 4 per thread with eight operand
+  // blocks: as a kernel of its own, once per unit, they cost a call 5 us.  Requested before the first keys and turned
+  // after those are requested; the caller's barrier publishes them.
+  static constexpr int PIECES = D / 8, QY = (NB * 16 * PIECES + PP_THREADS - 1) / PP_THREADS;
+  struct QRaw { uint4 w[QY]; float4 t[QY][2]; };
+  __device__ inline void request_queries(QRaw& q, const Params& p, const uint16_t* Qw, int W, int unit) const {
+    const int kvh = unit % p.Hkv, b = unit / p.Hkv;
+#pragma unroll
+    for (int y = 0; y < QY; ++y) {
+      const int x = threadIdx.x + y * PP_THREADS, piece = x % PIECES, row = min(x / PIECES, W * p.G - 1);
+      const int i = row / p.G, g = row % p.G;
+      q.w[y] = reinterpret_cast<const uint4*>(Qw + (((size_t)b * W + i) * p.H + (size_t)kvh * p.G + g) * D)[piece];
+      const float4* cs = reinterpret_cast<const float4*>(tab + (size_t)(T - W + i) * (D / 2) + piece * 4);
+      q.t[y][0] = cs[0];
+      q.t[y][1] = cs[1];
+    }
+  }
+  __device__ inline void turn_queries(const QRaw& q, uint16_t* sm_q, int live_rows) const {
+#pragma unroll
+    for (int y = 0; y < QY; ++y) {
+      const int x = threadIdx.x + y * PP_THREADS, piece = x % PIECES, row = x / PIECES;
+      uint4 hi, lo;
+      turn_pair(q.w[y].x, q.t[y][0].x, q.t[y][0].y, hi.x, lo.x);
+      turn_pair(q.w[y].y, q.t[y][0].z, q.t[y][0].w, hi.y, lo.y);
+      turn_pair(q.w[y].z, q.t[y][1].x, q.t[y][1].y, hi.z, lo.z);
+      turn_pair(q.w[y].w, q.t[y][1].z, q.t[y][1].w, hi.w, lo.w);
+      if (row >= live_rows) hi = lo = make_uint4(0, 0, 0, 0);
+      if (x < NB * 16 * PIECES) {                 // (two operand blocks at head_dim 64: fewer pieces than threads)
+        uint4* dst = reinterpret_cast<uint4*>(sm_q) + (size_t)row * PIECES + (piece ^ q_swz(D, row));
+        dst[0] = hi;
+        dst[NB * 16 * PIECES] = lo;
       }
     }
   }
@@ -182,26 +207,6 @@ struct PromptStream {
   }
 };
 
-// The window's queries turned to their positions (query i of the window at T - W + i) and split into bf16 hi and
-// lo parts: pp_qrot [unit][hi, lo][128 rows][D], row i * G + g, rows past W * G zero.
-template <int D>
-__global__ void prompt_turn_queries_kernel(Params p, const uint16_t* __restrict__ Qw, int T, int W) {
-  const int unit = blockIdx.y, kvh = unit % p.Hkv, b = unit / p.Hkv;
-  unsigned* dst = reinterpret_cast<unsigned*>(p.pp_qrot + (size_t)unit * 2 * 128 * D);
-  for (int x = blockIdx.x * blockDim.x + threadIdx.x; x < 128 * (D / 2); x += gridDim.x * blockDim.x) {
-    const int pair = x % (D / 2), row = x / (D / 2);
-    unsigned hi = 0, lo = 0;
-    if (row < W * p.G) {
-      const int i = row / p.G, g = row % p.G;
-      const unsigned w = reinterpret_cast<const unsigned*>(Qw + (((size_t)b * W + i) * p.H + (size_t)kvh * p.G + g) * D)[pair];
-      const float2 cs = p.rope_tab[(size_t)(T - W + i) * (D / 2) + pair];
-      turn_pair(w, cs.x, cs.y, hi, lo);
-    }
-    dst[(size_t)row * (D / 2) + pair] = hi;
-    dst[(size_t)(128 + row) * (D / 2) + pair] = lo;
-  }
-}
-
 // ---------------------------------------------------------------------------------------------
 // stats: per (unit, slice, query row) the maximum and the sum of exp2(logit - maximum) over the slice
 // ---------------------------------------------------------------------------------------------
@@ -230,9 +235,14 @@ __global__ __launch_bounds__(PP_THREADS) void prompt_stats_kernel(Params p, cons
   constexpr int AHEAD = (NB < 8 && !ROPE) ? 2 : 1;
   KB k0, k1, k2, k3;
   int base = st.begin + st.wave * PP_TILE;
+  typename PS::QRaw qraw;
+  if constexpr (ROPE) st.request_queries(qraw, p, Qw, W, unit);
   st.load_block(k0, base); st.load_block(k1, base + 16);
   if (AHEAD == 2) { st.load_block(k2, base + PP_STEP); st.load_block(k3, base + PP_STEP + 16); }
-  if constexpr (ROPE) __syncthreads();               // the queries are in LDS
+  if constexpr (ROPE) {
+    st.turn_queries(qraw, stats_q, W * p.G);
+    __syncthreads();                                 // the queries are in LDS
+  }
   // One operand block of 16 keys at a time: its accumulators are consumed before the next block's exist.
   // `ragged` (a type, so that the common case carries no masking code): some query does not see some key.
   auto block = [&](auto ragged, KB& k, int tile, int h) {
@@ -320,7 +330,10 @@ __global__ __launch_bounds__(PP_THREADS) void prompt_scores_kernel(Params p, con
   KB k0, k1;
   const int first = st.begin + st.wave * PP_TILE;
   int base = first < st.end ? first + (st.end - 1 - first) / PP_STEP * PP_STEP : first - PP_STEP;
+  typename PS::QRaw qraw;
+  if constexpr (ROPE) st.request_queries(qraw, p, Qw, W, unit);
   st.load_block(k0, base); st.load_block(k1, base + 16);
+  if constexpr (ROPE) st.turn_queries(qraw, scores_q, W * p.G);
 
   if (tid < NB * 16) {                 // the slices' (max, sum) of this query row -> the row's max and 1 / sum
     const float* src = p.pp_stat + ((size_t)unit * nsplit * 128 + tid) * 2;
@@ -644,7 +657,6 @@ int launch_streams(const Params& p, const uint16_t* Qw, const uint16_t* K, int T
   if (lds > 48 * 1024 && hip_failed(hipFuncSetAttribute((const void*)prompt_scores_kernel<D, NB, ROPE>,
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)))
     return TREEKV_EHIP;
-  if constexpr (ROPE) hipLaunchKernelGGL((prompt_turn_queries_kernel<D>), dim3(128 * (D / 2) / 256, p.U), dim3(256), 0, s, p, Qw, T, W);
   hipLaunchKernelGGL((prompt_stats_kernel<D, NB, ROPE>), dim3(nsplit, p.U), dim3(PP_THREADS), q_lds, s, p, Qw, K, T, W,
                      rows_per_split, nsplit);
   hipLaunchKernelGGL((prompt_scores_kernel<D, NB, ROPE>), dim3(nsplit, p.U), dim3(PP_THREADS), lds, s, p, Qw, K, T, W,
