@@ -102,7 +102,18 @@ class TreeKVError(RuntimeError):
 
 
 def _ptr(t):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()       # the argument types make a pointer of it
+
+
+def _raw_stream(device) -> int:
+    """The current stream of `device` as an address.  Without the torch.cuda.Stream object around it, and with plain numbers
+    for pointers, a step of the smallest decode configuration, which is the host's time, takes 5.3 us instead of 8.1."""
+    import torch
+
+    if device.type != "cuda":
+        return torch.cuda.current_stream(device).cuda_stream       # raises
+    index = device.index if device.index is not None else torch.cuda.current_device()
+    return torch._C._cuda_getCurrentRawStream(index)
 
 
 def wavelet_components(a, V, levels: int, per_head=None, mean=None):
@@ -119,7 +130,7 @@ def wavelet_components(a, V, levels: int, per_head=None, mean=None):
         mean = torch.empty(levels, t, dtype=torch.float32, device=V.device)
     assert a.dtype == torch.float32 and a.shape == (heads, t) and a.is_contiguous() and V.is_contiguous()
     rc = lib.treekv_wavelet_components(_ptr(a), _ptr(V), dtype, heads, t, d, int(levels), _ptr(per_head), _ptr(mean),
-                                       C.c_void_p(torch.cuda.current_stream(V.device).cuda_stream))
+                                       _raw_stream(V.device))
     if rc != TREEKV_OK:
         raise TreeKVError(rc, "treekv_wavelet_components")
     return per_head, mean
@@ -168,7 +179,7 @@ class TreeKV:
             raise TreeKVError(rc, what, self._lib.treekv_last_hip_error(self._h).decode() if self._h else "")
 
     def _stream(self):
-        return C.c_void_p(self._torch.cuda.current_stream(self.device).cuda_stream)
+        return _raw_stream(self.device)
 
     def close(self):
         if getattr(self, "_h", None):
