@@ -946,9 +946,8 @@ __device__ inline float4 get_shared4(__amdgpu_buffer_rsrc_t r, int float_index) 
 // A unit's slices merged by one workgroup, then the step's epilogue: every load, then the arithmetic.  The caller has
 // written the retained list except for the entry the decision fills in.  Everything is requested in one go; code that would
 // spare loads (the own slice's logits from LDS, the old scores requested mid-stream) was slower by more than it saved.
-constexpr int MAX_SPLITS = 64;
 constexpr int MERGE_BATCH = 8;
-static_assert(MAX_SPLITS % MERGE_BATCH == 0, "the slices' statistics are padded to whole batches");
+static_assert(DECODE_MAX_SPLITS % MERGE_BATCH == 0, "the slices' statistics are padded to whole batches");
 template <typename T, int D, int G>
 __device__ inline void merge_slices(const Params& p, int unit, const Step& st, const T* knew, const T* vnew, int* meta,
                                     float2* sm_ml, float* sm_sc, float* __restrict__ out, int32_t* __restrict__ retained,
@@ -1113,7 +1112,7 @@ __global__ __launch_bounds__(SPLIT_THREADS) void decode_split_kernel(Params p, c
   float* sm_wm = sm_acc + WAVES * G * D;
   float* sm_wl = sm_wm + WAVES * G;
   float* sm_s = smem + St::LDS_FLOATS_FIXED;   // [G][rows_per_split]
-  __shared__ float2 sm_ml[MERGE ? MAX_SPLITS * G : 1];
+  __shared__ float2 sm_ml[MERGE ? DECODE_MAX_SPLITS * G : 1];
   __shared__ float sm_sc[2];
   __shared__ int sm_last;
 
@@ -1194,7 +1193,7 @@ __global__ __launch_bounds__(SPLIT_THREADS) void decode_merge_kernel(Params p, c
                                                                      int32_t* __restrict__ retained,
                                                                      int32_t* __restrict__ n_retained,
                                                                      int32_t* __restrict__ evicted) {
-  __shared__ float2 sm_ml[MAX_SPLITS * G];
+  __shared__ float2 sm_ml[DECODE_MAX_SPLITS * G];
   __shared__ float sm_sc[2];
   const int unit = blockIdx.x, tid = threadIdx.x;
   int* meta = p.meta + (size_t)unit * META_STRIDE;
@@ -1292,7 +1291,7 @@ bool decode_shape_fits(const Params& p) {
   size_t b = 0;
   if (p.dtype == TREEKV_BF16) b = p.D == 128 ? stream_lds_d<uint16_t, 128>(p) : p.D == 64 ? stream_lds_d<uint16_t, 64>(p) : 0;
   else if (p.dtype == TREEKV_F32) b = p.D == 128 ? stream_lds_d<float, 128>(p) : p.D == 64 ? stream_lds_d<float, 64>(p) : 0;
-  return b != 0 && b <= LDS_LIMIT;
+  return b != 0 && b <= LDS_LIMIT && p.nsplit <= DECODE_MAX_SPLITS;
 }
 
 int launch_decode(const Params& p, const void* q, const void* k, const void* v, float* out, int32_t* retained,

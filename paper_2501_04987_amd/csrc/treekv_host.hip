@@ -412,10 +412,33 @@ int pick_splits(const treekv_config& c) {
     // two short slices: 128 x 256 9.1, one 8.6; 96 x 256 8.3, 8.2
     if (units > 64 && group == 1 && c.budget <= 256) splits = 1;
   }
-  // The entry point with static scratch takes every context that the longer slices used before would have let it take.
-  if (splits > 1 && split_scratch_bytes(units, group, c.budget + 1, c.head_dim, splits) > (size_t)TREEKV_STATIC_SCRATCH_BYTES)
-    return units >= 160 ? 1 : (160 + units - 1) / units;
   return splits;
+}
+
+// About 160 workgroups in all, at most 32 slices and at most one per 128 slots or part of them: the number for contexts whose scratch would not fit
+// the static array with pick_splits' one.
+int pick_few_splits(const treekv_config& c) {
+  const int units = c.batch * c.kv_heads, by_length = (c.budget + 1 + 127) / 128;
+  int splits = units >= 192 ? 1 : (160 + units - 1) / units;
+  if (splits > by_length) splits = by_length;
+  return splits > 32 ? 32 : splits;
+}
+
+// Sets the shape of the decode kernels: `splits` slices, more if a slice's logits do not fit one workgroup's LDS; false if
+// they never do.  Whether they fit is asked of slices rounded up to 64 slots, though 16 is what the kernels need, so that the
+// contexts the library accepts and the numbers it settles on stay those it had with the longer slices.
+bool set_splits(tkv::Params& p, int splits) {
+  bool fits;
+  for (;;) {
+    p.nsplit = splits;
+    p.rows_per_split = ((p.cap + splits - 1) / splits + 63) / 64 * 64;
+    fits = tkv::decode_shape_fits(p);
+    if (fits || splits >= tkv::DECODE_MAX_SPLITS) break;
+    splits = splits < 2 ? 2 : splits + (splits + 1) / 2;
+    if (splits > tkv::DECODE_MAX_SPLITS) splits = tkv::DECODE_MAX_SPLITS;
+  }
+  p.rows_per_split = ((p.cap + p.nsplit - 1) / p.nsplit + 15) / 16 * 16;
+  return fits;
 }
 
 }  // namespace
@@ -438,7 +461,7 @@ int treekv_init_ex(treekv_ctx** out, const treekv_config* cfg_in) {
   if (c.flags & ~(TREEKV_KEEP_LEFT | TREEKV_SCORE_ACCUMULATED | TREEKV_POSITION_RERANK)) return TREEKV_EINVAL;
   if (!(c.rope_base >= 0.0f) || isinf(c.rope_base)) return TREEKV_EINVAL;
   if (c.rope_base == 0.0f) c.rope_base = 10000.0f;
-  if (c.max_chunk < 0 || c.kv_splits < 0 || c.kv_splits > 64) return TREEKV_EINVAL;
+  if (c.max_chunk < 0 || c.kv_splits < 0 || c.kv_splits > tkv::DECODE_MAX_SPLITS) return TREEKV_EINVAL;
   if (!(c.softmax_scale >= 0.0f) || isinf(c.softmax_scale)) return TREEKV_EINVAL;
   if (c.head_dim != 64 && c.head_dim != 128) return TREEKV_EUNSUPPORTED;
   const int G = c.q_heads / c.kv_heads;
@@ -449,7 +472,6 @@ int treekv_init_ex(treekv_ctx** out, const treekv_config* cfg_in) {
   if (c.max_prompt < 0) return TREEKV_EINVAL;
   if (c.max_prompt > (1 << 24)) return TREEKV_EUNSUPPORTED;
   if (c.softmax_scale == 0.0f) c.softmax_scale = 1.0f / sqrtf((float)c.head_dim);
-  if (c.kv_splits == 0) c.kv_splits = pick_splits(c);
 
   treekv_ctx* ctx = new (std::nothrow) treekv_ctx;
   if (!ctx) return TREEKV_EINVAL;
@@ -459,18 +481,16 @@ int treekv_init_ex(treekv_ctx** out, const treekv_config* cfg_in) {
   p.budget = c.budget; p.cap = c.budget + 1; p.n_sink = c.n_sink; p.n_recent = c.n_recent;
   p.m = c.budget - c.n_sink - c.n_recent;
   p.B = c.batch; p.H = c.q_heads; p.Hkv = c.kv_heads; p.G = G; p.D = c.head_dim; p.U = c.batch * c.kv_heads;
-  p.dtype = c.dtype; p.flags = c.flags; p.nsplit = c.kv_splits; p.max_chunk = c.max_chunk;
+  p.dtype = c.dtype; p.flags = c.flags; p.max_chunk = c.max_chunk;
   p.max_prompt = c.max_prompt;
   p.rope_base = c.rope_base;
   p.scale_log2e = c.softmax_scale * 1.4426950408889634f;
-  // a unit whose logits do not fit one workgroup's LDS is split further
-  for (;;) {
-    p.rows_per_split = ((p.cap + p.nsplit - 1) / p.nsplit + 15) / 16 * 16;
-    if (tkv::decode_shape_fits(p) || p.nsplit >= 64) break;
-    p.nsplit = p.nsplit < 2 ? 2 : p.nsplit + (p.nsplit + 1) / 2;
-    if (p.nsplit > 64) p.nsplit = 64;
-  }
-  if (!tkv::decode_shape_fits(p)) { delete ctx; return TREEKV_EUNSUPPORTED; }
+  bool fits = set_splits(p, c.kv_splits > 0 ? c.kv_splits : pick_splits(c));
+  // the entry point with static scratch takes every context that the smaller number would let it take
+  if (c.kv_splits == 0 && p.nsplit > 1 &&
+      split_scratch_bytes(p.U, p.G, p.cap, p.D, p.nsplit) > (size_t)TREEKV_STATIC_SCRATCH_BYTES)
+    fits = set_splits(p, pick_few_splits(c));
+  if (!fits) { delete ctx; return TREEKV_EUNSUPPORTED; }
   ctx->cfg.kv_splits = p.nsplit;
   ctx->ws_bytes = tkv::carve(p, nullptr);
   *out = ctx;

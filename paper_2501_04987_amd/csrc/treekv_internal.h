@@ -68,6 +68,7 @@ struct Params {
   uint16_t* pf_qrot;        // [hi, lo][B][max_chunk][H][D] bf16: the chunk's queries, likewise
 };
 constexpr int PROMPT_MAX_SPLITS = 64;
+constexpr int DECODE_MAX_SPLITS = 64;    // slices of a unit the decode step's merge is laid out for
 
 // HIP errors.  A launch_* function ends with finish_launch(), which takes HIP's last error (and so clears
 // it); hip_failed(e) is true for e != hipSuccess.  Either way the error is remembered, per host thread,

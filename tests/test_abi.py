@@ -125,6 +125,43 @@ def test_splits_chosen(binding, units, group, budget, splits):
     assert cfg.kv_splits == splits
 
 
+def _splits(binding, units, group, head_dim, f32, flags, budget):
+    rc, h = _init(binding, budget=budget, q_heads=units * group, kv_heads=units, head_dim=head_dim,
+                  dtype=binding.TREEKV_F32 if f32 else binding.TREEKV_BF16, flags=flags, n_sink=4,
+                  n_recent=budget - budget // 2 - 4)
+    if rc != 0:
+        return rc
+    cfg = binding.treekv_config()
+    binding.load().treekv_get_config(h, C.byref(cfg))
+    binding.load().treekv_destroy(h)
+    return cfg.kv_splits
+
+
+@pytest.mark.parametrize("units,group,head_dim,f32,rerank,budget,splits", [
+    (2, 8, 64, True, False, 262144, 64), (2, 8, 64, True, False, 270000, 64), (2, 4, 64, True, False, 524288, 64),
+    (2, 1, 128, False, False, 2100000, 64), (3, 1, 128, False, False, 1500000, 48), (4, 1, 64, False, False, 1200000, 32),
+    (8, 1, 128, False, False, 524288, 20), (32, 2, 64, False, False, 65536, 5), (144, 1, 128, False, False, 30000, 2),
+    (1, 8, 64, True, False, 524288, None), (1, 1, 128, False, False, 4500000, None), (2, 8, 64, False, True, 262144, None),
+    (1, 1, 64, False, False, 1 << 24, None),
+])
+def test_splits_of_contexts_beyond_the_static_scratch(binding, units, group, head_dim, f32, rerank, budget, splits):
+    """Few slices where more of them would not fit the static scratch; None: logits that do not fit LDS in 64 slices, which
+    is what the merge takes, are refused."""
+    flags = binding.TREEKV_POSITION_RERANK if rerank else 0
+    assert _splits(binding, units, group, head_dim, f32, flags, budget) == (splits or binding.TREEKV_EUNSUPPORTED)
+
+
+def test_splits_never_exceed_what_the_merge_takes(binding):
+    assert binding.TREEKV_EUNSUPPORTED < 0
+    for units in (1, 2, 3, 4, 7, 16, 130):
+        for group in (1, 2, 4, 8):
+            for head_dim, f32, flags in ((64, True, 0), (128, False, 0), (64, False, binding.TREEKV_POSITION_RERANK)):
+                for e in range(4, 25):
+                    for budget in (1 << e, (1 << e) + (1 << e - 1) + 3):
+                        n = _splits(binding, units, group, head_dim, f32, flags, budget)
+                        assert n == binding.TREEKV_EUNSUPPORTED or 1 <= n <= 64, (units, group, head_dim, f32, flags, budget, n)
+
+
 def test_prompt_compression_host_checks(binding):
     """treekv_prefill_prompt refuses what does not fit before anything is enqueued, and its scratch is part of the
     workspace only when max_prompt asks for it."""
