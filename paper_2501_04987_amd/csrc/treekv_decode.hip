@@ -190,6 +190,10 @@ struct Stream {
     // slots: 49.6 us a launch, 48.4 so).  The order arrays are therefore read whole and not through the words, and the
     // tables go to LDS without a stop in registers (through registers they cost 10 of them and the split kernel its second
     // workgroup per compute unit).
+    // The instance with 8 query heads spills; through a copy of their own for these addresses the lane's place in a row
+    // stays in registers in the loop (160 units x 1024 slots 65.2 us, 69.1 with one variable; 64 x 2048 67.9 and 71.8).
+    int ptid = tid;
+    if constexpr (ROPE && G == 8) asm volatile("" : "+v"(ptid));
     constexpr bool lds_tab = ROPE == ROPE_LDS;
     constexpr int RV = D / 4;                             // 16-byte pieces of a table row
     constexpr int E_PRE = ROPE ? 4 : 0, R_PRE = ROPE ? 2 : 0;
@@ -203,16 +207,16 @@ struct Stream {
 #pragma unroll
       for (int x = 0; x < META_STRIDE; ++x) words[x] = meta[x];
 #pragma unroll
-      for (int x = 0; x < E_PRE; ++x) ev[x] = Eu[min(tid + x * THREADS, 2 * p.m - 1)];
+      for (int x = 0; x < E_PRE; ++x) ev[x] = Eu[min(ptid + x * THREADS, 2 * p.m - 1)];
 #pragma unroll
-      for (int x = 0; x < R_PRE; ++x) rv[x] = Ru[max(min(tid + x * THREADS, p.n_recent - 1), 0)];
+      for (int x = 0; x < R_PRE; ++x) rv[x] = Ru[max(min(ptid + x * THREADS, p.n_recent - 1), 0)];
       if constexpr (lds_tab) {
         // a table row is laid out so that the LPR lanes of a row read consecutive 16-byte pieces: piece x of lane l at
         // [x][l]; 64 pieces at a time, the last 64 overlapping those before
         const int total = tab_rows(p.cap) * RV;
         const unsigned lds_tab_base = __builtin_amdgcn_readfirstlane(lds_address(sm_tab));
         for (int e0 = __builtin_amdgcn_readfirstlane(wave) * 64; e0 < total; e0 += THREADS) {
-          const int s0 = min(e0, total - 64), e = s0 + lane, r = e / RV, c = e % LPR * TV + e % RV / LPR;
+          const int s0 = min(e0, total - 64), e = s0 + (ptid & 63), r = e / RV, c = e % LPR * TV + e % RV / LPR;
           const int pos = min(r < tab_a ? r * TAB_STEP : r - tab_a, p.cap - 1);   // rows past cap - 1 are never looked up
           async_copy16(reinterpret_cast<const uint4*>(p.rope_tab + (size_t)pos * (D / 2)) + c, lds_tab_base + s0 * 16);
         }
