@@ -383,62 +383,95 @@ size_t split_scratch_bytes(int units, int group, int cap, int head_dim, int spli
   return split_logits_bytes(units, group, cap) + tkv::align_up((size_t)units * splits * group * (size_t)(head_dim + 2) * sizeof(float));
 }
 
+// Whether the decode kernels' LDS holds a slice of `splits`.  Asked of slices rounded up to 64 slots, though 16 is what the
+// kernels need, so that the contexts the library accepts and the numbers it settles on stay those it had with the longer slices.
+bool slices_fit(tkv::Params p, int splits) {
+  p.nsplit = splits;
+  p.rows_per_split = ((p.cap + splits - 1) / splits + 63) / 64 * 64;
+  return tkv::decode_shape_fits(p);
+}
+
 // One 512-thread workgroup per unit (one kernel, the fused shape) or several slices of the unit's slots: as many as give
-// every one of the 256 compute units a workgroup, at 128 slots or more each.  Measured, us per step, bf16 x 128 unless noted:
+// every one of the 256 compute units a workgroup, at about 128 slots or more each.  Measured, us per step, bf16 x 128 unless noted:
 //   units x slots  G   1 slice   2      3      4      5      6      7      8     other
 //   32 x 1024      1    17.8   12.1   10.3    9.5    9.0    9.0    8.9    9.1   16: 11.5   (fp32: 5 11.6, 8 11.3)
 //   32 x 1024      4    22.0   16.9   14.6   14.0   12.9   12.2   12.0   12.0   16: 18.5   (8 heads: 5 15.4, 8 14.9)
 //   32 x 4096      4    41.3   41.4   31.9   27.6   24.5   23.3   21.9   21.8   16: 29.8
 //   64 x 4096      1    58.4   38.3   29.8   29.1   33.6   32.5   30.6   31.2
 //   128 x 1024     1    21.9   17.2   18.3   17.6
+// A row of 128 bytes (bf16, head_dim 64) streams in half the time, so that one query head's slices are about 208 slots:
+//   16 x 2048, 64  1    18.2   12.5   10.5    9.6    9.1    8.9    8.6    8.5   10: 9.0, 16: 9.6
+//   32 x 1024, 64  1    11.4    9.3    8.6    8.1    8.2    8.2    8.4    8.8
+//   48 x 640, 64   1     9.1    8.3    8.0    7.9    8.2
+//   64 x 400, 64   1     7.6    7.7    7.7    8.0
+// The same with up to 16 units, which leave compute units idle anyway, from eight slices on only: 1 x 1024, 64 4 slices 7.1, 8
+// 6.9; 1 x 2048, 64 8 slices 7.6, 16 8.0.  With positions re-assigned 128 slots stay: 32 x 256, 64 one slice 8.8, three 8.3.
+//
 // From 129 units two slices leave workgroups of a second round behind; three come out even again up to 170 units (two
-// workgroups per compute unit, or two full rounds), if a slice is long enough for its fixed cost: 160 x 4096 one slice 69.3,
-// two 73.5, three 63.6, G = 4 91.9, 92.1, 74.5; 160 x 1536 30.4, 32.0, 28.0, G = 4 36.5, 41.7, 36.9; 144 x 512 13.2, 14.7,
-// 12.8, G = 4 17.8, 22.7, 20.7.  From 171 units one is best nearly everywhere (192 x 1536: 32.3, 34.8, 35.9).
-int pick_splits(const treekv_config& c) {
-  const int units = c.batch * c.kv_heads, group = c.q_heads / c.kv_heads;
-  int splits = 1;
-  if (units > 128) {
-    if (units <= 170 && c.budget >= (group == 1 ? 512 : 1536)) splits = 3;
-  } else {
-    splits = 256 / units;
-    // The merge takes slices eight at a time, so beyond eight the number goes up in eights: 8 x 1024 slots 8 slices 7.8, 9
-    // 8.1; 8 x 4096 16 slices 10.9, 20 10.9, 24 11.1, 32 11.6, G = 4 16.4, 16.8, 16.3, 17.6.  With eight query heads it
-    // takes longest, and a slice is then 256 slots: 8 x 2048 x 64 8 slices 13.4, 16 14.3.
-    int by_length = c.budget / 128 + 1;
-    if (by_length > 8) by_length = group < 8 ? by_length / 8 * 8 : c.budget / 256 < 16 ? 8 : 16;
-    if (by_length > 24) by_length = 24;
-    if (splits > by_length) splits = by_length;
-    // two short slices: 128 x 256 9.1, one 8.6; 96 x 256 8.3, 8.2
-    if (units > 64 && group == 1 && c.budget <= 256) splits = 1;
+// workgroups per compute unit, or two full rounds) if a slice is long enough for its fixed cost, which THREE_FROM says, and
+// are better than two where one does not fit LDS (160 x 1300, G = 8: two slices 41.8, three 36.1).  One slice against three:
+//   bf16 x 128, G = 1  160 x 512 13.2 / 13.3, 144 x 512 13.3 / 12.6, 160 x 1536 30.4 / 28.0;  G = 2  160 x 1300 32.3 / 31.7, x 1536
+//               36.2 / 34.6;  G = 4  160 x 1536 34.7 / 36.6, x 2048 46.9 / 44.6;  G = 8  160 x 1024 26.8 / 31.1
+//   bf16 x 64   G = 1  152 x 1024 12.7 / 13.3, x 1300 15.9 / 15.0, 160 x 1792 18.9 / 19.3, x 2048 21.4 / 21.0;  G = 2  160 x 1300
+//               17.3 / 17.6, x 1536 20.1 / 19.3;  G = 4  160 x 1536 20.4 / 20.6, x 2048 25.2 / 25.1;  G = 8  160 x 2048 26.7 / 29.3
+//   bf16 x 128, re-assigned  G = 1  160 x 512 15.6 / 15.1;  G = 2  160 x 1024 27.5 / 29.0, x 1536 38.5 / 37.1;  G = 4  160 x 1300
+//               42.8 / 43.0, x 1536 49.6 / 48.2;  G = 8  160 x 512 43.5 / 45.2, x 800 58.0 / 55.4
+//   bf16 x 64, re-assigned   G = 1  160 x 512 11.5 / 12.6, x 1024 15.7 / 15.6;  G = 2  160 x 2048 27.8 / 30.4;  G = 4  160 x 3000
+//               48.2 / 49.6;  G = 8  160 x 1536 58.1 / 57.9, x 2048 71.7 / 68.3
+//   fp32 x 128  G = 1  160 x 256 12.4 / 13.1, x 512 20.8 / 19.9;  G = 4  160 x 256 18.5 / 18.8, x 512 30.4 / 25.7
+//   fp32 x 64   G = 1  132 x 512 12.9 / 11.8, 160 x 512 12.4 / 12.7, x 1024 20.7 / 19.9;  G = 4  160 x 800 22.3 / 22.4, x 1024 27.4 / 26.0
+// From 171 units the rule takes one.
+constexpr int NEVER = 1 << 30;
+constexpr int THREE_FROM[6][4] = {      // budgets; query heads per KV head: 1, 2, 4, 8
+    {512, 1536, 2048, NEVER},           // bf16 x 128
+    {1280, 1536, 2048, NEVER},          // bf16 x 64
+    {512, 1536, 1536, 768},             // bf16 x 128, positions re-assigned
+    {1024, 3072, 4096, 2048},           // bf16 x 64, positions re-assigned
+    {512, 512, 512, 512},               // fp32 x 128
+    {512, 1024, 1024, 1024},            // fp32 x 64
+};
+int pick_splits(const tkv::Params& p) {
+  const bool bf16 = p.dtype == TREEKV_BF16, rerank = (p.flags & TREEKV_POSITION_RERANK) != 0;
+  const int row_bytes = p.D * (bf16 ? 2 : 4);
+  if (p.U > 170) return 1;
+  if (p.U > 128) {
+    int from = THREE_FROM[(bf16 ? (rerank ? 2 : 0) : 4) + (p.D == 64)][p.G == 1 ? 0 : p.G == 2 ? 1 : p.G == 4 ? 2 : 3];
+    if (p.G == 1 && p.U > 152 && row_bytes < 512 && !rerank) from += from / 2;
+    return p.budget >= from || !slices_fit(p, 1) ? 3 : 1;
   }
-  return splits;
+  const bool thin = p.G == 1 && row_bytes == 128 && !rerank;
+  int by_length = p.budget / 128 + 1;
+  if (thin && p.U > 16) by_length = p.budget < 320 ? 1 : p.budget < 624 ? 2 : p.budget / 208;
+  else if (thin && by_length > 8) by_length = p.budget < 8 * 208 ? 8 : p.budget / 208;
+  // The merge takes slices eight at a time, so beyond eight the number goes up in eights: 8 x 1024 slots 8 slices 7.8, 9
+  // 8.1; 8 x 4096 16 slices 10.9, 20 10.9, 24 11.1, 32 11.6, G = 4 16.4, 16.8, 16.3, 17.6.  With eight query heads it
+  // takes longest, and a slice is then 256 slots: 8 x 2048 x 64 8 slices 13.4, 16 14.3.
+  if (by_length > 8) by_length = p.G < 8 ? by_length / 8 * 8 : p.budget / 256 < 16 ? 8 : 16;
+  if (by_length > 24) by_length = 24;
+  // two short slices: 128 x 256 9.0, one 8.7 (rows of 512 bytes 11.4, 12.9; positions re-assigned 10.8, 11.4)
+  if (p.U > 64 && p.G == 1 && p.budget <= 256 && !rerank && row_bytes <= 256) return 1;
+  return by_length < 256 / p.U ? by_length : 256 / p.U;
 }
 
-// About 160 workgroups in all, at most 32 slices and at most one per 128 slots or part of them: the number for contexts whose scratch would not fit
-// the static array with pick_splits' one.
-int pick_few_splits(const treekv_config& c) {
-  const int units = c.batch * c.kv_heads, by_length = (c.budget + 1 + 127) / 128;
-  int splits = units >= 192 ? 1 : (160 + units - 1) / units;
+// About 160 workgroups in all, at most 32 slices and at most one per 128 slots or part of them: the number for contexts whose
+// scratch would not fit the static array with pick_splits' one.
+int pick_few_splits(const tkv::Params& p) {
+  const int by_length = (p.cap + 127) / 128;
+  int splits = p.U >= 192 ? 1 : (160 + p.U - 1) / p.U;
   if (splits > by_length) splits = by_length;
   return splits > 32 ? 32 : splits;
 }
 
 // Sets the shape of the decode kernels: `splits` slices, more if a slice's logits do not fit one workgroup's LDS; false if
-// they never do.  Whether they fit is asked of slices rounded up to 64 slots, though 16 is what the kernels need, so that the
-// contexts the library accepts and the numbers it settles on stay those it had with the longer slices.
+// they never do.
 bool set_splits(tkv::Params& p, int splits) {
-  bool fits;
-  for (;;) {
-    p.nsplit = splits;
-    p.rows_per_split = ((p.cap + splits - 1) / splits + 63) / 64 * 64;
-    fits = tkv::decode_shape_fits(p);
-    if (fits || splits >= tkv::DECODE_MAX_SPLITS) break;
+  while (!slices_fit(p, splits) && splits < tkv::DECODE_MAX_SPLITS) {
     splits = splits < 2 ? 2 : splits + (splits + 1) / 2;
     if (splits > tkv::DECODE_MAX_SPLITS) splits = tkv::DECODE_MAX_SPLITS;
   }
-  p.rows_per_split = ((p.cap + p.nsplit - 1) / p.nsplit + 15) / 16 * 16;
-  return fits;
+  p.nsplit = splits;
+  p.rows_per_split = ((p.cap + splits - 1) / splits + 15) / 16 * 16;
+  return slices_fit(p, splits);
 }
 
 }  // namespace
@@ -485,11 +518,11 @@ int treekv_init_ex(treekv_ctx** out, const treekv_config* cfg_in) {
   p.max_prompt = c.max_prompt;
   p.rope_base = c.rope_base;
   p.scale_log2e = c.softmax_scale * 1.4426950408889634f;
-  bool fits = set_splits(p, c.kv_splits > 0 ? c.kv_splits : pick_splits(c));
+  bool fits = set_splits(p, c.kv_splits > 0 ? c.kv_splits : pick_splits(p));
   // the entry point with static scratch takes every context that the smaller number would let it take
   if (c.kv_splits == 0 && p.nsplit > 1 &&
       split_scratch_bytes(p.U, p.G, p.cap, p.D, p.nsplit) > (size_t)TREEKV_STATIC_SCRATCH_BYTES)
-    fits = set_splits(p, pick_few_splits(c));
+    fits = set_splits(p, pick_few_splits(p));
   if (!fits) { delete ctx; return TREEKV_EUNSUPPORTED; }
   ctx->cfg.kv_splits = p.nsplit;
   ctx->ws_bytes = tkv::carve(p, nullptr);

@@ -113,7 +113,9 @@ def test_splits_follow_lds_capacity(binding):
 
 @pytest.mark.parametrize("units,group,budget,splits", [
     (32, 1, 1024, 8), (32, 8, 2048, 8), (2, 4, 4096, 24), (2, 8, 4096, 16), (96, 1, 256, 1), (96, 4, 256, 2), (128, 4, 4096, 2),
-    (129, 1, 512, 3), (170, 4, 1536, 3), (170, 4, 1535, 1), (171, 1, 4096, 1), (192, 1, 2048, 1), (1, 1, 64, 1),
+    (129, 1, 512, 3), (153, 1, 512, 1), (153, 1, 768, 3), (170, 2, 1536, 3), (170, 4, 2048, 3), (170, 4, 2047, 1), (171, 1, 4096, 1),
+    (192, 1, 2048, 1), (1, 1, 64, 1), (1, 1, 128, 2), (32, 1, 300, 3), (160, 8, 1024, 1),
+    (160, 8, 1500, 3),             # logits one workgroup's LDS does not hold
     (160, 1, 26000, 1),            # three slices' scratch would not fit the static array; one slice needs none
 ])
 def test_splits_chosen(binding, units, group, budget, splits):
@@ -160,6 +162,23 @@ def test_splits_never_exceed_what_the_merge_takes(binding):
                     for budget in (1 << e, (1 << e) + (1 << e - 1) + 3):
                         n = _splits(binding, units, group, head_dim, f32, flags, budget)
                         assert n == binding.TREEKV_EUNSUPPORTED or 1 <= n <= 64, (units, group, head_dim, f32, flags, budget, n)
+
+
+@pytest.mark.parametrize("units,group,head_dim,f32,rerank,budget,splits", [
+    # rows of 128 bytes: slices of about 208 slots beyond 16 units, and from eight slices on
+    (32, 1, 64, False, False, 319, 1), (32, 1, 64, False, False, 320, 2), (48, 1, 64, False, False, 640, 3),
+    (32, 1, 64, False, False, 1024, 4), (16, 1, 64, False, False, 1024, 8), (16, 1, 64, False, False, 2048, 8),
+    (8, 1, 64, False, False, 4096, 16), (32, 2, 64, False, False, 1024, 8), (32, 1, 64, False, True, 1024, 8),
+    # 129 to 170 units: one slice or three
+    (144, 1, 64, False, False, 1279, 1), (144, 1, 64, False, False, 1280, 3), (160, 1, 64, False, False, 1919, 1),
+    (160, 1, 64, False, False, 1920, 3), (160, 8, 64, False, False, 2048, 1), (160, 2, 64, False, True, 2048, 1),
+    (160, 4, 128, True, False, 512, 3), (160, 4, 64, True, False, 1023, 1), (160, 8, 64, False, True, 2048, 3),
+    # two short slices
+    (128, 1, 128, False, False, 256, 1), (128, 1, 128, True, False, 256, 2), (128, 1, 128, False, True, 256, 2),
+])
+def test_splits_chosen_by_row_size(binding, units, group, head_dim, f32, rerank, budget, splits):
+    flags = binding.TREEKV_POSITION_RERANK if rerank else 0
+    assert _splits(binding, units, group, head_dim, f32, flags, budget) == splits
 
 
 def test_prompt_compression_host_checks(binding):
