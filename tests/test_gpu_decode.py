@@ -220,12 +220,12 @@ def test_split_merge_edges(binding, oracle, G, d, dtype, budget, splits):
 @pytest.mark.parametrize("G,d,dtype,budget,splits,flags", [
     (1, 128, "bf16", 300, 7, 0),     # one padded batch of slices, their length a multiple of 16 only
     (8, 64, "bf16", 200, 8, 0),      # a whole batch; four slices' outputs requested at a time
-    (4, 128, "bf16", 257, 17, 0),    # three batches, the last of one slice and that one row
+    (4, 128, "bf16", 257, 17, 0),    # three batches, the last of one slice, and that two rows
     (2, 64, "f32", 130, 24, 0),      # empty slices inside the last batch
-    (1, 64, "bf16", 2060, 9, TREEKV_POSITION_RERANK),   # ranks beyond the entries requested up front
+    (1, 64, "bf16", 2060, 9, TREEKV_POSITION_RERANK),   # ring entries beyond those requested up front
 ])
 def test_split_merge_batches(binding, oracle, G, d, dtype, budget, splits, flags):
-    """Slices merged eight at a time, whatever number there is; the order arrays longer than a thread's first requests."""
+    """Slices merged eight at a time, whatever number there is; a recent window longer than a thread's first requests."""
     fill, steps = [512] * (budget // 512) + [budget % 512], 6
     T = budget + steps
     Q, K, V = inputs.batch_streams("lowrank" if dtype == "bf16" else "iid", 43, T, 1, 2, G, d, dtype=dtype)

@@ -91,13 +91,15 @@ def test_rerank_differs_from_plain_and_from_original_positions(binding, oracle):
 
 
 def _chunks(binding, oracle, schedule, *, B, H, Hkv, d, budget, n_sink, n_recent, seed, max_chunk=0, flags=0,
-            rope_base=0.0, units=None, dtype="bf16"):
+            rope_base=0.0, units=None, dtype="bf16", kv_splits=0):
     """Prefill chunks (and decode steps, 0) with re-assigned positions: the n0 cached tokens sit at ranks 0..n0-1, chunk
     token i at n0 + i; compared call by call."""
     T = sum(max(L, 1) for L in schedule)
     Q, K, V = inputs.batch_streams("lowrank" if dtype == "bf16" else "iid", seed, T, B, Hkv, H // Hkv, d, dtype=dtype)
     kv = binding.TreeKV(budget, H, d, kv_heads=Hkv, batch=B, dtype=dtype, n_sink=n_sink, n_recent=n_recent,
-                        max_chunk=max_chunk, flags=flags | binding.TREEKV_POSITION_RERANK, rope_base=rope_base)
+                        max_chunk=max_chunk, flags=flags | binding.TREEKV_POSITION_RERANK, rope_base=rope_base,
+                        kv_splits=kv_splits)
+    assert kv_splits in (0, kv.cfg.kv_splits)
     st = ph.run_schedule(oracle, kv, Q, K, V, schedule, dtype=dtype, units=units)
     st["score_err"] = ph.compare_scores(kv, st["results"], dtype)
     assert st["flagged"] <= max(2, st["decisions"] // 500), st["flagged"]
@@ -130,11 +132,35 @@ def test_rerank_chunks_fp32_storage(binding, oracle, G, d):
             n_recent=17, max_chunk=100, seed=66, dtype="f32", rope_base=300.0)
 
 
-def test_rerank_budget_beyond_the_lds_angle_tables(binding, oracle):
-    """6500 slots: the decode step's two small angle tables no longer fit beside the logits and the pairs come from
-    the context's full table; filled by chunks, then decode steps that evict."""
+@pytest.mark.parametrize("splits", [1, 5])
+def test_rerank_budget_beyond_the_lds_angle_tables(binding, oracle, splits):
+    """6500 slots at head_dim 128: the decode step's two small angle tables take 167 rows of 512 bytes, more than the 80 KB
+    they may have, and the pairs come from the context's full table; filled by chunks, then decode steps that evict."""
+    _chunks(binding, oracle, [512] * 13 + [0] * 20, B=1, H=1, Hkv=1, d=128, budget=6500, n_sink=4, n_recent=1000,
+            max_chunk=512, seed=67, kv_splits=splits)
+
+
+def test_rerank_long_budget_with_lds_angle_tables(binding, oracle):
+    """6500 slots at head_dim 64: order arrays several times longer than a thread's first requests, tables in LDS."""
     _chunks(binding, oracle, [512] * 13 + [0] * 120, B=1, H=1, Hkv=1, d=64, budget=6500, n_sink=4, n_recent=1000,
             max_chunk=512, seed=67)
+
+
+@pytest.mark.parametrize("splits", [1, 5])
+def test_rerank_more_evictions_into_a_round_than_requested_up_front(binding, oracle, splits):
+    """Order array of 2 x 2594 entries, 2300 evictions into its first round: both the entries before the round's evictions
+    and those behind what they consumed go past the 2048 a workgroup requests up front."""
+    _chunks(binding, oracle, [512] * 5 + [40] + [512] * 4 + [252] + [0] * 6, B=1, H=2, Hkv=2, d=64, budget=2600, n_sink=1,
+            n_recent=5, max_chunk=512, seed=69, kv_splits=splits)
+
+
+@pytest.mark.parametrize("G,d,budget", [(4, 128, 3500), (1, 128, 6000), (8, 64, 2900)])
+def test_rerank_fused_decode_with_tables_at_the_end_of_lds(binding, oracle, G, d, budget):
+    """One workgroup per unit whose logits and ranks push the angle tables past the first 128 KB of LDS (they end at
+    144 KB with 4 heads x 128, at 147 with 8 x 64 and at 130 with 1 x 128)."""
+    fill = [512] * (budget // 512) + [budget % 512]
+    _chunks(binding, oracle, fill + [200] + [0] * 6, B=1, H=2 * G, Hkv=2, d=d, budget=budget, n_sink=4,
+            n_recent=budget // 3, max_chunk=512, seed=70, kv_splits=1)
 
 
 def test_rerank_chunks_pure_algorithm1_many_tiles(binding, oracle):
