@@ -107,13 +107,14 @@ def _ptr(t):
 
 def _raw_stream(device) -> int:
     """The current stream of `device` as an address.  Without the torch.cuda.Stream object around it, and with plain numbers
-    for pointers, a step of the smallest decode configuration, which is the host's time, takes 5.3 us instead of 8.1."""
+    for pointers, a step of the smallest decode configuration, which is the host's time, takes 5.3 us instead of 8.1.  A torch
+    without that (unofficial) call, and a device that is no GPU, which raises, take the public one."""
     import torch
 
-    if device.type != "cuda":
-        return torch.cuda.current_stream(device).cuda_stream       # raises
-    index = device.index if device.index is not None else torch.cuda.current_device()
-    return torch._C._cuda_getCurrentRawStream(index)
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None or device.type != "cuda":
+        return torch.cuda.current_stream(device).cuda_stream
+    return raw(device.index if device.index is not None else torch.cuda.current_device())
 
 
 def wavelet_components(a, V, levels: int, per_head=None, mean=None):

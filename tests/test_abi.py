@@ -97,6 +97,21 @@ def test_missing_library_is_loud(binding, monkeypatch):
         binding.load()
 
 
+def test_current_stream_with_and_without_the_raw_call(binding, monkeypatch):
+    import torch
+
+    class Stream:
+        def __init__(self, index):
+            self.cuda_stream = 1000 + index
+
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda device: Stream(device.index))
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda index: 70 + index, raising=False)
+    assert binding._raw_stream(torch.device("cuda", 2)) == 72 and binding._raw_stream(torch.device("cuda")) == 73
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream")
+    assert binding._raw_stream(torch.device("cuda", 2)) == 1002
+
+
 def test_splits_follow_lds_capacity(binding):
     """A configuration whose per-unit logits do not fit one workgroup's LDS is split over more workgroups at init."""
     rc, h = _init(binding, budget=16384, q_heads=32, kv_heads=8, head_dim=128, batch=64, kv_splits=0)
