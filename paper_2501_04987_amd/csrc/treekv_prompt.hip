@@ -89,9 +89,10 @@ struct PromptStream {
   // ROPE: the (cos, sin) pairs of those dims at key base + lr are those at position base, the same for all keys of the
   // block (t_base, one row of the table per block), times those at lr, which never change (t_lane).  A row of pairs per
   // key was twice the key's own bytes on the way through the compute unit's load path: 2 x 12000 tokens x 8 KV heads x 4
-  // 81.0 us a call, 78.0 so.  The product's rounding, 2e-7 of an angle's pair, does not show beside the missing lo.lo term:
-  // token scores are off by 3.4e-6 to 1.8e-5 (2-norm, against 64 bits) over ten prompts of 1024 to 32768 tokens either way,
-  // larger in six and smaller in four of them, 0.7 % in the mean where single prompts differ by 4 to 8 %.
+  // 81.0 us a call, 78.0 so.  The product's rounding (a pair is off by 3.5e-8 rms, one from the table by 2.1e-8) does not show
+  // beside the missing lo.lo term: token scores are off by 1e-6 to 1e-4 (2-norm, against 64 bits) over 210 prompts of 1024 to
+  // 32768 tokens either way, larger in 111 and smaller in 96 of them, by 1.0025 +- 0.0033 in the geometric mean.  With the
+  // fourth product the error is 0.79 of that and the call up to 7 % longer.
   uint4 t_base[ROPE ? 2 * KS : 1], t_lane[ROPE ? 2 * KS : 1];
   uint4 qa[ROPE ? 1 : NB][KS];
   const uint16_t* sq;          // ROPE: LDS [hi, lo][NB * 16 rows][D], 16-byte pieces swizzled by row
@@ -245,7 +246,8 @@ __global__ __launch_bounds__(PP_THREADS) void prompt_stats_kernel(Params p, cons
   // two tiles of 32 keys in flight per wave: (k0, k1) and (k2, k3); a block is requested again, two tiles on,
   // as soon as its logits are out
   // (one tile with all eight operand blocks of queries: the registers do not hold more)
-  // (and with the rotary angles travelling with the keys)
+  // (and with the keys' angles, a row of the table per block: a second tile brings a long slice nothing, 190.8 and 191.5 us
+  // at 32 heads x 32768 tokens, and costs a short one its start, 32.6 and 37.4 at 4 heads x 4096)
   constexpr int AHEAD = (NB < 8 && !ROPE) ? 2 : 1;
   KB k0, k1, k2, k3;
   int base = st.begin + st.wave * PP_TILE;
