@@ -12,7 +12,8 @@
 //            (hi + lo) so that rounding P costs 2^-16, not 2^-9, and the probabilities' sums down the
 //            workgroup's rows.  Writes O; the column sums go, as 64-bit fixed point, into one accumulator
 //            per column of the unit with integer atomic adds (which commute exactly: whatever order the
-//            workgroups arrive in, the sum is the same to the bit).
+//            workgroups arrive in, the sum is the same to the bit).  Up to 2560 visible columns a workgroup of 32
+//            rows keeps their logits in registers and passes over the columns once.
 //   replay   grid U.  Adds the accumulated column sums to the scores (Algorithm 1's S update) and clears the
 //            accumulators, then Algorithm 1's eviction for the chunk's tokens with frozen scores.  Inside one
 //            sweep of idx over the tree region the scopes are disjoint pairs, so a sweep is one
@@ -23,6 +24,8 @@
 //
 // Token ids during the replay: a slot number (< cap) for a cached token, cap + i for chunk
 // token i that has no slot yet.
+
+#include <type_traits>
 
 #include "treekv_internal.h"
 
@@ -763,6 +766,394 @@ __global__ __launch_bounds__(AT_THREADS, D == 64 && !ROPE ? 4 : 2) void prefill_
 }
 
 // ---------------------------------------------------------------------------------------------
+// attend with the logits kept in registers
+// ---------------------------------------------------------------------------------------------
+// One workgroup owns 32 query rows of one head and keeps all their logits: a wave takes 32-column blocks w, w + 8, .. of
+// the visible columns, up to ten of them, 16 registers each.  Queries meet keys once and every logit has one exponential,
+// where the two-sweep kernel above does both twice.  What is left of its structure:
+//   logits   S^T = K Q^T with v_mfma_f32_32x32x16_bf16, a lane holding 16 columns of one row.  The exponentials of block t
+//            are taken while the products of block t + 1 run, against the lane's running maximum; what each block's are
+//            relative to is kept (ref) instead of rescaling them.
+//   merge    maxima and sums: two lanes of a row, then eight waves through LDS; one barrier.
+//   O^T      += V^T P^T.  A lane's logits are the B operand as they lie (with the columns of a k-step in the order the
+//            transposing reads of V fetch them in); P is split into two bf16 halves as above.
+//   sums     of a block's columns over the 32 rows stay inside the wave and go straight to the unit's accumulators.
+// A wave reads only what it requested itself, two blocks ahead, so the blocks take no barrier.  Lane-dependent addresses
+// are worked out anew where they are used: held, they would spill (256 registers, all of them taken at the last block).
+//
+// Bound by the vector ALU's issue (a block costs a wave some 440 cycles of it for the logits and 500 for O, the products
+// of which take 270 and 550 of the matrix pipe) and by the path from L2: a workgroup takes in every K and V row, 604 MB
+// for 512 tokens into 2048 slots at 32 heads, 5.3 us for a workgroup's keys alone, where 8.3 are measured with the
+// arithmetic and 5.0 for the arithmetic alone; for O 5.0, 9.6 and 8.1.  Starting up, merging and writing out take 7 us of a
+// workgroup's 26, which is why short chunks gain most: one sequence of 8 KV heads, 100 tokens into 1024 slots, 38.4 ->
+// 22.6 us a call; 32 heads, 32 into 2048, 53.2 -> 31.2; 512 into 2048 72 -> 65, with re-assigned positions 112 -> 95.
+// Measured and not kept: v_dot2 for the remainder of the split (it runs on the matrix pipe: 5 % longer), twelve waves of
+// seven blocks at head_dim 64 (no change), wave priorities around the products or by wave (no change).
+typedef __attribute__((ext_vector_type(16))) float f32x16_t;
+
+constexpr int RES_ROWS = 32;                       // query rows of a workgroup
+constexpr int RES_WAVES = AT_THREADS / 64;
+constexpr int RES_BLOCKS = 10;                     // 32-column blocks of logits a wave holds: 160 registers
+typedef unsigned uint4v_t __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) const uint4v_t lds_uint4_t;
+
+template <int D, bool ROPE>
+struct ResidentLds {
+  static constexpr int STAGE = 32 * D * 2;                          // one block of K (one part of it with ROPE) or V rows
+  static constexpr int STAGES = 2;
+  static constexpr int RING = RES_WAVES * STAGES * STAGE;                   // every wave its own stages
+  static_assert(STAGES * STAGE == RES_ROWS * D * 4, "a wave's stages hold its outputs at the end");
+  static constexpr int STATS = RING;                                // [waves][32 rows] (max, sum)
+  static constexpr int QLO = STATS + RES_WAVES * RES_ROWS * 8;              // the queries' second parts, as operands (ROPE)
+  static constexpr int BYTES = QLO + (ROPE ? RES_ROWS * D * 2 : 0);
+};
+
+__device__ inline f32x16_t mfma32(const uint4& a, const uint4& b, const f32x16_t& c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
+}
+
+// the same address, in scalar registers
+__device__ inline const char* scalar_ptr(const void* ptr) {
+  const uint64_t a = (uint64_t)(uintptr_t)ptr;
+  const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)a), hi = __builtin_amdgcn_readfirstlane((unsigned)(a >> 32));
+  return reinterpret_cast<const char*>((uintptr_t)((uint64_t)hi << 32 | lo));
+}
+
+template <int D, bool ROPE>
+__global__ __launch_bounds__(AT_THREADS, 2) void prefill_attend_resident_kernel(Params p, const uint16_t* __restrict__ Q,
+                                                                             const uint16_t* __restrict__ Kc,
+                                                                             const uint16_t* __restrict__ Vc, int L,
+                                                                             int row_tiles, float* __restrict__ out) {
+  using Lds = ResidentLds<D, ROPE>;
+  constexpr int KS = D / 16;                         // k-steps of the q.k contraction
+  constexpr int DB = D / 32;                         // 32-wide blocks of the head dimension
+  constexpr int PARTS = D / 8, ROWB = D * 2;         // 16-byte pieces, bytes of a row
+  constexpr int RPC = 1024 / ROWB;                   // rows per 1 KB request
+  constexpr int REQ = 32 / RPC;                      // requests per block
+  constexpr int KPARTS = ROPE ? 2 : 1;
+  extern __shared__ __attribute__((aligned(1024))) uint16_t pf_smem[];
+  char* smem = reinterpret_cast<char*>(pf_smem);
+
+  // a unit's row tiles share one XCD's L2 (see the two-sweep kernel); the longest row tiles first
+  const int n_items = row_tiles * p.G * p.U, per_xcd = (n_items + 7) / 8;
+  const int item = ((int)blockIdx.x % 8) * per_xcd + (int)blockIdx.x / 8;
+  if (item >= n_items) return;
+  const int row_tile = __builtin_amdgcn_readfirstlane(row_tiles - 1 - item % row_tiles);
+  const int head = __builtin_amdgcn_readfirstlane(item / row_tiles);                 // (unit, query head of its group)
+  const int unit = __builtin_amdgcn_readfirstlane(head / p.G), g = head - unit * p.G;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r32 = lane & 31, half = lane >> 5, lr = lane & 15, g1 = (lane >> 4) & 1;
+  const int b = __builtin_amdgcn_readfirstlane(unit / p.Hkv), kvh = unit - b * p.Hkv, h = kvh * p.G + g;
+  // B operands: query row r32, dims 16 ks + 8 half .. + 7 (rows past the chunk repeat its last row)
+  const uint16_t* Qsrc = ROPE ? p.pf_qrot : Q;
+  const size_t q_part = (size_t)p.B * p.max_chunk * p.H * D;      // pf_qrot: [hi, lo][B][max_chunk][H][D]
+  const int q_rows = ROPE ? p.max_chunk : L;
+  const uint16_t* qp = Qsrc + (((size_t)b * q_rows + min(row_tile * RES_ROWS + r32, L - 1)) * p.H + h) * D + half * 8;
+  uint4 qa[KS];
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) qa[ks] = *reinterpret_cast<const uint4*>(qp + ks * 16);
+  const int* meta = p.meta + (size_t)unit * META_STRIDE;
+  const int n = __builtin_amdgcn_readfirstlane(meta[META_N]), fslot = __builtin_amdgcn_readfirstlane(meta[META_FREE]);
+  const int rbase = row_tile * RES_ROWS, my_row = rbase + r32;
+  // columns: the cached tokens' slots in slot order without the free one, then the chunk's tokens; blocks of 32 of either
+  const int cache_blk = (n + 31) / 32, nblk = cache_blk + row_tile + 1;
+  const int cnt = (nblk - wave + RES_WAVES - 1) / RES_WAVES;                           // this wave's blocks: wave, wave + RES_WAVES, ..
+
+  const size_t krot_rows = (size_t)p.cap + p.max_chunk;            // pf_krot: [U][hi, lo][cap + max_chunk][D]
+  const uint16_t* Ku = ROPE ? p.pf_krot + (size_t)unit * 2 * krot_rows * D : (const uint16_t*)p.K + (size_t)unit * p.cap * D;
+  const uint16_t* Vu = (const uint16_t*)p.V + (size_t)unit * p.cap * D;
+  const int vstride = p.Hkv * D, kstride = ROPE ? D : vstride;     // of the chunk's own rows
+  const uint16_t* Kcu = ROPE ? Ku + (size_t)p.cap * D : Kc + ((size_t)b * L * p.Hkv + kvh) * D;
+  const uint16_t* Vcu = Vc + ((size_t)b * L * p.Hkv + kvh) * D;
+  const size_t klo_off = krot_rows * D;
+
+  // ---- requests: the wave's blocks of K (with ROPE the hi, then the lo part of each), then its blocks of V ----
+  // slot s of row r of a staged block holds 16-byte piece s ^ KSWZ(r) or s ^ VSWZ(r), so that the operand reads touch
+  // every bank once
+  auto kswz = [](int r) { return D == 128 ? (r & 15) : ((r >> 1) & 7); };
+  auto vswz = [](int r) { return D == 128 ? ((r & 3) << 2) : (((r >> 1) & 1) << 2); };
+  const int a_lrow = lane / PARTS, a_slot = lane % PARTS;
+  const unsigned k_from = a_lrow * ROWB + (a_slot ^ kswz(a_lrow)) * 16;        // of request x: ^ (x % 4) * 64 or (x % 2) * 64
+  static_assert(D == 64 || D == 128, "swizzles are written for head_dim 64 and 128");
+  const unsigned ring = __builtin_amdgcn_readfirstlane(lds_address(pf_smem)) + wave * (Lds::STAGES * Lds::STAGE);
+  // bit i: the wave's i-th block is a run of cache rows / one that starts a row further on, behind the free slot / reaches
+  // past what the first row sees
+  unsigned run_blocks, moved_blocks, mask_blocks;
+  {
+    const int blk = wave + lane * RES_WAVES;
+    const bool is_cache = blk < cache_blk;
+    const int col0 = (is_cache ? blk : blk - cache_blk) * 32, from = fslot - col0;
+    run_blocks = (unsigned)__ballot(is_cache && col0 + 32 <= n && (from <= 0 || from >= 32));
+    moved_blocks = (unsigned)__ballot(from <= 0);
+    mask_blocks = (unsigned)__ballot(col0 + 31 > (is_cache ? n - 1 : rbase));
+  }
+  auto request_rows = [&](const uint16_t* cache_src, const uint16_t* chunk_src, int stride, int i, unsigned m0, auto is_k) {
+    int l = lane;
+    asm volatile("" : "+v"(l));                      // worked out anew each time: held, this would take the logits' registers
+    const unsigned v_from = l / PARTS * ROWB + (l % PARTS ^ vswz(l / PARTS)) * 16;            // the same for every request
+    auto from_of = [&](int x) { return decltype(is_k)::value ? k_from ^ (unsigned)((D == 128 ? x & 3 : x & 1) * 64) : v_from; };
+    if (run_blocks >> i & 1) {
+      const char* base = scalar_ptr(reinterpret_cast<const char*>(cache_src) + (unsigned)((wave + i * RES_WAVES) * 32 * ROWB) +
+                                    (moved_blocks >> i & 1) * ROWB);
+#pragma unroll
+      for (int x = 0; x < REQ; x += 4)
+        async_copy16_run(base + x * 1024, m0 + x * 1024, from_of(x), from_of(x + 1), from_of(x + 2), from_of(x + 3));
+    } else {                                         // rows past the last one that exists repeat it (they are masked)
+      const int blk = wave + i * RES_WAVES;
+      const bool is_cache = blk < cache_blk;
+      const int col0 = (is_cache ? blk : blk - cache_blk) * 32;
+      const int rstride = is_cache ? D : stride;
+      const char* base = scalar_ptr((is_cache ? cache_src : chunk_src) + (size_t)col0 * rstride);
+      const int lim = (is_cache ? p.cap : L) - 1 - col0, moved_from = is_cache ? fslot - col0 : 32;
+#pragma unroll 1
+      for (int x = 0; x < REQ; ++x) {
+        const int c = x * RPC + l / PARTS, row = min(c + (c >= moved_from ? 1 : 0), lim);
+        async_copy16_offset(base, (unsigned)(row * rstride) * 2 + (from_of(x) & (ROWB - 1)), m0 + x * 1024);
+      }
+    }
+  };
+  const int nk = cnt * KPARTS;
+  auto request_k = [&](int u) {                      // u-th part-block of K
+    const size_t off = ROPE && (u & 1) ? klo_off : 0;
+    request_rows(Ku + off, Kcu + off, kstride, ROPE ? u >> 1 : u, ring + (u & 1) * Lds::STAGE, std::true_type{});
+  };
+  auto request_v = [&](int i) {                      // i-th block of V
+    if (i < cnt) request_rows(Vu, Vcu, vstride, i, ring + ((nk + i) & 1) * Lds::STAGE, std::false_type{});
+  };
+  auto request_after_k = [&](int u) { if (u < nk) request_k(u); else request_v(u - nk); };
+  // block u of K and V together has landed: of what was requested after it, only block u + 1 may be out
+  auto landed = [&](int u) { if (u + 1 < nk + cnt) wait_vmcnt<REQ>(); else wait_vmcnt<0>(); };
+  // a staged block's operand reads have returned: its stage can be requested anew
+  auto reads_done = [&]() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); };
+
+  const uint4* qlo = reinterpret_cast<const uint4*>(smem + Lds::QLO) + lane;      // [KS][64 lanes]
+  if constexpr (ROPE) {
+    static_assert(KS <= 8, "one k-step per wave");
+    if (wave < KS) reinterpret_cast<uint4*>(smem + Lds::QLO)[wave * 64 + lane] = *reinterpret_cast<const uint4*>(qp + q_part + wave * 16);
+    __syncthreads();
+  }
+  if (cnt > 0) {
+    request_k(0);
+    request_after_k(1);
+  }
+
+  // ------------------------------------------------------------------------------------------
+  // logits, and their exponentials against the running maximum of the lane
+  // ------------------------------------------------------------------------------------------
+  const float sc = p.scale_log2e;
+  f32x16_t s[RES_BLOCKS];            // S^T: component e is column 8 (e / 4) + 4 half + e % 4 of row r32
+  float ref[RES_BLOCKS];             // what block t's exponentials are relative to (scaled log2 domain)
+  float m_run = NEG_BIG, l_run = 0.f;
+  const unsigned stages = lds_address(pf_smem) + wave * (Lds::STAGES * Lds::STAGE);
+  const unsigned k_lane = stages + r32 * ROWB + (half ^ kswz(r32)) * 16;       // k-step ks: piece 2 ks + half
+  auto mask = [&](f32x16_t& x, int t) {
+    if (mask_blocks >> t & 1) {
+      const int blk = wave + t * RES_WAVES;
+      const bool is_cache = blk < cache_blk;
+      const int lim = (is_cache ? n - 1 - blk * 32 : my_row - (blk - cache_blk) * 32) - half * 4;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) x[e] = (e >> 2) * 8 + (e & 3) <= lim ? x[e] : -INFINITY;
+    }
+  };
+  auto exps = [&](f32x16_t& x, int t) {
+    float mx = fmaxf(x[0], x[1]);
+#pragma unroll
+    for (int e = 2; e < 16; e += 2) mx = max3(mx, x[e], x[e + 1]);
+    const float m_new = fmaxf(m_run, mx * sc);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) x[e] = fast_exp2(fmaf(x[e], sc, -m_new));
+    const float s0 = (x[0] + x[1]) + (x[2] + x[3]), s1 = (x[4] + x[5]) + (x[6] + x[7]);
+    const float s2 = (x[8] + x[9]) + (x[10] + x[11]), s3 = (x[12] + x[13]) + (x[14] + x[15]);
+    l_run = fmaf(l_run, fast_exp2(m_run - m_new), (s0 + s1) + (s2 + s3));
+    m_run = m_new;
+    ref[t] = m_new;
+  };
+  auto read_k = [&](uint4 (&k)[KS], int u) {
+    unsigned a = k_lane;
+    asm volatile("" : "+v"(a));
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) k[ks] = __builtin_bit_cast(uint4, *(lds_uint4_t*)(uintptr_t)((a ^ (ks * 32)) + (u & 1) * Lds::STAGE));
+  };
+#pragma unroll
+  for (int t = 0; t < RES_BLOCKS; ++t) {
+    if (t < cnt) {
+      f32x16_t acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      uint4 k[KS];
+      landed(t * KPARTS);
+      read_k(k, t * KPARTS);
+      reads_done();
+      request_after_k(t * KPARTS + 2);
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) acc = mfma32(k[ks], qa[ks], acc);
+      if constexpr (ROPE) {
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) acc = mfma32(k[ks], qlo[ks * 64], acc);
+        landed(t * 2 + 1);
+        read_k(k, t * 2 + 1);
+        reads_done();
+        request_after_k(t * 2 + 3);
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) acc = mfma32(k[ks], qa[ks], acc);
+      }
+      s[t] = acc;
+      if (t > 0) exps(s[t - 1 < 0 ? 0 : t - 1], t - 1);          // while the products run
+      mask(s[t], t);
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < RES_BLOCKS; ++t)
+    if (t == cnt - 1) exps(s[t], t);
+
+  // ---- row statistics: the two lanes of a row, then the waves ----
+  float* st = reinterpret_cast<float*>(smem + Lds::STATS);
+  {
+    const float mo = __shfl_xor(m_run, 32, 64), lo = __shfl_xor(l_run, 32, 64);
+    const float mn = fmaxf(m_run, mo);
+    const float l = l_run * fast_exp2(m_run - mn) + lo * fast_exp2(mo - mn);
+    if (half == 0) *reinterpret_cast<float2*>(st + (wave * RES_ROWS + r32) * 2) = make_float2(mn, l);
+  }
+  // (not __syncthreads, which would wait for the blocks of V on their way; here and below only LDS passes between waves)
+  auto block_sync = [] { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+  block_sync();
+  float mx = NEG_BIG, sum = 0.f;
+  {
+    float2 w[RES_WAVES];
+#pragma unroll
+    for (int i = 0; i < RES_WAVES; ++i) w[i] = *reinterpret_cast<const float2*>(st + (i * RES_ROWS + r32) * 2);
+#pragma unroll
+    for (int i = 0; i < RES_WAVES; ++i) mx = fmaxf(mx, w[i].x);
+#pragma unroll
+    for (int i = 0; i < RES_WAVES; ++i) sum += w[i].y * fast_exp2(w[i].x - mx);
+  }
+  const float inv = my_row < L ? 1.0f / sum : 0.f;                 // rows past the chunk must not reach the column sums
+  // to probabilities: the first blocks while the matrix pipe works on the block before them, the others here, because there
+  // is no register for their references later
+  constexpr int LATE = 4;
+  auto scale = [&](int t) {
+    const float f = fast_exp2(ref[t] - mx) * inv;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) s[t][e] *= f;
+  };
+#pragma unroll
+  for (int t = LATE; t < RES_BLOCKS; ++t)
+    if (t < cnt) scale(t);
+
+  // ------------------------------------------------------------------------------------------
+  // O^T += V^T P^T, column sums
+  // ------------------------------------------------------------------------------------------
+  f32x16_t o[DB];
+#pragma unroll
+  for (int d = 0; d < DB; ++d)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) o[d][e] = 0.f;
+  // the lane's address for the transposing read: row 4 half + lr / 4 of a k-step's 16 (second read: 8 rows on), dims
+  // 32 db + 16 g1 + 4 (lr % 4) ..
+  const int v_row = half * 4 + (lr >> 2);
+  const unsigned v_lane = stages + v_row * ROWB + (lr & 1) * 8 + ((g1 * 2 + ((lr >> 1) & 1)) ^ vswz(v_row)) * 16;
+  // one k-step's eight probabilities as P^T operands, two bf16 parts each (see the two-sweep kernel)
+  auto split = [&](const f32x16_t& x, int k, uint4& phi, uint4& plo) {
+    phi = make_uint4(pack_bf16(x[k], x[k + 1]), pack_bf16(x[k + 2], x[k + 3]), pack_bf16(x[k + 4], x[k + 5]), pack_bf16(x[k + 6], x[k + 7]));
+    const unsigned h[4] = {phi.x, phi.y, phi.z, phi.w};
+    unsigned l[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      l[e] = pack_bf16(x[k + e * 2] - __uint_as_float(h[e] << 16), x[k + e * 2 + 1] - __uint_as_float(h[e] & 0xffff0000u));
+    plo = make_uint4(l[0], l[1], l[2], l[3]);
+  };
+  // the sums of a block's 32 columns over the 32 rows; the probabilities are used up
+  auto column_sums = [&](f32x16_t& x) {
+    float y[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {                    // the two 16-lane halves of the rows: lanes g1 = 0 take column e, g1 = 1 column e + 8
+      const auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(x[e]), __float_as_uint(x[e + 8]), false, false);
+      y[e] = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+    }
+    const float2 c = row16_sum8(y);
+    return lr & 1 ? c.y : c.x;
+  };
+  // integer adds commute exactly: the sums are the same to the bit whatever order a unit's row tiles and heads arrive in
+  const int cap_cols = (p.cap + AT_COLS - 1) / AT_COLS * AT_COLS;
+  const int cs_stride = cap_cols + (p.max_chunk + AT_COLS - 1) / AT_COLS * AT_COLS;
+  unsigned long long* cs_acc = p.pf_colacc + (size_t)unit * cs_stride;
+  auto add_columns = [&](int t, float sum) {         // lanes lr % 4 < 2 hold one column each
+    const int blk = wave + t * RES_WAVES;
+    const bool is_cache = blk < cache_blk;
+    int l = lane;
+    asm volatile("" : "+v"(l));
+    const int c = (l >> 4 & 1) * 8 + (l >> 2 & 3) * 2 + (l & 1);         // the accumulator whose sum column_sums left here
+    const int col = (is_cache ? blk : blk - cache_blk) * 32 + (c >> 2) * 8 + (l >> 5) * 4 + (c & 3);
+    const int at = is_cache ? col + (col >= fslot ? 1 : 0) : cap_cols + col;
+    const float x = sum * 256.f, whole = floorf(x);  // 2^40 times the sum, in two 32-bit words
+    const unsigned long long fix = (unsigned long long)(unsigned)whole << 32 | (unsigned)rintf((x - whole) * 0x1p32f);
+    if ((l & 2) == 0 && col < (is_cache ? n : L)) atomicAdd(cs_acc + (unsigned)at, fix);
+  };
+  float csum;
+  uint4 phi[2], plo[2];
+  auto prepare = [&](int t) {
+    if (t < LATE) scale(t);
+    split(s[t], 0, phi[0], plo[0]);
+    split(s[t], 8, phi[1], plo[1]);
+    csum = column_sums(s[t]);
+  };
+  if (cnt > 0) prepare(0);
+#pragma unroll
+  for (int t = 0; t < RES_BLOCKS; ++t) {
+    if (t < cnt) {
+      const int u = nk + t;
+      landed(u);
+      unsigned va0 = v_lane + (u & 1) * Lds::STAGE;
+      asm volatile("" : "+v"(va0));
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+        uint4 va[DB];
+#pragma unroll
+        for (int d = 0; d < DB; ++d) {
+          const unsigned a = (va0 ^ (d * 64)) + ks * 16 * ROWB;
+          const short4_t t0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_t*)(uintptr_t)a);
+          const short4_t t1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_t*)(uintptr_t)(a + 8 * ROWB));
+          const uint2 a0 = __builtin_bit_cast(uint2, t0), a1 = __builtin_bit_cast(uint2, t1);
+          va[d] = make_uint4(a0.x, a0.y, a1.x, a1.y);
+        }
+        if (ks == 1) {
+          add_columns(t, csum);                      // (ahead of the requests, which are waited for later than it)
+          reads_done();
+          request_v(t + 2);
+        }
+#pragma unroll
+        for (int d = 0; d < DB; ++d) o[d] = mfma32(va[d], phi[ks], o[d]);
+#pragma unroll
+        for (int d = 0; d < DB; ++d) o[d] = mfma32(va[d], plo[ks], o[d]);
+      }
+      if (t + 1 < RES_BLOCKS) prepare(t + 1);        // (of no use behind the last one, and of no harm)
+    }
+  }
+
+  // ---- add the waves' outputs ----
+  // a wave's own stages take its outputs; 16-byte piece x of row r sits in slot x ^ r
+  constexpr int OP = D / 4;
+  float4* xo = reinterpret_cast<float4*>(smem + wave * (Lds::STAGES * Lds::STAGE));
+#pragma unroll
+  for (int d = 0; d < DB; ++d)
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      xo[r32 * OP + ((d * 8 + q * 2 + half) ^ (r32 & (OP - 1)))] = make_float4(o[d][q * 4], o[d][q * 4 + 1], o[d][q * 4 + 2], o[d][q * 4 + 3]);
+  block_sync();
+  for (int y = tid; y < RES_ROWS * OP; y += AT_THREADS) {
+    const int row = y / OP, x = y % OP;
+    if (rbase + row >= L) break;                     // rows ascend with y
+    const float4* src = reinterpret_cast<const float4*>(smem) + row * OP + (x ^ (row & (OP - 1)));
+    float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int w = 0; w < RES_WAVES; ++w) {
+      const float4 v = src[w * RES_ROWS * OP];
+      a.x += v.x; a.y += v.y; a.z += v.z; a.w += v.w;
+    }
+    *reinterpret_cast<float4*>(out + (((size_t)b * L + rbase + row) * p.H + h) * D + x * 4) = a;
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
 // attend for fp32 storage
 // ---------------------------------------------------------------------------------------------
 // The same four steps (logits, row softmax, output, column sums) with v_mfma_f32_16x16x4_f32: fp32 operands, fp32
@@ -1389,14 +1780,22 @@ int launch_prefill_d(const Params& p, const void* Q, const void* K, const void* 
   const uint16_t* q = (const uint16_t*)Q;
   const uint16_t* k = (const uint16_t*)K;
   const uint16_t* v = (const uint16_t*)V;
-  const int row_tiles = (L + ROW_TILE - 1) / ROW_TILE;
   const bool rope = (p.flags & TREEKV_POSITION_RERANK) != 0;
   if (rope) {
     const int rows = p.budget + L + L * p.G;           // at most: every cached key, the chunk's keys and queries
     hipLaunchKernelGGL(prefill_turn_kernel<D>, dim3((rows * (D / 8) + 255) / 256, p.U), dim3(256), 0, s, p, q, k, L);
   }
-  auto attend = rope ? prefill_attend_kernel<D, true> : prefill_attend_kernel<D, false>;
-  const size_t lds = AttendLds<D>::BYTES;
+  // Logits in registers where a workgroup's fit: the fixed part of the call is shorter by far and the keys are multiplied once.
+  // Plain head_dim 64, where four waves of the two-sweep kernel share a SIMD, only while that leaves compute units idle or
+  // nearly so (us a call, two sweeps / registers, 512 tokens into 2048 slots: 16 heads 51 / 31, 32 heads 53 / 48, 48 heads
+  // 73 / 67, 64 heads 73 / 76; 256 heads: 32 tokens 51 / 43, 64 tokens 53 / 57).
+  const int res_tiles = (L + RES_ROWS - 1) / RES_ROWS, res_items = res_tiles * p.G * p.U;
+  const bool resident = (p.budget + 31) / 32 + (L + 31) / 32 <= RES_WAVES * RES_BLOCKS &&
+                        (D == 128 || rope || res_items <= 256 || (res_items <= 768 && res_tiles >= 4));
+  auto attend = resident ? (rope ? prefill_attend_resident_kernel<D, true> : prefill_attend_resident_kernel<D, false>)
+                         : (rope ? prefill_attend_kernel<D, true> : prefill_attend_kernel<D, false>);
+  const int row_tiles = resident ? res_tiles : (L + ROW_TILE - 1) / ROW_TILE;
+  const size_t lds = !resident ? AttendLds<D>::BYTES : rope ? ResidentLds<D, true>::BYTES : ResidentLds<D, false>::BYTES;
   if (lds > 48 * 1024 &&
       hip_failed(hipFuncSetAttribute((const void*)attend, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)))
     return TREEKV_EHIP;

@@ -102,6 +102,24 @@ def test_prefill_free_slot_at_a_tile_edge(binding, oracle, d, free):
          n_recent=400 - free - 1, max_chunk=400, seed=24, flags=binding.TREEKV_KEEP_LEFT)
 
 
+@pytest.mark.parametrize("d,rerank,G,budget,schedule", [
+    (128, False, 1, 31, [31, 32, 33, 1]),              # blocks and row tiles of 32: exact, one over, one under
+    (128, False, 2, 64, [64, 64, 95, 0, 97]),
+    (128, True, 1, 96, [40, 56, 33, 0, 31]),
+    (64, False, 1, 255, [200, 55, 64, 32, 0, 5]),      # eight waves, one block each and one less
+    (64, True, 2, 257, [257, 40, 3]),
+    (128, False, 1, 2048, [512, 512, 512, 512, 512, 31]),    # 80 blocks: all that registers hold
+    (128, True, 1, 2016, [512, 512, 512, 480, 512, 512]),
+    (128, False, 1, 2049, [512, 512, 512, 512, 512, 512]),   # one slot more: the two-sweep kernel, except for a shorter chunk
+    (64, False, 1, 2049, [512, 512, 512, 512, 480, 512]),
+])
+def test_prefill_logits_in_registers(binding, oracle, d, rerank, G, budget, schedule):
+    """Edges of the 32-column blocks, of the 32-row tiles and of what a workgroup's registers hold."""
+    flags = binding.TREEKV_POSITION_RERANK if rerank else 0
+    _run(binding, oracle, schedule, B=1, H=2 * G, Hkv=2, d=d, budget=budget, n_sink=min(2, budget // 4),
+         n_recent=budget // 3, max_chunk=512, seed=11, flags=flags, units=[(0, 1)])
+
+
 def test_prefill_argument_errors(binding):
     import torch
 
