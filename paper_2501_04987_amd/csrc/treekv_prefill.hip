@@ -5,7 +5,7 @@
 // scores are then frozen and Algorithm 1's append / compare / evict / advance
 // is replayed for the L tokens.  L = 1 gives the decode step.
 //
-// Three launches per chunk (with re-assigned positions a fourth before them, which turns keys and queries):
+// Three launches per chunk, two for short ones (with re-assigned positions a fourth before them, which turns keys and queries):
 //   attend   grid row tiles x G x U (ids remapped so that a unit's row tiles share an XCD's L2).  Two passes
 //            over all visible columns with MFMA (16x16x32 bf16): the first finds the row statistics, the
 //            second forms the final probabilities, O^T += V^T P^T with P split into two bf16 halves
@@ -20,7 +20,7 @@
 //            parallel pass; sweeps run one after the other.  Then surviving chunk tokens are
 //            matched with freed slots (ballot ranks), the order arrays are rewritten and the retained
 //            positions emitted.
-//   scatter  one wave per chunk token: the surviving rows are copied into their slots.
+//   scatter  one wave per chunk token: the surviving rows are copied into their slots (short chunks: by the replay).
 //
 // Token ids during the replay: a slot number (< cap) for a cached token, cap + i for chunk
 // token i that has no slot yet.
@@ -1482,7 +1482,11 @@ __host__ __device__ inline size_t replay_lds_words(int m, int cap, int r, int L)
 // Tokens that lose a scope: a cached token frees its slot, a chunk token that has no slot yet just disappears.  The
 // k-th slot freed (in the order of the eviction steps, the slot that was free before the chunk first) goes to the
 // k-th surviving chunk token without a slot (in chunk order); the one slot left over is the next call's free slot.
-template <bool IN_LDS>
+//
+// HELD > 0: the kernel also copies the surviving rows into their slots.  A thread asks for HELD 16-byte pieces of the
+// chunk's K and of its V at the start, holds them while the evictions are worked out and stores those whose token lives:
+// the loads cost nothing beside the replay's own round trips, and the launch of the scatter kernel is saved.
+template <bool IN_LDS, int HELD>
 __global__ __launch_bounds__(RP_THREADS) void prefill_replay_kernel(Params p, int L, const uint4* __restrict__ Kc,
                                                                     const uint4* __restrict__ Vc, int row_vec,
                                                                     int32_t* __restrict__ retained,
@@ -1534,19 +1538,39 @@ __global__ __launch_bounds__(RP_THREADS) void prefill_replay_kernel(Params p, in
     a_pre[u] = acc[min(x, cap - 1)];
     n_pre[u] = acc[cap_cols + min(x, L - 1)];
   }
+  // The order arrays are read whole, dead entries too: which are live hangs on a bookkeeping word, one round trip more.
+  constexpr int PRE_E = 4;
+  int e_pre[PRE_E], pe_pre[PRE_E], r_pre = 0;
   if constexpr (IN_LDS) {
-    // only the live entries: after j0 evictions of the sweep in progress the region reads E[0, j0) and E[2 j0, m + j0)
-    for (int i0 = 0; i0 < m; i0 += 4 * RP_THREADS) {
-      int e[4], pe[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) { const int x = tree_index(min(i0 + u * RP_THREADS + tid, m - 1), j0); e[u] = Eg[x]; pe[u] = PEg[x]; }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int k = i0 + u * RP_THREADS + tid;
-        if (k < m) { Eu[tree_index(k, j0)] = e[u]; PEu[tree_index(k, j0)] = pe[u]; }
-      }
+    for (int u = 0; u < PRE_E; ++u) {
+      const int x = min(u * RP_THREADS + tid, 2 * m - 1);
+      e_pre[u] = Eg[x];
+      pe_pre[u] = PEg[x];
     }
-    for (int i = tid; i < r; i += RP_THREADS) Ru[i] = Rg[i];
+    r_pre = Rg[min(tid, max(r, 1) - 1)];
+  }
+  constexpr int HOLD = HELD > 0 ? HELD : 1;
+  uint4v_t k_held[HOLD], v_held[HOLD];                // pieces u * 1024 + tid of the unit's L rows of row_vec pieces
+  if constexpr (HELD > 0) {
+    const int kvh = unit % p.Hkv, b = unit / p.Hkv;
+#pragma unroll
+    for (int u = 0; u < HELD; ++u) {
+      const int x = min(u * RP_THREADS + tid, L * row_vec - 1), i = x / row_vec, e = x - i * row_vec;
+      const size_t src = (((size_t)b * L + i) * p.Hkv + kvh) * row_vec + e;
+      k_held[u] = reinterpret_cast<const uint4v_t*>(Kc)[src];
+      v_held[u] = reinterpret_cast<const uint4v_t*>(Vc)[src];
+    }
+  }
+  if constexpr (IN_LDS) {
+#pragma unroll
+    for (int u = 0; u < PRE_E; ++u) {
+      const int x = u * RP_THREADS + tid;
+      if (x < 2 * m) { Eu[x] = e_pre[u]; PEu[x] = pe_pre[u]; }
+    }
+    for (int x = PRE_E * RP_THREADS + tid; x < 2 * m; x += RP_THREADS) { Eu[x] = Eg[x]; PEu[x] = PEg[x]; }
+    if (tid < r) Ru[tid] = r_pre;
+    for (int i = RP_THREADS + tid; i < r; i += RP_THREADS) Ru[i] = Rg[i];
   }
 
   // ---- Algorithm 1's S update for the whole chunk: add the column sums the attend kernel left in the accumulators ----
@@ -1729,7 +1753,18 @@ __global__ __launch_bounds__(RP_THREADS) void prefill_replay_kernel(Params p, in
     if (n_retained) n_retained[unit] = n_final;
   }
 
-  if constexpr (IN_LDS) {
+  if constexpr (HELD > 0) {
+#pragma unroll
+    for (int u = 0; u < HELD; ++u) {
+      const int x = u * RP_THREADS + tid, i = x / row_vec, e = x - i * row_vec;
+      const int slot = x < L * row_vec ? dest[i] : -1;
+      if (slot >= 0) {
+        const size_t dst = ((size_t)unit * cap + slot) * row_vec + e;
+        reinterpret_cast<uint4v_t*>(p.K)[dst] = k_held[u];
+        reinterpret_cast<uint4v_t*>(p.V)[dst] = v_held[u];
+      }
+    }
+  } else if constexpr (IN_LDS) {
     int* dest_g = p.pf_flag + (size_t)unit * (cap + p.max_chunk) + cap;
     for (int i = tid; i < L; i += RP_THREADS) dest_g[i] = dest[i];
   }
@@ -1758,16 +1793,24 @@ int launch_replay(const Params& p, const void* K, const void* V, int L, int32_t*
                   int32_t* evicted, hipStream_t s) {
   const size_t rp_lds = replay_lds_words(p.m, p.cap, p.n_recent, L) * sizeof(int);
   const int row_vec = p.D * (p.dtype == TREEKV_BF16 ? 2 : 4) / 16;
+  // Pieces of a unit's K rows per thread.  Beyond four, one workgroup's copies outlast the launch they save: 32 heads x 512
+  // tokens of head_dim 128 into 2048 slots 68.0 us a call with eight, 67.3 with the scatter kernel; the same of head_dim 64,
+  // four pieces, 47.9 and 50.0; 8 heads, 100 tokens into 1024 slots 20.9 and 22.6; 4 heads, 8 into 300 14.4 and 16.1.
+  constexpr int HELD_MAX = 4;
+  const int held = (int)(((size_t)L * row_vec + RP_THREADS - 1) / RP_THREADS);
   if (rp_lds <= 140 * 1024) {
-    auto replay = prefill_replay_kernel<true>;
+    auto replay = held <= 1 ? prefill_replay_kernel<true, 1> : held <= 2 ? prefill_replay_kernel<true, 2>
+                : held <= HELD_MAX ? prefill_replay_kernel<true, HELD_MAX>
+                : prefill_replay_kernel<true, 0>;
     if (rp_lds > 48 * 1024 &&
         hip_failed(hipFuncSetAttribute((const void*)replay, hipFuncAttributeMaxDynamicSharedMemorySize, (int)rp_lds)))
       return TREEKV_EHIP;
     hipLaunchKernelGGL(replay, dim3(p.U), dim3(RP_THREADS), rp_lds, s, p, L, (const uint4*)K, (const uint4*)V, row_vec,
                        retained, n_retained, evicted);
+    if (held <= HELD_MAX) return finish_launch();
   } else {
     if (2 * (size_t)L + 1 > (size_t)p.cap + p.max_chunk) return TREEKV_EUNSUPPORTED;   // its lists live in pf_list
-    hipLaunchKernelGGL(prefill_replay_kernel<false>, dim3(p.U), dim3(RP_THREADS), 0, s, p, L, (const uint4*)K,
+    hipLaunchKernelGGL((prefill_replay_kernel<false, 0>), dim3(p.U), dim3(RP_THREADS), 0, s, p, L, (const uint4*)K,
                        (const uint4*)V, row_vec, retained, n_retained, evicted);
   }
   hipLaunchKernelGGL(prefill_scatter_kernel, dim3((L + 256 / row_vec - 1) / (256 / row_vec), p.U), dim3(256), 0, s, p, (const uint4*)K, (const uint4*)V, L, row_vec);

@@ -120,6 +120,19 @@ def test_prefill_logits_in_registers(binding, oracle, d, rerank, G, budget, sche
          n_recent=budget // 3, max_chunk=512, seed=11, flags=flags, units=[(0, 1)])
 
 
+@pytest.mark.parametrize("d,dtype,schedule", [
+    (128, "bf16", [64, 65, 128, 129, 256, 257]),       # 16-byte pieces of a row times tokens around 1, 2 and 4 x 1024
+    (64, "bf16", [128, 129, 256, 257, 512, 511]),
+    (64, "f32", [64, 65, 128, 129, 256, 257]),
+    (128, "f32", [32, 33, 64, 65, 128, 129]),
+])
+def test_prefill_rows_copied_by_the_replay(binding, oracle, d, dtype, schedule):
+    """Chunk lengths around those at which a thread of the replay holds one more piece, or the scatter kernel takes over."""
+    kind = "lowrank" if dtype == "bf16" else "iid"
+    _run(binding, oracle, schedule, B=2, H=2, Hkv=2, d=d, budget=150, n_sink=2, n_recent=60, max_chunk=512, seed=3,
+         dtype=dtype, kind=kind, units=[(0, 1), (1, 0)])
+
+
 def test_prefill_argument_errors(binding):
     import torch
 
