@@ -10,7 +10,7 @@
 // through a small LDS tile as whole rows of the output.
 //
 //   wavelet_components_kernel   grid (ceil(t / 128), heads) x 256 threads -> per_head [heads][levels][t]
-//   wavelet_mean_kernel         grid ceil(levels * t / 32) x 1024 threads -> mean [levels][t], heads added in a fixed order
+//   wavelet_mean_kernel         a workgroup per 16 (32) outputs x 512 (1024) threads -> mean [levels][t], heads added in a fixed order
 
 #include "treekv_internal.h"
 
@@ -159,23 +159,31 @@ __global__ __launch_bounds__(WV_THREADS, sizeof(T) * D > 256 ? 2 : 6) void wavel
   }
 }
 
-// Mean over the heads: a workgroup owns 32 adjacent outputs (whole 128-byte lines) and adds up the heads of every output in
+// Mean over the heads: a workgroup owns 16 or 32 adjacent outputs and adds up the heads of every output in
 // an order that depends on nothing but `heads`: 128 head lanes take every 128th head each, eight lanes' sums go up a tree,
 // the 16 results are added one after the other.
 //   QUADS   a thread is one head lane of four outputs (16-byte loads), the tree is lane exchanges.
 //   else    (per_head not 16-byte aligned, or rows that are no whole groups of four outputs) a thread is four head lanes of
 //           one output, the tree goes through LDS.
-// Bound by the bytes a compute unit can have in flight (the grid is one workgroup per 32 outputs, 80 at 5 levels of 512):
-// with 16-byte loads, 16 of them per thread, 256 KB.  At 8192 heads 22 us (84 MB, most of it still in the memory-side cache,
-// because the components kernel reads V past it); 35 us with 4-byte loads, 31 us with 16 outputs (64-byte pieces of
-// a head's row) per workgroup.
-constexpr int MEAN_COLS = 32, MEAN_THREADS = 1024, MEAN_LANES = 128;
+// Bound by the bytes in flight and by what still is in the memory-side cache (the components kernel reads V past it): with
+// 16-byte loads, 16 of them per thread, and half a 128-byte line per workgroup, so that 5 levels of 512 give 160 of them, the
+// two halves of a line on one XCD.  A whole call at 8192 heads x 512: 206.1 us (207.9 with whole lines, 215.5 with quarters),
+// 64 wide 117.3 (120.0, 126.4), 64 heads x 96 7.2 (8.2, 6.9); the kernel alone took 35 us with 4-byte loads, 22 with whole lines.
+constexpr int MEAN_LANES = 128;
 template <bool QUADS>
-__global__ __launch_bounds__(MEAN_THREADS) void wavelet_mean_kernel(const float* __restrict__ per_head, int heads, int n,
+struct Mean {
+  static constexpr int COLS = QUADS ? 16 : 32, THREADS = MEAN_LANES * COLS / 4;
+  static constexpr int SHARE = 32 / COLS;            // workgroups that read the same 128-byte lines
+};
+template <bool QUADS>
+__global__ __launch_bounds__(Mean<QUADS>::THREADS) void wavelet_mean_kernel(const float* __restrict__ per_head, int heads, int n,
                                                                     float* __restrict__ mean) {
-  constexpr int GROUPS = MEAN_LANES / 8;
+  constexpr int GROUPS = MEAN_LANES / 8, MEAN_COLS = Mean<QUADS>::COLS, MEAN_THREADS = Mean<QUADS>::THREADS;
+  constexpr int SHARE = Mean<QUADS>::SHARE;
   __shared__ float red[GROUPS][MEAN_COLS];
-  const int tid = threadIdx.x, first = blockIdx.x * MEAN_COLS;
+  // workgroups are dealt to the 8 XCDs in turn: those that share lines get ids 8 apart, so one of them brings the line in
+  const int w = blockIdx.x, line = w / (8 * SHARE) * 8 + w % 8;
+  const int tid = threadIdx.x, first = line * 32 + w / 8 % SHARE * MEAN_COLS;
   if constexpr (QUADS) {
     constexpr int TX = MEAN_COLS / 4;
     const int tx = tid % TX, lane = tid / TX, i = first + tx * 4;
@@ -188,12 +196,12 @@ __global__ __launch_bounds__(MEAN_THREADS) void wavelet_mean_kernel(const float*
       }
     }
 #pragma unroll
-    for (int o = TX; o < 64; o <<= 1)
+    for (int o = TX; o < 8 * TX; o <<= 1)
 #pragma unroll
       for (int e = 0; e < 4; ++e) acc[e] += __shfl_xor(acc[e], o, 64);
-    if (tid % 64 < TX) {
+    if (tid % (8 * TX) < TX) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) red[tid / 64][tx * 4 + e] = acc[e];
+      for (int e = 0; e < 4; ++e) red[tid / (8 * TX)][tx * 4 + e] = acc[e];
     }
   } else {
     constexpr int STEP = MEAN_THREADS / MEAN_COLS;
@@ -250,8 +258,12 @@ int launch_wavelet(const float* a, const void* V, int dtype, int heads, int t, i
   if (mean) {
     const int n = levels * t;
     // 16-byte loads need whole groups of four outputs in every head's row
-    auto kern = n % 4 == 0 && (reinterpret_cast<uintptr_t>(per_head) & 15) == 0 ? wavelet_mean_kernel<true> : wavelet_mean_kernel<false>;
-    hipLaunchKernelGGL(kern, dim3((n + MEAN_COLS - 1) / MEAN_COLS), dim3(MEAN_THREADS), 0, s, per_head, heads, n, mean);
+    const int lines = (n + 31) / 32;
+    if (n % 4 == 0 && (reinterpret_cast<uintptr_t>(per_head) & 15) == 0)
+      hipLaunchKernelGGL(wavelet_mean_kernel<true>, dim3((lines + 7) / 8 * 8 * Mean<true>::SHARE), dim3(Mean<true>::THREADS), 0, s,
+                         per_head, heads, n, mean);
+    else
+      hipLaunchKernelGGL(wavelet_mean_kernel<false>, dim3((lines + 7) / 8 * 8), dim3(Mean<false>::THREADS), 0, s, per_head, heads, n, mean);
   }
   return finish_launch();
 }
