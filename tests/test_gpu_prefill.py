@@ -93,13 +93,67 @@ def test_prefill_len1_equals_decode(binding, oracle):
     assert (a.scores() - b.scores()).abs().max().item() < 1e-3
 
 
-@pytest.mark.parametrize("free", [127, 128, 129, 143, 255, 399])
+@pytest.mark.parametrize("budget,free", [(400, f) for f in (127, 128, 129, 143, 255, 399)] +
+                         [(2600, f) for f in (127, 128, 129, 143, 2559, 2560, 2575, 2599)])
 @pytest.mark.parametrize("d", [64, 128])
-def test_prefill_free_slot_at_a_tile_edge(binding, oracle, d, free):
-    """A full cache of 400 slots (three whole tiles and a part) whose free slot lies at the edge of a 128-column tile, of a
-    wave's 16 columns, or at the end: two tree slots, the right one of which the decode step frees (keep-left)."""
-    _run(binding, oracle, [400, 0, 130, 0, 64], B=1, H=2, Hkv=2, d=d, budget=400, n_sink=free - 1,
-         n_recent=400 - free - 1, max_chunk=400, seed=24, flags=binding.TREEKV_KEEP_LEFT)
+def test_prefill_free_slot_at_a_tile_edge(binding, oracle, d, budget, free):
+    """A full cache whose free slot lies at the edge of a 32-column block, of a 128-column tile or of a wave's 16 columns, in
+    the last, partial one, or at the end: two tree slots, the right one of which the decode step frees (keep-left).  400
+    slots: logits in registers, blocks of 32; 2600 slots, more than registers hold: two sweeps, tiles of 128."""
+    _run(binding, oracle, [budget, 0, 130, 0, 64], B=1, H=2, Hkv=2, d=d, budget=budget, n_sink=free - 1,
+         n_recent=budget - free - 1, max_chunk=budget, seed=24, flags=binding.TREEKV_KEEP_LEFT,
+         units=None if budget == 400 else [(0, 1)])
+
+
+@pytest.mark.parametrize("G,budget,n_sink,n_recent,schedule", [
+    (8, 72, 3, 20, [50, 90, 0, 128, 13]),              # fewer slots than a 128-column tile
+    (4, 130, 2, 40, [1, 63, 64, 65, 0, 127, 128]),     # row tiles of 64, a tile of the cache and two columns of the next
+    (2, 127, 0, 0, [127, 1, 129, 0, 33]),
+    (1, 400, 127, 271, [400, 0, 130, 0, 64]),          # the free slot at a tile's first column ..
+    (1, 400, 142, 256, [400, 0, 130, 0, 64]),          # .. and inside a wave's 16 (keep-left)
+])
+def test_prefill_two_sweeps_many_heads(binding, oracle, G, budget, n_sink, n_recent, schedule):
+    """320 query heads x 64: more row tiles than the kernel with its logits in registers is given at plain head_dim 64, so
+    every one of these small caches is swept twice."""
+    flags = binding.TREEKV_KEEP_LEFT if budget == 400 else 0
+    _run(binding, oracle, schedule, B=2, H=160, Hkv=160 // G, d=64, budget=budget, n_sink=n_sink, n_recent=n_recent,
+         max_chunk=max(schedule), seed=25, flags=flags, units=[(0, 0), (1, 160 // G - 1)])
+
+
+@pytest.mark.parametrize("d,G,flag", [(64, 1, 0), (64, 4, 0), (128, 2, 0), (64, 2, 8), (128, 1, 8)])
+def test_prefill_two_sweeps_ragged_chunks(binding, oracle, d, G, flag):
+    """Chunk lengths around the 64-row and 128-column tiles into a cache of 2600 slots, nearly empty, at its budget, evicting."""
+    assert flag in (0, binding.TREEKV_POSITION_RERANK)
+    _run(binding, oracle, [1, 63, 64, 65, 127, 0, 129, 191, 1901, 128, 63, 0, 65, 129, 1], B=1, H=2 * G, Hkv=2, d=d, budget=2600,
+         n_sink=3, n_recent=900, max_chunk=1901, seed=26, flags=flag, units=[(0, 1)])
+
+
+@pytest.mark.parametrize("G", [1, 4])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("rerank", [False, True])
+def test_prefill_both_attend_kernels_agree(binding, d, rerank, G):
+    """The same chunks into 520 slots (logits in registers) and into 2600 (two sweeps) while both fill.  What may differ: a
+    probability's exponent (below 2^8) is rounded to 2^-16, a few times that is 1e-4 of its value and of the scores, which
+    add them up; for the outputs, the halves of P leave out up to 2^-16 of a probability more on either side."""
+    import torch
+
+    lengths = [1, 31, 32, 33, 2, 63, 30, 129, 64, 100, 3, 32]
+    assert sum(lengths) == 520
+    Q, K, V = (ph.to_device(x, "bf16").transpose(0, 1) for x in
+               inputs.batch_streams("lowrank", 27, 520, 2, 3, G, d, dtype="bf16"))
+    flags = binding.TREEKV_POSITION_RERANK if rerank else 0
+    small, large = (binding.TreeKV(c, 3 * G, d, kv_heads=3, batch=2, dtype="bf16", n_sink=2, n_recent=100, max_chunk=129,
+                                   flags=flags) for c in (520, 2600))
+    at = 0
+    for n in lengths:
+        x = [t[:, at:at + n].contiguous() for t in (Q, K, V)]
+        a, b = small.new_outputs(n), large.new_outputs(n)
+        small.prefill_chunk(*x, n, *a)
+        large.prefill_chunk(*x, n, *b)
+        at += n
+        err = (a[0] - b[0]).abs().max().item()
+        assert err <= V.abs().max().item() * (1e-4 + 2.0 ** -15), (n, err)
+        torch.testing.assert_close(small.scores()[..., :at], large.scores()[..., :at], rtol=1e-4, atol=1e-9)
 
 
 @pytest.mark.parametrize("d,rerank,G,budget,schedule", [

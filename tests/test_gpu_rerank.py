@@ -170,13 +170,16 @@ def test_rerank_chunks_pure_algorithm1_many_tiles(binding, oracle):
             max_chunk=300, seed=64)
 
 
-@pytest.mark.parametrize("free", [127, 128, 129, 143, 255, 399])
+@pytest.mark.parametrize("budget,free", [(400, f) for f in (127, 128, 129, 143, 255, 399)] +
+                         [(2600, f) for f in (127, 128, 129, 143, 2559, 2560, 2575, 2599)])
 @pytest.mark.parametrize("d", [64, 128])
-def test_rerank_chunks_free_slot_at_a_tile_edge(binding, oracle, d, free):
-    """A full cache of 400 slots (three whole tiles and a part) whose free slot lies at the edge of a 128-column tile, of a
-    wave's 16 columns, or at the end: two tree slots, the right one of which the decode step frees (keep-left)."""
-    _chunks(binding, oracle, [400, 0, 130, 0, 64], B=1, H=2, Hkv=2, d=d, budget=400, n_sink=free - 1,
-            n_recent=400 - free - 1, max_chunk=400, seed=68, flags=binding.TREEKV_KEEP_LEFT)
+def test_rerank_chunks_free_slot_at_a_tile_edge(binding, oracle, d, budget, free):
+    """A full cache whose free slot lies at the edge of a 32-column block, of a 128-column tile or of a wave's 16 columns, in
+    the last, partial one, or at the end: two tree slots, the right one of which the decode step frees (keep-left).  400
+    slots: logits in registers, blocks of 32; 2600 slots, more than registers hold: two sweeps, tiles of 128."""
+    _chunks(binding, oracle, [budget, 0, 130, 0, 64], B=1, H=2, Hkv=2, d=d, budget=budget, n_sink=free - 1,
+            n_recent=budget - free - 1, max_chunk=budget, seed=68, flags=binding.TREEKV_KEEP_LEFT,
+            units=None if budget == 400 else [(0, 1)])
 
 
 def test_rerank_chunk_of_one_token_equals_decode(binding, oracle):
