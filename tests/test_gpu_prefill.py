@@ -298,12 +298,18 @@ def test_prefill_fp32_non_finite_rows_stay_their_own(binding, d, n0):
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("rerank", [False, True])
 @pytest.mark.parametrize("rise", [0, 20, 40, 60, 100])
-def test_prefill_rows_whose_logits_rise(binding, d, rerank, rise):
+@pytest.mark.parametrize("budget", [512, 2600])
+def test_prefill_rows_whose_logits_rise(binding, d, rerank, rise, budget):
     """Keys of the second tile lie `rise` (in log2) above those of the first: what a row's sums are taken against changes
-    on the way (or, up to 2^16, does not).  One query per head, so a token's score is its probability, and a head's
-    scores add up to one but for the error of the normaliser log2(sum).  Bound, in log2 units: log2(sum) <= 8 is
-    rounded twice (2 * 2^-22, and the same for its own instruction), times ln 2 = 6e-7; the sums' own rounding is some
-    2^-23.  A reference left 40 or 60 below the logits rounds log2(sum) and the exponentials' arguments to 2^-19."""
+    on the way.  One query per head, so a token's score is its probability, and a head's scores add up to one but for the
+    error of the normaliser.
+    2600 slots, two sweeps: the reference is raised at 2^16 only, the normaliser is log2(sum).  Bound, in log2 units:
+    log2(sum) <= 8 is rounded twice (2 * 2^-22, and the same for its own instruction), times ln 2 = 6e-7; the sums' own
+    rounding is some 2^-23.  A reference left 40 or 60 below the logits rounds log2(sum) and the exponentials' arguments to
+    2^-19.
+    512 slots, logits in registers: every block of 32 columns has its own reference and is brought to the row's by one
+    exponential, its part of the sum by up to three (from block to block, between the lanes and between the waves), then
+    1/sum: five roundings of 2^-23 beside those of the sums, 7e-7."""
     import torch
 
     H, n0 = 64, 256
@@ -317,11 +323,11 @@ def test_prefill_rows_whose_logits_rise(binding, d, rerank, rise):
     Q[..., d - 2] = 8
     V = torch.randn(1, n0 + 1, H, d, device="cuda", generator=g).to(torch.bfloat16)
     scale = 0.7                                               # (not ln 2: with it the exponents would be exact)
-    kv = binding.TreeKV(512, H, d, kv_heads=H, n_sink=2, n_recent=8, softmax_scale=scale, rope_base=1e38,
+    kv = binding.TreeKV(budget, H, d, kv_heads=H, n_sink=2, n_recent=8, softmax_scale=scale, rope_base=1e38,
                         flags=binding.TREEKV_POSITION_RERANK if rerank else 0)
     kv.prefill_chunk(Q[:, :n0].contiguous(), K[:, :n0].contiguous(), V[:, :n0].contiguous(), n0, *kv.new_outputs(n0))
     snap, lay = kv.export_state(), kv.state_layout()
-    snap[lay.S:lay.S + H * 512 * 4] = 0
+    snap[lay.S:lay.S + H * budget * 4] = 0
     kv.import_state(snap)
     out = kv.new_outputs(1)
     kv.prefill_chunk(Q[:, n0:].contiguous(), K[:, n0:].contiguous(), V[:, n0:].contiguous(), 1, *out)
