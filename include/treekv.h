@@ -180,6 +180,9 @@ int treekv_decode_step_static(treekv_ctx* ctx, const void* q, const void* k, con
  * With bf16 storage the two contractions run on the bf16 matrix instructions; with fp32
  * storage on the fp32 ones (held to 1e-5), for at most
  * 10240 visible columns (budget + 1 + len; TREEKV_EUNSUPPORTED beyond).
+ * Identical calls repeat bit for bit, but the kernel is chosen by the sizes of the whole call, as the number of a
+ * decode step's slices is (kv_splits = 0): the same sequence alone and in a batch may differ in the last bits of
+ * its outputs and scores, and so in which token of an all but exact tie it evicts.
  */
 int treekv_prefill_chunk(treekv_ctx* ctx, const void* Q, const void* K, const void* V, int len,
                          void* out, int32_t* retained, int32_t* n_retained, int32_t* evicted,

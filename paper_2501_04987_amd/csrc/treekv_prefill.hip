@@ -12,8 +12,9 @@
 //            (hi + lo) so that rounding P costs 2^-16, not 2^-9, and the probabilities' sums down the
 //            workgroup's rows.  Writes O; the column sums go, as 64-bit fixed point, into one accumulator
 //            per column of the unit with integer atomic adds (which commute exactly: whatever order the
-//            workgroups arrive in, the sum is the same to the bit).  Up to 2560 visible columns a workgroup of 32
-//            rows keeps their logits in registers and passes over the columns once.
+//            workgroups arrive in, the sum is the same to the bit).  Up to 2560 visible columns (and, at
+//            plain head_dim 64, while row tiles are few) a workgroup of 32 rows keeps their logits in registers and passes
+//            over the columns once.
 //   replay   grid U.  Adds the accumulated column sums to the scores (Algorithm 1's S update) and clears the
 //            accumulators, then Algorithm 1's eviction for the chunk's tokens with frozen scores.  Inside one
 //            sweep of idx over the tree region the scopes are disjoint pairs, so a sweep is one
@@ -779,14 +780,15 @@ __global__ __launch_bounds__(AT_THREADS, D == 64 && !ROPE ? 4 : 2) void prefill_
 //            transposing reads of V fetch them in); P is split into two bf16 halves as above.
 //   sums     of a block's columns over the 32 rows stay inside the wave and go straight to the unit's accumulators.
 // A wave reads only what it requested itself, two blocks ahead, so the blocks take no barrier.  Lane-dependent addresses
-// are worked out anew where they are used: held, they would spill (256 registers, all of them taken at the last block).
+// are worked out anew where they are used: held, they would spill at head_dim 128 (255 registers of 256 are in use there, 256
+// with ROPE; 227 at head_dim 64).
 //
 // Bound by the vector ALU's issue (a block costs a wave some 440 cycles of it for the logits and 500 for O, the products
 // of which take 270 and 550 of the matrix pipe) and by the path from L2: a workgroup takes in every K and V row, 604 MB
 // for 512 tokens into 2048 slots at 32 heads, 5.3 us for a workgroup's keys alone, where 8.3 are measured with the
 // arithmetic and 5.0 for the arithmetic alone; for O 5.0, 9.6 and 8.1.  Starting up, merging and writing out take 7 us of a
-// workgroup's 26, which is why short chunks gain most: one sequence of 8 KV heads, 100 tokens into 1024 slots, 38.4 ->
-// 22.6 us a call; 32 heads, 32 into 2048, 53.2 -> 31.2; 512 into 2048 72 -> 65, with re-assigned positions 112 -> 95.
+// workgroup's 26, which is why short chunks gain most: one sequence of 8 KV heads, 100 tokens into 1024 slots, 38.9 ->
+// 23.0 us a call; 32 heads, 32 into 2048, 53.4 -> 31.6; 512 into 2048 71.4 -> 66.1, with re-assigned positions 110.3 -> 94.3.
 // Measured and not kept: v_dot2 for the remainder of the split (it runs on the matrix pipe: 5 % longer), twelve waves of
 // seven blocks at head_dim 64 (no change), wave priorities around the products or by wave (no change).
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
@@ -1538,7 +1540,8 @@ __global__ __launch_bounds__(RP_THREADS) void prefill_replay_kernel(Params p, in
     a_pre[u] = acc[min(x, cap - 1)];
     n_pre[u] = acc[cap_cols + min(x, L - 1)];
   }
-  // The order arrays are read whole, dead entries too: which are live hangs on a bookkeeping word, one round trip more.
+  // The order arrays are read whole, dead entries too: which are live hangs on a bookkeeping word, one round trip more (32 heads,
+  // 512 tokens into 2048 slots 66.1 -> 65.1 us a call; short chunks the same, 8 heads, 100 into 1024 23.0).
   constexpr int PRE_E = 4;
   int e_pre[PRE_E], pe_pre[PRE_E], r_pre = 0;
   if constexpr (IN_LDS) {
@@ -1795,7 +1798,8 @@ int launch_replay(const Params& p, const void* K, const void* V, int L, int32_t*
   const int row_vec = p.D * (p.dtype == TREEKV_BF16 ? 2 : 4) / 16;
   // Pieces of a unit's K rows per thread.  Beyond four, one workgroup's copies outlast the launch they save: 32 heads x 512
   // tokens of head_dim 128 into 2048 slots 68.0 us a call with eight, 67.3 with the scatter kernel; the same of head_dim 64,
-  // four pieces, 47.9 and 50.0; 8 heads, 100 tokens into 1024 slots 20.9 and 22.6; 4 heads, 8 into 300 14.4 and 16.1.
+  // four pieces, 49.1 and 50.1; of head_dim 128, 8 heads, 100 tokens into 1024 slots 21.3 and 23.0; 4 heads, 8 into 300 14.6
+  // and 16.2.
   constexpr int HELD_MAX = 4;
   const int held = (int)(((size_t)L * row_vec + RP_THREADS - 1) / RP_THREADS);
   if (rp_lds <= 140 * 1024) {
@@ -1830,8 +1834,14 @@ int launch_prefill_d(const Params& p, const void* Q, const void* K, const void* 
   }
   // Logits in registers where a workgroup's fit: the fixed part of the call is shorter by far and the keys are multiplied once.
   // Plain head_dim 64, where four waves of the two-sweep kernel share a SIMD, only while that leaves compute units idle or
-  // nearly so (us a call, two sweeps / registers, 512 tokens into 2048 slots: 16 heads 51 / 31, 32 heads 53 / 48, 48 heads
-  // 73 / 67, 64 heads 73 / 76; 256 heads: 32 tokens 51 / 43, 64 tokens 53 / 57).
+  // nearly so: one 32-row workgroup for each of the 256, or up to three where long chunks make their lengths uneven.  us a call,
+  // two sweeps / registers, 512 tokens into 2048 slots: 24 heads 52 / 45, 32 heads 54 / 49, 48 heads 73 / 63, 64 heads 76 / 76,
+  // 128 heads 134 / 143; 256 heads: 32 tokens 40 / 25, 64 tokens 42 / 41, 100 tokens 62 / 70.  The number of slots changes how
+  // much is won, not by which: over 16 to 2048 slots, 8 to 1024 heads and 8 to 2000 tokens the ratio of the two is 0.97 to 1.95
+  // at head_dim 128 (below 1 by 1-3 % for some calls of 2000 row tiles and more), 1.01 to 2.0 with re-assigned positions, and at
+  // plain head_dim 64 1.14 to 1.8 up to 256 row tiles, 0.99 to 1.36 up to 768, and beyond, where two sweeps are kept, 0.75 to 1.0
+  // (1.2 for the shortest chunks).
+  // The row tiles are those of the whole call, so at plain head_dim 64 a sequence's last bits can depend on how many share it.
   const int res_tiles = (L + RES_ROWS - 1) / RES_ROWS, res_items = res_tiles * p.G * p.U;
   const bool resident = (p.budget + 31) / 32 + (L + 31) / 32 <= RES_WAVES * RES_BLOCKS &&
                         (D == 128 || rope || res_items <= 256 || (res_items <= 768 && res_tiles >= 4));

@@ -167,8 +167,9 @@ __global__ __launch_bounds__(WV_THREADS, sizeof(T) * D > 256 ? 2 : 6) void wavel
 //           one output, the tree goes through LDS.
 // Bound by the bytes in flight and by what still is in the memory-side cache (the components kernel reads V past it): with
 // 16-byte loads, 16 of them per thread, and half a 128-byte line per workgroup, so that 5 levels of 512 give 160 of them, the
-// two halves of a line on one XCD.  A whole call at 8192 heads x 512: 206.1 us (207.9 with whole lines, 215.5 with quarters),
-// 64 wide 117.3 (120.0, 126.4), 64 heads x 96 7.2 (8.2, 6.9); the kernel alone took 35 us with 4-byte loads, 22 with whole lines.
+// two halves of a line on one XCD.  A whole call at 8192 heads x 512: 207-210 us (209-213 with whole lines), 64 wide 115.8
+// (118.0), 64 heads x 96 5.4 (5.4); quarters of a line were slower than whole ones (215.5 and 210.6, 64 wide 126.4 and 120.0).
+// The kernel alone took 35 us with 4-byte loads, 22 with whole lines, 20 now.
 constexpr int MEAN_LANES = 128;
 template <bool QUADS>
 struct Mean {
